@@ -1,0 +1,957 @@
+// PQ convolution as an implicit GEMM on the fp16 matrix cores, with the
+// weights rebuilt from the sub-codebooks.
+//
+// Paper: Sec. 3.2, Eq. (7).  The sum over subspaces and kernel positions of
+// < D^(m)_{k_m(c_t, p_k)}, S^(m)_{p_s} > is the dense correlation with the
+// weights W[c_t][m C'_s + j][p_k] = D^(m)_{k_m(c_t, p_k)}[j] (Eq. (6)).  The
+// table form trades C'_s multiply-adds for one table read; on this machine a
+// table read costs 4 bytes of LDS bandwidth per output (at best 131 TB/s =
+// 3.3e13 reads/s, 2.4e13 reached), while the matrix cores do 1.2e15 fp16
+// multiply-adds per second.  With the three products per multiply-add below
+// that is 4e14, twelve times the read rate, so up to C'_s = 8 the products
+// win wherever the layer fills the tiles.
+//
+// Precision.  Each fp32 factor v is scaled by a power of two and split into
+// two fp16 values, v 2^e = h + l 2^-11 (round to nearest: h has 11 bits, l
+// the next 11 or more, |v 2^e - h - l 2^-11| <= 2^-24 |v 2^e|).  A product is
+// h h' + (h l' + l h') 2^-11, the left-out l l' being below 2^-24 of it; the
+// MFMA adds the exact fp16 products in fp32.  h h' and the cross terms have
+// accumulators of their own, so that scaling l by 2^11 keeps it out of the
+// fp16 subnormals: a factor keeps its 22 bits down to 2^-28 of the largest
+// one, and its absolute error below that is 2^-51 of the largest one.  A
+// workgroup whose inputs (or a layer whose codewords) span more than that --
+// the largest of 8 neighbouring channels, or of a codeword, below 2^-26 to
+// 2^-29 of the largest value -- or hold an infinity, a NaN or values near the
+// ends of the fp32 range repeats its tile with fp32 MFMA on the unsplit
+// values.
+//
+// Work.  A tile is 128 output channels (64 where the layer has no more) x 96
+// output positions; its reduction runs over units (chunk of 16 SUB input
+// channels, kernel tap, 16 channels).  Two workgroups run per CU, so that
+// one's start, scale exchange and stores hide behind the other's products.
+// Each makes the same number of whole tiles; the tiles left over are cut into
+// equal pieces at any unit, whose sums a second kernel adds in run order.
+//
+// Within a workgroup the 4 waves are TW channel groups of 32 x KG reduction
+// groups: a wave owns 32 channels x 96 positions (v_mfma_f32_32x32x16_f16) and
+// every KG-th unit.  Its 144 accumulator registers are what sets the tile: the
+// products' chain, the chains folded (below) and the cross terms.  The weight
+// operands come from memory in the order the instruction reads them, three
+// units ahead (a wave reads only its own channels: nothing is loaded twice by
+// a workgroup).  The input is staged in LDS chunk by chunk, [grid
+// position][channel] with zero halos, so that a tap is one constant shift of
+// the lanes' rows; the fp32 -> fp16 split happens on the way into LDS,
+// double-buffered behind the previous chunk's products.
+//
+// Bound and measured (MI355X).  With no staging at all the kernel takes 0.78
+// of its time (VGG conv3 shape, 16 x 256 x 56 x 56 -> 256, 3x3: 194 -> 156 us with
+// 128-position tiles), without weight loads 0.97, without LDS reads 1.0; the
+// matrix cores are busy about half the time at the 1.96 GHz they run at under
+// this load.  The rest is each tile's start (scale exchange and first loads,
+// 5 us) and end (2 us).  Against the table kernels, through a plan: AlexNet
+// conv3 shape, 32 images: 84 -> 47 us; conv2 with its max-pool, 37 images: 307 ->
+// 122 us; VGG conv3 shape per call: 273 -> 219 us (0.27 of the fp16 peak).  One
+// workgroup of 8 waves per CU instead of two of 4: 55 us, 252 us; 128-position tiles without the fold: 51 us, 207 us at
+// up to 1.4 times the table kernel's error.
+#include <stdio.h>
+#include <stdlib.h>
+
+#include "qcnn_internal.h"
+
+namespace qcnn {
+
+// Division of n < 2^31 by a divisor fixed on the host: n / d = (n m) >> 32 >> s
+// with m = ceil(2^(32 + s) / d), s = ceil(log2 d) - 1 (d = 1: m unused).
+struct FastDiv {
+  uint32_t d, m, s;
+  FastDiv() = default;
+  explicit FastDiv(uint32_t d_) : d(d_), m(0), s(0) {
+    if (d < 2) return;
+    while ((2u << s) < d) ++s;
+    m = (uint32_t)(((((uint64_t)1 << (32 + s)) + d - 1) / d));
+  }
+  __device__ __forceinline__ int div(int n) const { return d < 2 ? n : (int)(__umulhi((uint32_t)n, m) >> s); }
+};
+
+struct DenseParams {
+  int N, Cs, H, W, M, K, Csp, Ct, dk, stride, pad, Ho, Wo;
+  int S, sw;        // column strips per image, output columns per strip
+  int PW, PH;       // staged grid: positions per row, rows per (image, strip)
+  int ss, gs;       // grid positions per output step, input positions per grid step
+  int Q;            // output slots N S Ho sw
+  int SUB;          // 16-channel groups per chunk
+  int chunks, taps, upt;  // chunks and units (chunk, tap, 16 channels) of a tile
+  int tblocks, tiles, groups;
+  int whole, shared0;  // tiles that each run makes alone; first of the shared tiles, cut at any unit
+  int sruns;           // runs that take a piece of the shared tiles' units
+  int rows;         // staged grid positions per tile, a multiple of 64
+  int pitch;        // bytes per staged position
+  int relu;
+  int per_run, extra;  // shared units per run; the first `extra` runs have one more
+  FastDiv d_sw, d_Ho, d_S, d_PW, d_PH, d_upt, d_upc, d_SUB, d_dk, d_tb;
+};
+
+namespace {
+
+constexpr int kThreads = 256;
+constexpr int kWaves = kThreads / kWave;  // two workgroups per CU
+constexpr int kNT = 96;  // positions per tile
+constexpr int kCF = kNT / 32;
+constexpr int kSumStride = kNT + 8;  // floats per channel of a tile's sums in LDS
+constexpr int kCUs = 256;
+constexpr int kFold = 9;
+constexpr uint32_t kOOB = 0x80000000u;  // buffer offset past every input: reads 0
+
+typedef _Float16 h8 __attribute__((ext_vector_type(8)));
+typedef float f4v __attribute__((ext_vector_type(4)));
+typedef float f16v __attribute__((ext_vector_type(16)));
+
+// Header of a layer's dense weights: the power of two they are scaled by and
+// whether they must be used unsplit (fp32).
+struct DenseHead {
+  int scale_exp;
+  int f32;
+};
+constexpr size_t kHeadBytes = 256;
+
+// First shared unit of run w, and the run that holds shared unit u.
+__host__ __device__ inline int run_begin(const DenseParams& p, int w) {
+  w = w < p.sruns ? w : p.sruns;
+  return w * p.per_run + (w < p.extra ? w : p.extra);
+}
+__device__ inline int run_of(const DenseParams& p, int u) {
+  const int big = p.extra * (p.per_run + 1);
+  return u < big ? u / (p.per_run + 1) : p.extra + (u - big) / p.per_run;
+}
+
+__device__ __forceinline__ uint32_t wave_max(uint32_t v) {
+#define QCNN_STEP(ctrl, rm) v = max(v, (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, ctrl, rm, 0xf, false));
+  QCNN_STEP(0x111, 0xf) QCNN_STEP(0x112, 0xf) QCNN_STEP(0x114, 0xf) QCNN_STEP(0x118, 0xf)
+  QCNN_STEP(0x142, 0xa) QCNN_STEP(0x143, 0xc)
+#undef QCNN_STEP
+  return (uint32_t)__builtin_amdgcn_readlane((int)v, 63);
+}
+
+// Exponent that brings a largest magnitude (fp32 bits of |v|) to 2^12 .. 2^13,
+// leaving two bits for later chunks to grow; 0 for an all-zero input.
+__device__ __forceinline__ int scale_for(uint32_t maxbits) { return maxbits ? 12 - ((int)(maxbits >> 23) - 127) : 0; }
+
+// Magnitudes whose scaling stays inside the normal fp32 range.
+__device__ __forceinline__ bool scalable(uint32_t maxbits) {
+  return maxbits == 0 || (maxbits >= (27u << 23) && maxbits < (227u << 23));
+}
+
+struct Ptrs {
+  const float* x;
+  const float* D;
+  const char* w;      // head, then weights [channel group of 32][unit][step 2][hi, lo][lane][8] fp16
+  CodeStream codes;   // for the fp32 form
+  const float* bias;
+  float* y;
+  float* partial;     // [2 per run][MT][kNT]
+};
+
+// The kernel's parameters, read again from the kernel argument segment: an
+// opaque copy of its address keeps the compiler from holding every parameter
+// of every phase in scalar registers throughout (184 of them spilled).
+struct Args {
+  Ptrs g;
+  DenseParams p;
+};
+typedef const __attribute__((address_space(4))) Args* ArgsPtr;
+__device__ __forceinline__ const Args& args_again() {
+  ArgsPtr a = (ArgsPtr)__builtin_amdgcn_kernarg_segment_ptr();
+  asm volatile("" : "+s"(a));
+  return *(const Args*)a;
+}
+
+// One wave-wide set of 8 fp32 accumulator groups.
+struct Acc {
+  f16v a[kCF], c[kCF];  // h h' and cross terms since the last fold of a
+  f16v sum[kCF];        // a folded
+};
+
+// The weights of 8 channels for the fp32 form, decoded from the codes.
+__device__ __forceinline__ void decode8(const Ptrs& g, const DenseParams& p, int t, int tap, int ch0, float (&v)[8]) {
+#pragma unroll
+  for (int j = 0; j < 8; ++j) {
+    const int ch = ch0 + j;
+    v[j] = 0.f;
+    if (t < p.Ct && ch < p.Cs) {
+      const int m = ch / p.Csp;
+      uint32_t code = code_at(g.codes, ((size_t)t * p.taps + tap) * p.M + m);
+      code = min(code, (uint32_t)(p.K - 1));
+      v[j] = g.D[((size_t)m * p.K + code) * p.Csp + (ch - m * p.Csp)];
+    }
+  }
+}
+
+// Everything a workgroup keeps for one tile.
+template <int IT>
+struct TileState {
+  uint32_t voff[IT];    // byte offset in x of this lane's staged position (channel 0), or past the end
+  int rowb[kCF];        // LDS byte offset of the lane's output position in each 32-column group, tap (0, 0)
+};
+
+// The products of units [u0, u1) of one tile in split form.  Returns false
+// when that form does not hold the inputs' range.
+template <int TW, int IT>
+__device__ __forceinline__ bool products(const TileState<IT>& ts, int tgrp, int u0, int u1, char* lds,
+                                         uint32_t* exch, Acc& acc, int& x_exp) {
+  const Args& args = args_again();
+  const Ptrs& g = args.g;
+  const DenseParams& p = args.p;
+  constexpr int KG = kWaves / TW;
+  const int lane = threadIdx.x & (kWave - 1);
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
+  const int kg = wave / TW;
+  const int HW4 = p.H * p.W * 4;
+  const int upc = p.taps * p.SUB;  // units per chunk
+  const int buf_bytes = p.rows * p.pitch;
+  const int wgroups = p.rows >> 6;
+  const int vecs = 2 * p.SUB;
+  const __amdgpu_buffer_rsrc_t xres = __builtin_amdgcn_make_buffer_rsrc(
+      const_cast<float*>(g.x), 0, (int)((size_t)p.N * p.Cs * HW4), 0x00020000);
+
+#pragma unroll
+  for (int j = 0; j < kCF; ++j)
+#pragma unroll
+    for (int r = 0; r < 16; ++r) acc.a[j][r] = acc.c[j][r] = acc.sum[j][r] = 0.f;
+
+  // ---- input staging: wave item i = wave + 8 k is (64 positions, 8 channels):
+  // position group i % wgroups, channel group i / wgroups of the chunk.
+  // Channels past C_s hold 0: whole groups by an offset past the buffer, the
+  // rest of a last group after its load.
+  float xv[IT][8];
+  int ivec[IT], igrp[IT];
+#pragma unroll
+  for (int k = 0; k < IT; ++k) {
+    ivec[k] = (wave + kWaves * k) / wgroups;
+    igrp[k] = (wave + kWaves * k) - ivec[k] * wgroups;
+  }
+  auto load_chunk = [&](int chunk) {
+#pragma unroll
+    for (int k = 0; k < IT; ++k) {
+      const int ch0 = chunk * 16 * p.SUB + ivec[k] * 8;
+      const uint32_t off = ivec[k] < vecs && ch0 < p.Cs ? ts.voff[k] + (uint32_t)(ch0 * HW4) : kOOB;
+#pragma unroll
+      for (int j = 0; j < 8; ++j)
+        xv[k][j] = __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(xres, off + (uint32_t)(j * HW4), 0, 0));
+      if (ch0 < p.Cs && ch0 + 8 > p.Cs) {  // wave-uniform
+#pragma unroll
+        for (int j = 1; j < 8; ++j)
+          if (ch0 + j >= p.Cs) xv[k][j] = 0.f;
+      }
+    }
+  };
+  auto store_chunk = [&](char* buf, int e) {
+    const float s = __uint_as_float((uint32_t)(e + 127) << 23);
+#pragma unroll
+    for (int k = 0; k < IT; ++k) {
+      if (ivec[k] >= vecs) continue;  // wave-uniform
+      h8 hi, lo;
+#pragma unroll
+      for (int j = 0; j < 8; ++j) {
+        const float v = xv[k][j] * s;
+        hi[j] = (_Float16)v;
+        lo[j] = (_Float16)((v - (float)hi[j]) * 2048.f);
+      }
+      char* dst = buf + (igrp[k] * 64 + lane) * p.pitch + (ivec[k] >> 1) * 64 + (ivec[k] & 1) * 16;
+      *reinterpret_cast<h8*>(dst) = hi;
+      *reinterpret_cast<h8*>(dst + 32) = lo;
+    }
+  };
+  // Largest magnitude of the loaded values, and the smallest non-zero one of
+  // the per-thread maxima over 8 channels, exchanged over the workgroup.
+  // Two exchange buffers: a wave may publish again before the slowest one
+  // has read the last exchange.
+  int xb = 0;
+  auto publish = [&]() {
+    xb ^= 2 * kWaves;
+    uint32_t mx = 0, inv = 0;  // inv: ~(smallest non-zero maximum - 1)
+#pragma unroll
+    for (int k = 0; k < IT; ++k) {
+      uint32_t v = 0;
+#pragma unroll
+      for (int j = 0; j < 8; ++j) v = max(v, __float_as_uint(xv[k][j]) & 0x7fffffffu);
+      mx = max(mx, v);
+      inv = max(inv, ~(v - 1u));  // v = 0 gives 0
+    }
+    mx = wave_max(mx);
+    inv = wave_max(inv);
+    if (lane == 0) {
+      exch[xb + wave] = mx;
+      exch[xb + kWaves + wave] = inv;
+    }
+  };
+  // After the barrier that follows publish(): the scale for that chunk given
+  // the current one (kUnset before the first non-zero chunk); false when the
+  // split form does not hold it.
+  constexpr int kUnset = 1 << 20;
+  auto agree = [&](int& e) -> bool {
+    uint32_t mx = 0, inv = 0;
+#pragma unroll
+    for (int i = 0; i < kWaves; ++i) {
+      mx = max(mx, exch[xb + i]);
+      inv = max(inv, exch[xb + kWaves + i]);
+    }
+    mx = __builtin_amdgcn_readfirstlane(mx);
+    inv = __builtin_amdgcn_readfirstlane(inv);
+    if (mx == 0) return true;
+    if (!scalable(mx)) return false;
+    if ((int)(mx >> 23) - 127 + e > 14) e = scale_for(mx);
+    return (int)((~inv + 1u) >> 23) - 127 + e >= -14;
+  };
+
+  const int c_first = p.d_upc.div(u0), c_last = p.d_upc.div(u1 - 1);
+  int e = kUnset;
+  bool ok = true;
+  load_chunk(c_first);
+
+  // ---- weight operands: unit u of the tile at 2048 u, three of this wave's
+  // units in flight.  The loads run past the tile's last unit into the next
+  // group's weights or the padding after them.
+  int u = u0 + kg;  // this wave's next unit
+  const char* wp = g.w + kHeadBytes + ((size_t)tgrp * p.upt + u) * 2048;
+  h8 wh[3], wl[3];
+  auto load_w = [&](int slot) {
+    wh[slot] = *reinterpret_cast<const h8*>(wp + lane * 16);
+    wl[slot] = *reinterpret_cast<const h8*>(wp + lane * 16 + 1024);
+    wp += KG * 2048;
+  };
+  load_w(0);
+  load_w(1);
+  load_w(2);
+
+  publish();
+  __syncthreads();
+  ok = agree(e);
+  store_chunk(lds, e == kUnset ? 0 : e);
+  if (c_first < c_last) load_chunk(c_first + 1);
+
+  // The LDS rows of the wave's unit: (ky PW + kx) pitch + sub 64, kept by
+  // increments.
+  int sub, kx, off;
+  {
+    const int v = u - c_first * upc;
+    const int tap = p.d_SUB.div(v);
+    sub = v - tap * p.SUB;
+    const int ky = p.d_dk.div(tap);
+    kx = tap - ky * p.dk;
+    off = (ky * p.PW + kx) * p.pitch + sub * 64;
+  }
+  const int lane_k = (lane >> 5) * 16;
+  const int tap_step = p.pitch - p.SUB * 64, row_step = (p.PW - p.dk) * p.pitch;
+  int parity = 0;  // LDS buffer of the current chunk
+  int folded = 0;  // steps since the last fold
+
+  auto step = [&](int slot) {
+    const char* base = lds + parity * buf_bytes + off + lane_k;
+    h8 bh[kCF], bl[kCF];
+    auto read_b = [&](int j) {
+      bh[j] = *reinterpret_cast<const h8*>(base + ts.rowb[j]);
+      bl[j] = *reinterpret_cast<const h8*>(base + ts.rowb[j] + 32);
+    };
+    read_b(0);
+    read_b(1);
+#pragma unroll
+    for (int j = 0; j < kCF; ++j) {
+      acc.a[j] = __builtin_amdgcn_mfma_f32_32x32x16_f16(wh[slot], bh[j], acc.a[j], 0, 0, 0);
+      acc.c[j] = __builtin_amdgcn_mfma_f32_32x32x16_f16(wl[slot], bh[j], acc.c[j], 0, 0, 0);
+      if (j > 0) acc.c[j - 1] = __builtin_amdgcn_mfma_f32_32x32x16_f16(wh[slot], bl[j - 1], acc.c[j - 1], 0, 0, 0);
+      if (j + 2 < kCF) read_b(j + 2);
+      __builtin_amdgcn_sched_barrier(0);
+    }
+    acc.c[kCF - 1] = __builtin_amdgcn_mfma_f32_32x32x16_f16(wh[slot], bl[kCF - 1], acc.c[kCF - 1], 0, 0, 0);
+    __builtin_amdgcn_sched_barrier(0);
+    load_w(slot);
+    u += KG;
+#pragma unroll
+    for (int k = 0; k < KG; ++k) {
+      off += 64;
+      if (++sub == p.SUB) {
+        sub = 0;
+        off += tap_step;
+        if (++kx == p.dk) {
+          kx = 0;
+          off += row_step;
+        }
+      }
+    }
+    __builtin_amdgcn_sched_barrier(0);
+  };
+
+  for (int c = c_first; c <= c_last; ++c) {
+    // Loaded: chunk c + 1, one chunk ahead of its products.  Its scale is
+    // agreed on across the barrier that also hands over chunk c's LDS rows.
+    const bool more = c < c_last;
+    if (more) publish();
+    __syncthreads();
+    int e_next = e;
+    if (more) {
+      ok &= agree(e_next);
+      store_chunk(lds + (parity ^ 1) * buf_bytes, e_next == kUnset ? 0 : e_next);
+      if (c + 1 < c_last) load_chunk(c + 2);
+    }
+    const int u_end = min(u1, (c + 1) * upc);
+    while (u + 2 * KG < u_end) {
+      step(0);
+      step(1);
+      step(2);
+    }
+    while (u < u_end) {  // at most two
+      step(0);
+      const h8 th = wh[0], tl = wl[0];
+      wh[0] = wh[1];
+      wl[0] = wl[1];
+      wh[1] = wh[2];
+      wl[1] = wl[2];
+      wh[2] = th;
+      wl[2] = tl;
+    }
+    // The MFMA adds 8 products at a time: the running sum is rounded K / 8
+    // times.  Folding it into a second one every kFold units or more keeps the
+    // chains short (96 -> 256 channels, 5x5, 64 images, relative error against
+    // float64: 2.8e-7 -> 1.5e-7; the table kernel's is 2.1e-7).
+    folded += u_end - c * upc;
+    if (folded >= kFold * KG || c == c_last) {
+      folded = 0;
+#pragma unroll
+      for (int j = 0; j < kCF; ++j)
+#pragma unroll
+        for (int r = 0; r < 16; ++r) {
+          acc.sum[j][r] += acc.a[j][r];
+          acc.a[j][r] = 0.f;
+        }
+    }
+    if (e_next < e && e != kUnset) {  // larger inputs ahead: the sums take their scale
+      const float f = __uint_as_float((uint32_t)max(1, e_next - e + 127) << 23);
+#pragma unroll
+      for (int j = 0; j < kCF; ++j)
+#pragma unroll
+        for (int r = 0; r < 16; ++r) {
+          acc.a[j][r] *= f;
+          acc.c[j][r] *= f;
+          acc.sum[j][r] *= f;
+        }
+    }
+    e = e_next;
+    off -= p.dk * p.PW * p.pitch;  // from past the last tap to the next chunk's first
+    parity ^= 1;
+  }
+  __syncthreads();  // the sums overwrite the staged rows
+  x_exp = e == kUnset ? 0 : e;
+  return ok;
+}
+
+// The sums of units [u0, u1) of 32 channels x 32 positions in fp32, operands
+// straight from memory: the form for inputs or codewords whose range the
+// split one does not hold.  `plane0`, iy, ix: the lane's output position's
+// image plane and input coordinates at tap (0, 0); iy < -2^20: no position.
+__device__ __forceinline__ f16v products_f32(int tgrp, int u0, int u1, int n, int iy, int ix) {
+  const Args& args = args_again();
+  const Ptrs& g = args.g;
+  const DenseParams& p = args.p;
+  const int lane = threadIdx.x & (kWave - 1);
+  const int upc = p.taps * p.SUB;
+  f16v acc;
+#pragma unroll
+  for (int r = 0; r < 16; ++r) acc[r] = 0.f;
+  for (int u = u0; u < u1; ++u) {
+    const int c = p.d_upc.div(u), v = u - c * upc;
+    const int tap = p.d_SUB.div(v), sub = v - tap * p.SUB;
+    const int yy = iy + tap / p.dk, xx = ix + tap % p.dk;
+    const int ch0 = (c * p.SUB + sub) * 16 + (lane >> 5) * 8;
+    const bool in = yy >= 0 && yy < p.H && xx >= 0 && xx < p.W;
+    float av[8], bv[8];
+    decode8(g, p, tgrp * 32 + (lane & 31), tap, ch0, av);
+#pragma unroll
+    for (int j = 0; j < 8; ++j)
+      bv[j] = in && ch0 + j < p.Cs ? g.x[(((size_t)n * p.Cs + ch0 + j) * p.H + yy) * p.W + xx] : 0.f;
+#pragma unroll
+    for (int j = 0; j < 8; ++j) acc = __builtin_amdgcn_mfma_f32_32x32x2f32(av[j], bv[j], acc, 0, 0, 0);
+  }
+  return acc;
+}
+
+// Output slot q is (n, strip, yo, xl).
+struct Slot {
+  int n, yo, xo;  // image, output row and column
+  int grid;       // staged grid position at tap (0, 0)
+};
+__device__ __forceinline__ Slot slot_of(const DenseParams& p, int q) {
+  const int row = p.d_sw.div(q), xl = q - row * p.sw;
+  const int pl = p.d_Ho.div(row), yo = row - pl * p.Ho;
+  const int n = p.d_S.div(pl);
+  return {n, yo, (pl - n * p.S) * p.sw + xl, (pl * p.PH + yo * p.ss) * p.PW + xl * p.ss};
+}
+
+template <int TW, int IT>
+__global__ __launch_bounds__(kThreads, 2) void conv_dense_kernel(Args unused) {
+  extern __shared__ float4 smem4[];
+  constexpr int KG = kWaves / TW;
+  constexpr int MT = 32 * TW;
+  char* lds = reinterpret_cast<char*>(smem4);
+  const int lane = threadIdx.x & (kWave - 1);
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
+  const int tw = wave % TW, kg = wave / TW;
+
+  // Runs XCD-major: neighbouring runs (which share inputs) run on one XCD.
+  const int b = blockIdx.x;
+  const int groups = args_again().p.groups;
+  const int w = (b & 7) * ((groups + 7) >> 3) + (b >> 3);
+  if (w >= groups) return;
+  const int run_u0 = run_begin(args_again().p, w), run_u1 = run_begin(args_again().p, w + 1);
+  const DenseHead head = *reinterpret_cast<const DenseHead*>(args_again().g.w);
+
+  for (int i = 0, u = run_u0;;) {
+    const DenseParams& p = args_again().p;
+    uint32_t* exch = reinterpret_cast<uint32_t*>(lds + max(2 * p.rows * p.pitch, MT * kSumStride * 4));
+    int tile, a0 = 0, a1 = p.upt;  // units [a0, a1) of the tile
+    if (i < p.whole) {
+      tile = w * p.whole + i++;
+    } else if (u < run_u1) {
+      tile = p.d_upt.div(u);
+      a0 = u - tile * p.upt;
+      a1 = min(p.upt, run_u1 - tile * p.upt);
+      u += a1 - a0;
+      tile += p.shared0;
+    } else {
+      break;
+    }
+    const int ptile = p.d_tb.div(tile);
+    const int tb = tile - ptile * p.tblocks, q0 = ptile * kNT;
+
+    const int g0 = slot_of(p, q0).grid;
+    TileState<IT> ts;
+#pragma unroll
+    for (int j = 0; j < kCF; ++j) ts.rowb[j] = (slot_of(p, min(q0 + 32 * j + (lane & 31), p.Q - 1)).grid - g0) * p.pitch;
+    const int wgroups = p.rows >> 6;
+#pragma unroll
+    for (int k = 0; k < IT; ++k) {
+      const int f = g0 + ((wave + kWaves * k) % wgroups) * 64 + lane;
+      const int row = p.d_PW.div(f), c = f - row * p.PW;
+      const int pl = p.d_PH.div(row), n = p.d_S.div(pl);
+      const int iy = (row - pl * p.PH) * p.gs - p.pad, ix = (pl - n * p.S) * p.sw * p.stride + c * p.gs - p.pad;
+      const bool in = n < p.N && iy >= 0 && iy < p.H && ix >= 0 && ix < p.W;
+      ts.voff[k] = in ? (uint32_t)(n * p.Cs * p.H * p.W + iy * p.W + ix) * 4u : kOOB;
+    }
+
+    const int tgrp = tb * TW + tw;
+    float* sums = reinterpret_cast<float*>(lds);  // [channel][position], kSumStride floats per channel
+    // Row r of lane l is channel (r & 3) + 8 (r >> 2) + 4 (l >> 5) of the wave's
+    // 32, column l % 32 of a 32-position group: a store's two halves fall on
+    // different halves of the banks.
+    float* own = sums + (32 * tw + 4 * (lane >> 5)) * kSumStride + (lane & 31);
+    bool split_form = head.f32 == 0;
+    if (split_form) {
+      Acc acc;
+      int x_exp;
+      split_form = products<TW, IT>(ts, tgrp, a0, a1, lds, exch, acc, x_exp);
+      // The reduction groups' sums, added in group order.
+      const int ue = -(x_exp + head.scale_exp);
+      for (int k = 0; k < KG; ++k) {
+        if (k == kg) {
+#pragma unroll
+          for (int j = 0; j < kCF; ++j)
+#pragma unroll
+            for (int r = 0; r < 16; ++r) {
+              float* at = own + ((r & 3) + 8 * (r >> 2)) * kSumStride + 32 * j;
+              const float v = ldexpf(acc.sum[j][r] + acc.c[j][r] * (1.f / 2048.f), ue);
+              *at = k == 0 ? v : *at + v;
+            }
+        }
+        __syncthreads();
+      }
+    }
+    if (!split_form) {
+      __syncthreads();
+      for (int j = kg; j < kCF; j += KG) {
+        const int q = q0 + 32 * j + (lane & 31);
+        const DenseParams& p = args_again().p;
+        const Slot o = slot_of(p, q);
+        const f16v sum = products_f32(tgrp, a0, a1, o.n, q < p.Q ? o.yo * p.stride - p.pad : -(1 << 24),
+                                      o.xo * p.stride - p.pad);
+#pragma unroll
+        for (int r = 0; r < 16; ++r) own[((r & 3) + 8 * (r >> 2)) * kSumStride + 32 * j] = sum[r];
+      }
+      __syncthreads();
+    }
+    // ---- the tile, or this run's share of its sums, to memory
+    const Args& after = args_again();
+    const Ptrs& g = after.g;
+    const DenseParams& pe = after.p;
+    if (a0 != 0 || a1 != pe.upt) {
+      // A run and its shared tile both only grow along the units: their sum is
+      // a place of its own.
+      float* part = g.partial + (size_t)(w + tile - pe.shared0) * (MT * kNT);
+      for (int i = threadIdx.x; i < MT * kNT / 4; i += kThreads)
+        reinterpret_cast<f4v*>(part)[i] =
+            *reinterpret_cast<const f4v*>(sums + i / (kNT / 4) * kSumStride + i % (kNT / 4) * 4);
+    } else {
+      constexpr int kRows = kThreads / kNT;  // channels at a time
+      const int ql = threadIdx.x % kNT;
+      const Slot o = slot_of(pe, q0 + ql);
+      if (threadIdx.x < kRows * kNT && q0 + ql < pe.Q && o.xo < pe.Wo) {
+        const int t_end = min(pe.Ct - tb * MT, MT), HoWo = pe.Ho * pe.Wo;
+        float* dst = g.y + ((size_t)o.n * pe.Ct + tb * MT) * HoWo + o.yo * pe.Wo + o.xo;
+#pragma unroll 4
+        for (int t = threadIdx.x / kNT; t < t_end; t += kRows) {
+          float v = sums[t * kSumStride + ql] + (g.bias ? g.bias[tb * MT + t] : 0.f);
+          if (pe.relu) v = fmaxf(v, 0.f);
+          dst[(size_t)t * HoWo] = v;
+        }
+      }
+    }
+    __syncthreads();  // the next tile's staging overwrites the sums
+  }
+}
+
+// y of the tiles that several runs share: their partial sums added in run
+// order, bias, ReLU.  A workgroup takes the positions x 16 channels of one
+// tile; 8 channels per thread with every run's loads in flight.
+__global__ __launch_bounds__(2 * kNT) void dense_reduce_kernel(const float* __restrict__ partial, DenseParams p, int MT,
+                                                           const float* __restrict__ bias, float* __restrict__ y) {
+  const int tile = p.shared0 + blockIdx.x;
+  const int t_u0 = blockIdx.x * p.upt;
+  const int wf = run_of(p, t_u0), wl = run_of(p, t_u0 + p.upt - 1);
+  if (wf == wl) return;  // one run made the whole tile and stored it
+  const int tb = tile % p.tblocks, q = (tile / p.tblocks) * kNT + threadIdx.x % kNT;
+  const int tl = blockIdx.y * 16 + (int)(threadIdx.x / kNT) * 8;
+  const int row = q / p.sw, xl = q - row * p.sw;
+  const int pl = row / p.Ho, yo = row - pl * p.Ho;
+  const int n = pl / p.S, xo = (pl - n * p.S) * p.sw + xl;
+  if (q >= p.Q || xo >= p.Wo) return;
+  float s[8];
+#pragma unroll
+  for (int i = 0; i < 8; ++i) s[i] = 0.f;
+  for (int w = wf; w <= wl; ++w) {
+    const size_t slot = w + blockIdx.x;
+    const float* src = partial + slot * (MT * kNT) + tl * kNT + threadIdx.x % kNT;
+#pragma unroll
+    for (int i = 0; i < 8; ++i) s[i] += src[i * kNT];
+  }
+#pragma unroll
+  for (int i = 0; i < 8; ++i) {
+    const int t = tb * MT + tl + i;
+    if (t < p.Ct) {
+      float v = s[i] + (bias ? bias[t] : 0.f);
+      if (p.relu) v = fmaxf(v, 0.f);
+      y[(((size_t)n * p.Ct + t) * p.Ho + yo) * p.Wo + xo] = v;
+    }
+  }
+}
+
+// Scale and form of a layer's weights: one workgroup over the codebooks.
+__global__ __launch_bounds__(1024) void dense_head_kernel(const float* __restrict__ D, int codewords, int Csp,
+                                                          DenseHead* __restrict__ head) {
+  __shared__ uint32_t sm[2][16];
+  uint32_t mx = 0, inv = 0;
+  auto mag = [](float f) { return __float_as_uint(f) & 0x7fffffffu; };
+  auto take = [&](uint32_t v) {
+    mx = max(mx, v);
+    inv = max(inv, ~(v - 1u));
+  };
+  if (Csp % 4 == 0 && (reinterpret_cast<uintptr_t>(D) & 15) == 0) {  // a codeword is whole 16-byte loads
+    const int q = Csp >> 2;
+#pragma unroll 4
+    for (int i = threadIdx.x; i < codewords; i += 1024) {
+      uint32_t v = 0;
+      for (int j = 0; j < q; ++j) {
+        const f4v d = reinterpret_cast<const f4v*>(D)[(size_t)i * q + j];
+        v = max(max(v, max(mag(d[0]), mag(d[1]))), max(mag(d[2]), mag(d[3])));
+      }
+      take(v);
+    }
+  } else {
+    for (int i = threadIdx.x; i < codewords; i += 1024) {
+      uint32_t v = 0;
+      for (int j = 0; j < Csp; ++j) v = max(v, mag(D[(size_t)i * Csp + j]));
+      take(v);
+    }
+  }
+  mx = wave_max(mx);
+  inv = wave_max(inv);
+  if ((threadIdx.x & 63) == 0) {
+    sm[0][threadIdx.x >> 6] = mx;
+    sm[1][threadIdx.x >> 6] = inv;
+  }
+  __syncthreads();
+  if (threadIdx.x == 0) {
+    for (int i = 1; i < 16; ++i) {
+      mx = max(mx, sm[0][i]);
+      inv = max(inv, sm[1][i]);
+    }
+    const int e = mx ? scale_for(mx) + 2 : 0;
+    head->scale_exp = e;
+    head->f32 = !scalable(mx) || (mx && (int)((~inv + 1u) >> 23) - 127 + e < -14);
+  }
+}
+
+// The split weights in operand order: one thread writes the 8 channels of one
+// lane, hi and lo.
+__global__ __launch_bounds__(256) void dense_weights_kernel(const float* __restrict__ D, CodeStream codes,
+                                                            DenseParams p, int tgroups, char* __restrict__ w) {
+  const int total = tgroups * p.upt * kWave;  // < 2^31: kMaxWeights
+  const int e = reinterpret_cast<const DenseHead*>(w)->scale_exp;
+  const float sc = __uint_as_float((uint32_t)min(254, max(1, e + 127)) << 23);  // only used when it is exact
+  const int upc = p.taps * p.SUB;
+  for (int i = blockIdx.x * 256 + threadIdx.x; i < total; i += gridDim.x * 256) {
+    const int lane = i & 63, r = i >> 6;
+    const int tg = p.d_upt.div(r), u = r - tg * p.upt;
+    const int chunk = p.d_upc.div(u), v = u - chunk * upc;
+    const int tap = p.d_SUB.div(v), sub = v - tap * p.SUB;
+    const int t = tg * 32 + (lane & 31);
+    const int ch0 = (chunk * p.SUB + sub) * 16 + (lane >> 5) * 8;
+    h8 hi, lo;
+    int m_prev = -1;
+    uint32_t code = 0;
+#pragma unroll
+    for (int j = 0; j < 8; ++j) {
+      const int ch = ch0 + j;
+      float x = 0.f;
+      if (t < p.Ct && ch < p.Cs) {
+        const int m = ch / p.Csp;
+        if (m != m_prev) {
+          code = min(code_at(codes, ((size_t)t * p.taps + tap) * p.M + m), (uint32_t)(p.K - 1));
+          m_prev = m;
+        }
+        x = D[((size_t)m * p.K + code) * p.Csp + (ch - m * p.Csp)] * sc;
+      }
+      hi[j] = (_Float16)x;
+      lo[j] = (_Float16)((x - (float)hi[j]) * 2048.f);
+    }
+    h8* dst = reinterpret_cast<h8*>(w + kHeadBytes + (size_t)r * 2048 + lane * 16);
+    dst[0] = hi;
+    dst[64] = lo;
+  }
+}
+
+struct DensePlan {
+  DenseParams p;
+  int TW, IT;
+  size_t lds, weight_bytes, partial_bytes;
+};
+
+// Weights read ahead of a tile's last step: two steps of 4 groups.
+constexpr size_t kWeightTail = 8 * 2048;
+constexpr size_t kMaxWeights = (size_t)32 << 20;
+
+// Column strips and the staged window of a tile: the strips that waste few
+// slots past the row's end and keep the window, and so the staging, small;
+// past two workgroups' share of the LDS only one runs.
+bool set_window(const ConvShape& s, DenseParams* p) {
+  double best = 0;
+  p->rows = 0;
+  for (int S = 1; S <= 16 && S <= s.Wo; ++S) {
+    const int sw = ceil_div(s.Wo, S);
+    if ((S - 1) * sw >= s.Wo) continue;
+    int PH = (s.Ho - 1) * p->ss + s.dk, PW = (sw - 1) * p->ss + s.dk;
+    if (S == 1 && p->gs == 1) {  // neighbouring rows and images share their zero halos
+      PW -= std::min(s.pad, std::max(0, PW - s.pad - s.W));
+      PH -= std::min(s.pad, std::max(0, PH - s.pad - s.H));
+    }
+    // The grid span of kNT consecutive output slots: steps of `ss`, plus what
+    // a row end and an image end add.
+    const long long rc = (kNT - 1 + sw - 1) / sw, ic = (kNT - 1 + (long long)sw * s.Ho - 1) / ((long long)sw * s.Ho);
+    const long long span = (kNT - 1) * (long long)p->ss + rc * std::max(0, p->ss * PW - sw * p->ss) +
+                           ic * std::max(0, (PH - s.Ho * p->ss) * PW) + (long long)(s.dk - 1) * (PW + 1) + 1;
+    if (span > 4096) continue;
+    const int rows = (int)(span + 63) / 64 * 64;
+    const size_t bytes = (size_t)2 * rows * p->pitch;
+    if (bytes > kLdsBytes - 256) continue;
+    const double score = (double)S * sw / s.Wo * (1.0 + rows / 2560.0) * (bytes > kLdsBytes / 2 - 256 ? 1.5 : 1.0);
+    if (p->rows && score >= best) continue;
+    best = score;
+    p->S = S; p->sw = sw; p->PW = PW; p->PH = PH; p->rows = rows;
+  }
+  return p->rows != 0;
+}
+
+bool make_plan(const ConvShape& s, DensePlan* out) {
+  if ((long long)s.N * s.Cs * s.H * s.W * 4 > (1LL << 31) - 1) return false;  // 32-bit buffer offsets
+  DenseParams p{};
+  p.N = s.N; p.Cs = s.Cs; p.H = s.H; p.W = s.W; p.M = s.M; p.K = s.K; p.Csp = s.Csp; p.Ct = s.Ct;
+  p.dk = s.dk; p.stride = s.stride; p.pad = s.pad; p.Ho = s.Ho; p.Wo = s.Wo;
+  p.taps = s.dk * s.dk;
+  if (s.dk > 15 || s.pad >= s.dk) return false;
+  // The staged grid is the input's, or for 1x1 kernels only the positions that
+  // outputs read.
+  p.ss = s.dk == 1 ? 1 : s.stride;
+  p.gs = s.dk == 1 ? s.stride : 1;
+  // Chunks of more channels where there are few taps to reuse a staged row;
+  // fewer where the window's rows would not fit a thread's staging registers.
+  int items = 0;
+  for (p.SUB = p.taps == 1 ? 4 : p.taps <= 4 ? 2 : 1; p.SUB > 0; --p.SUB) {
+    if (p.SUB > 1 && 16 * (p.SUB - 1) >= s.Cs) continue;
+    p.pitch = 64 * p.SUB + 16;
+    if (!set_window(s, &p)) continue;
+    items = ceil_div(p.rows / 64 * 2 * p.SUB, kWaves);
+    if (items <= 4) break;
+  }
+  if (p.SUB == 0) return false;
+  p.chunks = ceil_div(s.Cs, 16 * p.SUB);
+  p.upt = p.chunks * p.taps * p.SUB;
+  const int TW = s.Ct <= 64 ? 2 : 4;
+  const size_t sums = (size_t)32 * TW * kSumStride * 4;
+  out->lds = std::max((size_t)2 * p.rows * p.pitch, sums) + 256;
+  if (out->lds > kLdsBytes) return false;
+  const long long slots = (long long)s.N * p.S * s.Ho * p.sw;
+  if (slots > (1LL << 30) || (long long)s.N * p.S * p.PH * p.PW + 8192 > (1LL << 31)) return false;
+  p.Q = (int)slots;
+  p.tblocks = ceil_div(s.Ct, 32 * TW);
+  const long long tiles = (slots + kNT - 1) / kNT * p.tblocks;
+  if (tiles * p.upt >= (1LL << 30)) return false;
+  p.tiles = (int)tiles;
+  out->weight_bytes = kHeadBytes + (size_t)p.tblocks * TW * p.upt * 2048 + kWeightTail;
+  if (out->weight_bytes > kMaxWeights) return false;
+  // Two runs per CU.  Each makes tiles / runs whole tiles; the tiles left over
+  // are cut into equal pieces of at least 16 units.  Fewer runs where the
+  // pieces' sums would not fit the allocation-free entry point's scratch.
+  const size_t tile_bytes = (size_t)32 * TW * kNT * sizeof(float);
+  const long long room = (long long)((noalloc_scratch_bytes() - 1024 - out->weight_bytes) / tile_bytes);
+  long long runs = 2 * kCUs, left = 0, pieces = 0;
+  for (; runs > 0; --runs) {
+    left = tiles % runs;
+    pieces = std::min(runs, std::max(left, left * p.upt / 16));
+    if (left == 0 || pieces + left <= room) break;
+  }
+  if (runs < 1) return false;
+  p.whole = (int)(tiles / runs);
+  p.shared0 = (int)(tiles - left);
+  p.sruns = (int)pieces;
+  p.groups = (int)(p.whole ? runs : pieces);
+  p.per_run = pieces ? (int)(left * p.upt / pieces) : 0;
+  p.extra = pieces ? (int)(left * p.upt % pieces) : 0;
+  out->partial_bytes = (size_t)(pieces + left) * tile_bytes;
+  p.d_sw = FastDiv(p.sw); p.d_Ho = FastDiv(p.Ho); p.d_S = FastDiv(p.S); p.d_PW = FastDiv(p.PW); p.d_PH = FastDiv(p.PH);
+  p.d_upt = FastDiv(p.upt); p.d_upc = FastDiv(p.taps * p.SUB); p.d_SUB = FastDiv(p.SUB); p.d_dk = FastDiv(p.dk);
+  p.d_tb = FastDiv(p.tblocks);
+  out->p = p;
+  out->TW = TW;
+  out->IT = std::max(2, items);
+  return true;
+}
+
+template <int TW, int IT>
+hipError_t launch_one(const DensePlan& pl, const Ptrs& g, hipStream_t stream, LaunchTimer* timer) {
+  auto k = conv_dense_kernel<TW, IT>;
+  hipError_t e = allow_max_lds((const void*)k);
+  if (e != hipSuccess) return e;
+  return timed_launch(timer, k, dim3((pl.p.groups + 7) / 8 * 8), dim3(kThreads), (uint32_t)pl.lds, stream, Args{g, pl.p});
+}
+
+hipError_t launch_main(const DensePlan& pl, const Ptrs& g, hipStream_t stream, LaunchTimer* timer) {
+  switch (pl.TW * 10 + pl.IT) {
+    case 42: return launch_one<4, 2>(pl, g, stream, timer);
+    case 43: return launch_one<4, 3>(pl, g, stream, timer);
+    case 44: return launch_one<4, 4>(pl, g, stream, timer);
+    case 22: return launch_one<2, 2>(pl, g, stream, timer);
+    case 23: return launch_one<2, 3>(pl, g, stream, timer);
+    default: return launch_one<2, 4>(pl, g, stream, timer);
+  }
+}
+
+hipError_t launch_weights(const DensePlan& pl, const float* D, CodeStream codes, char* w, hipStream_t stream) {
+  const DenseParams& p = pl.p;
+  hipLaunchKernelGGL(dense_head_kernel, dim3(1), dim3(1024), 0, stream, D, p.M * p.K, p.Csp,
+                     reinterpret_cast<DenseHead*>(w));
+  const long long threads = (long long)p.tblocks * pl.TW * p.upt * kWave;
+  hipLaunchKernelGGL(dense_weights_kernel, dim3((unsigned)std::min<long long>(4096, (threads + 255) / 256)), dim3(256),
+                     0, stream, D, codes, p, p.tblocks * pl.TW, w);
+  return hipGetLastError();
+}
+
+hipError_t run_dense(const DensePlan& pl, const Ptrs& g, hipStream_t stream, bool timed) {
+  hipError_t e;
+  {
+    LaunchTimer timer(timed);
+    e = launch_main(pl, g, stream, &timer);
+  }
+  const DenseParams& p = pl.p;
+  const int shared = p.tiles - p.shared0;
+  if (e == hipSuccess && shared > 0 && !(p.extra == 0 && p.per_run % p.upt == 0)) {
+    hipLaunchKernelGGL(dense_reduce_kernel, dim3(shared, 2 * pl.TW), dim3(2 * kNT), 0, stream, g.partial, p, 32 * pl.TW,
+                       g.bias, g.y);
+    e = hipGetLastError();
+  }
+  return e;
+}
+
+size_t up256(size_t b) { return (b + 255) & ~(size_t)255; }
+
+}  // namespace
+
+bool conv_dense_supported(const ConvShape& s) {
+  DensePlan pl;
+  if (!make_plan(s, &pl)) return false;
+  return true;
+}
+
+// Where the products are the better way.  `table_chain`: how many table
+// entries the layer's table kernel adds up one after the other (0: none can
+// tile it but the generic kernel).
+//   * Precision: the table kernels' relative error grows with the square root
+//     of that chain (9 to 18 entries 1.0e-7, 72 1.5e-7, 144 2.1e-7, 288
+//     3.1e-7), this one's stays at 1.2e-7 to 1.6e-7 from 500 to 5000 products:
+//     not larger from about 48 entries on.
+//   * Time: the generic table kernel is slower by a factor of 10 or more
+//     (256 channels 13 x 13, 3x3, K = 256, 8 images: 1841 us against 28 us).  Against
+//     the other two a call has about 6 us more to win back, in a layer of at
+//     least 1.5e8 multiply-adds for C's <= 4 (256 -> 384 channels, 3x3 on
+//     13 x 13: 26 -> 21 us for one image, 177 -> 84 us for 64) and twice that for
+//     C's <= 8, whose table reads do twice the work (512 -> 512 channels, 14 x 14:
+//     28 -> 26 us for one, 284 -> 204 us for 64); and a tile has to be long enough
+//     for its first and last microseconds: 256 products per output, with
+//     64 output channels or fewer 512 (a tile then stages twice the input per
+//     product: 32 -> 64 channels on 28 x 28, 64 images: 33 us against 35 us).
+bool conv_dense_better(const ConvShape& s, int table_chain) {
+  if (!conv_dense_supported(s)) return false;
+  const int products = s.Cs * s.dk * s.dk, entries = s.M * s.dk * s.dk;
+  if (table_chain == 0) return entries >= 48;
+  const double macs = (double)s.N * s.Ho * s.Wo * s.Ct * products;
+  return table_chain >= 48 && products >= (s.Ct <= 64 ? 512 : 256) && macs >= (s.Csp <= 4 ? 1.5e8 : 3e8);
+}
+
+size_t conv_dense_workspace(const ConvShape& s) {
+  DensePlan pl;
+  return make_plan(s, &pl) ? up256(pl.weight_bytes) + pl.partial_bytes : 0;
+}
+
+size_t conv_dense_weight_bytes(const ConvShape& s) {
+  DensePlan pl;
+  return make_plan(s, &pl) ? up256(pl.weight_bytes) : 0;
+}
+
+hipError_t launch_conv_dense_weights(const ConvShape& s, const float* D, CodeStream codes, char* w,
+                                     hipStream_t stream) {
+  DensePlan pl;
+  if (!make_plan(s, &pl)) return hipErrorInvalidConfiguration;
+  return launch_weights(pl, D, codes, w, stream);
+}
+
+hipError_t launch_conv_dense(const ConvShape& s, const float* x, const float* D, CodeStream codes, const char* w,
+                             const float* bias, int relu, float* y, hipStream_t stream, const Workspace* ws,
+                             const PoolSpec* pool) {
+  DensePlan pl;
+  if (!make_plan(s, &pl)) return hipErrorInvalidConfiguration;
+  pl.p.relu = relu;
+  const size_t wb = w ? 0 : up256(pl.weight_bytes), pb = up256(pl.partial_bytes);
+  const size_t full = pool ? (size_t)s.N * s.Ct * s.Ho * s.Wo * sizeof(float) : 0;
+  Scratch scratch;
+  hipError_t e = scratch.take(stream, wb + pb + full, ws);
+  if (e != hipSuccess) return e;
+  char* base = scratch.get();
+  if (!w) {
+    e = launch_weights(pl, D, codes, base, stream);
+    if (e != hipSuccess) return e;
+    w = base;
+  }
+  float* ymap = pool ? reinterpret_cast<float*>(base + wb + pb) : y;
+  const Ptrs g{x, D, w, codes, bias, ymap, reinterpret_cast<float*>(base + wb)};
+  e = run_dense(pl, g, stream, ws == nullptr || ws->timed);
+  if (e != hipSuccess || !pool) return e;
+  return launch_maxpool(ymap, s.N, s.Ct, s.Ho, s.Wo, pool->k, pool->s, pool->Hp, pool->Wp, y, stream);
+}
+
+}  // namespace qcnn

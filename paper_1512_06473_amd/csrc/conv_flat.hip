@@ -946,6 +946,11 @@ size_t conv_flat_workspace(const ConvShape& s) {
   return make_plan(s, &pl) ? flat_ws(pl).total : 0;
 }
 
+int conv_flat_chain(const ConvShape& s) {
+  FlatPlan pl;
+  return make_plan(s, &pl) ? pl.p.v_per_split * pl.rows * pl.cols : 0;
+}
+
 bool conv_flat_pools(const ConvShape& s) {
   FlatPlan pl;
   return make_plan(s, &pl) && pl.p.splits > 1 && s.Ho * s.Wo <= kPoolMapMax &&

@@ -208,26 +208,40 @@ bool conv_supported(const ConvShape& s) {
 
 namespace {
 
-// Which conv kernel family serves a layer: the first of conv_flat,
-// conv_half, conv_pq_generic that can tile it.  QCNN_CONV_KERNEL = half puts
-// the two-table kernel first, = generic skips the first two (for comparisons
+// Which conv kernel family serves a layer: conv_dense where its products are
+// faster than table reads, else the first of conv_flat, conv_half,
+// conv_pq_generic that can tile it.  QCNN_CONV_KERNEL = dense, flat or half
+// puts that kernel first, = generic skips all but the last (for comparisons
 // and for tests of every kernel on shapes the default one also serves).
-int conv_kernel_choice() {
-  const char* v = getenv("QCNN_CONV_KERNEL");  // read per call: tests switch it within one process
-  if (!v) return 0;
-  if (strcmp(v, "half") == 0) return 1;
-  if (strcmp(v, "generic") == 0) return 2;
-  return 0;
+enum class ConvKernel { kFlat, kHalf, kGeneric, kDense };
+
+ConvKernel pick_table_kernel(const ConvShape& s) {
+  if (conv_flat_supported(s)) return ConvKernel::kFlat;
+  if (conv_half_supported(s)) return ConvKernel::kHalf;
+  return ConvKernel::kGeneric;
 }
 
-enum class ConvKernel { kFlat, kHalf, kGeneric };
+size_t table_workspace(const ConvShape& s, ConvKernel k) {
+  if (k == ConvKernel::kFlat) return conv_flat_workspace(s);
+  if (k == ConvKernel::kHalf) return conv_half_workspace(s);
+  return 0;  // the generic kernel reads the caller's codes directly
+}
 
 ConvKernel pick_conv_kernel(const ConvShape& s) {
-  const int choice = conv_kernel_choice();
-  if (choice == 1 && conv_half_supported(s)) return ConvKernel::kHalf;
-  if (choice != 2 && conv_flat_supported(s)) return ConvKernel::kFlat;
-  if (choice != 2 && conv_half_supported(s)) return ConvKernel::kHalf;
-  return ConvKernel::kGeneric;
+  const char* v = getenv("QCNN_CONV_KERNEL");  // read per call: tests switch it within one process
+  if (v && strcmp(v, "generic") == 0) return ConvKernel::kGeneric;
+  if (v && strcmp(v, "half") == 0 && conv_half_supported(s)) return ConvKernel::kHalf;
+  if (v && strcmp(v, "dense") == 0 && conv_dense_supported(s)) return ConvKernel::kDense;
+  if (v && (strcmp(v, "flat") == 0 || strcmp(v, "half") == 0)) return pick_table_kernel(s);
+  if (getenv("QCNN_TABLE_BUILD")) return pick_table_kernel(s);  // a comparison of the table builds
+  const int flat = conv_flat_chain(s);
+  if (conv_dense_better(s, flat || !conv_half_supported(s) ? flat : s.M * s.dk * s.dk)) {
+    // A layer that fits the allocation-free entry point's scratch with its
+    // table kernel keeps fitting it.
+    const size_t room = noalloc_scratch_bytes() - 256, need = conv_dense_workspace(s);
+    if (need <= room || table_workspace(s, pick_table_kernel(s)) > room) return ConvKernel::kDense;
+  }
+  return pick_table_kernel(s);
 }
 
 }  // namespace
@@ -243,17 +257,19 @@ ConvKernel kind_or_pick(const ConvShape& s, int kind) {
 }  // namespace
 
 size_t conv_forward_workspace(const ConvShape& s, int kind) {
-  switch (kind_or_pick(s, kind)) {
-    case ConvKernel::kFlat: return conv_flat_workspace(s);
-    case ConvKernel::kHalf: return conv_half_workspace(s);
-    default: return 0;  // the generic kernel reads the caller's codes directly
-  }
+  const ConvKernel k = kind_or_pick(s, kind);
+  // The dense kernel's layers ask for what their table kernel would: which
+  // layers the allocation-free entry point refuses does not depend on the
+  // kernel chosen.
+  if (k == ConvKernel::kDense) return std::max(conv_dense_workspace(s), table_workspace(s, pick_table_kernel(s)));
+  return table_workspace(s, k);
 }
 
 hipError_t launch_conv_forward(const ConvShape& s, const float* x, const float* D, CodeStream codes,
                                const float* bias, int relu, float* y, hipStream_t stream, const Workspace* ws,
                                int kind) {
   const ConvKernel k = kind_or_pick(s, kind);
+  if (k == ConvKernel::kDense) return launch_conv_dense(s, x, D, codes, nullptr, bias, relu, y, stream, ws);
   if (k == ConvKernel::kFlat) return launch_conv_flat(s, x, D, codes, bias, relu, y, stream, ws);
   if (k == ConvKernel::kHalf) return launch_conv_half(s, x, D, codes, bias, relu, y, stream, ws);
   Tiling t;
@@ -296,6 +312,8 @@ hipError_t launch_conv_pool_forward(const ConvShape& s, const float* x, const fl
                                     const float* bias, int relu, const PoolSpec& pool, float* y,
                                     hipStream_t stream, int kind) {
   const ConvKernel k = kind_or_pick(s, kind);
+  if (k == ConvKernel::kDense)
+    return launch_conv_dense(s, x, D, codes, nullptr, bias, relu, y, stream, nullptr, &pool);
   if (k == ConvKernel::kFlat && conv_flat_pools(s))
     return launch_conv_flat(s, x, D, codes, bias, relu, y, stream, nullptr, &pool);
   // One library buffer holds the layer's own temporaries and, after them,

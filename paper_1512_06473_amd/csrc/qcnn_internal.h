@@ -80,7 +80,7 @@ struct PoolSpec {
 };
 
 // The conv kernel family for a layer: 0 the flat kernel, 1 the two-table
-// kernel, 2 the generic one; conv_kernel_pick gives the one the launchers
+// kernel, 2 the generic one, 3 the dense one; conv_kernel_pick gives the one the launchers
 // pick now (QCNN_CONV_KERNEL is read per call; host-side, no HIP call).  The
 // launchers below take a `kind` from it, or -1 to pick at the call.
 int conv_kernel_pick(const ConvShape& s);
@@ -124,6 +124,8 @@ bool conv_supported(const ConvShape& s);
 // Stride-1 kernel on the flattened padded grid (conv_flat.hip).
 bool conv_flat_supported(const ConvShape& s);
 size_t conv_flat_workspace(const ConvShape& s);
+// Table entries that one output of the plan adds up in a row (0: no plan).
+int conv_flat_chain(const ConvShape& s);
 // True when the flat kernel's plan for this layer splits the subspaces over
 // workgroups and an output map fits its pooled split-sum kernel (which then
 // takes the pooling maxima).
@@ -150,6 +152,24 @@ bool conv_half_supported(const ConvShape& s);
 size_t conv_half_workspace(const ConvShape& s);
 hipError_t launch_conv_half(const ConvShape& s, const float* x, const float* D, CodeStream codes,
                             const float* bias, int relu, float* y, hipStream_t stream, const Workspace* ws);
+
+// Implicit GEMM on the fp16 matrix cores with weights rebuilt from the
+// codebooks (conv_dense.hip).  The weights are made by
+// launch_conv_dense_weights into conv_dense_weight_bytes(s) bytes (once per
+// plan), or, with w null, by the call itself in its workspace.
+bool conv_dense_supported(const ConvShape& s);
+// Supported, and better than the layer's table kernel, which adds up
+// `table_chain` table entries in a row (0: only the generic kernel tiles it).
+bool conv_dense_better(const ConvShape& s, int table_chain);
+size_t conv_dense_workspace(const ConvShape& s);
+size_t conv_dense_weight_bytes(const ConvShape& s);
+hipError_t launch_conv_dense_weights(const ConvShape& s, const float* D, CodeStream codes, char* w,
+                                     hipStream_t stream);
+// D and codes are read by the fp32 form of the kernel.  With `pool`, y is the
+// pooled map.
+hipError_t launch_conv_dense(const ConvShape& s, const float* x, const float* D, CodeStream codes, const char* w,
+                             const float* bias, int relu, float* y, hipStream_t stream, const Workspace* ws,
+                             const PoolSpec* pool = nullptr);
 
 // Brackets the main kernel of a call with a pair of HIP events on its
 // stream while kernel timing is switched on (qcnn_timing_enable); does

@@ -1,0 +1,165 @@
+"""GPU parity of the dense conv kernel (weights rebuilt from the codebooks,
+split-fp16 matrix products) at the edges of its tiles and of its number range.
+
+Held to the fp32 bound abs(gpu - oracle) <= 1e-5 A + 1e-6 (A: sum of the
+magnitudes of an output's products) on float data; equal bit for bit on small
+integers, which the split represents and sums exactly.  The tile is 96 output
+positions x 64 or 128 channels, a chunk 16 channels per kernel tap, and the
+tiles' units are cut into runs at any unit.
+"""
+import numpy as np
+import pytest
+import torch
+
+from paper_1512_06473_amd import workloads as wl
+
+pytestmark = pytest.mark.gpu
+
+RTOL, ATOL = 1e-5, 1e-6
+
+SHAPES = [
+    # N, Cs, H, W, Ct, dk, stride, pad, Csp, K
+    (1, 16, 14, 14, 32, 3, 1, 1, 4, 16),      # one chunk, fewer runs than CUs
+    (1, 16, 1, 96, 65, 1, 1, 0, 4, 32),       # exactly one tile of positions, 65 channels
+    (1, 20, 1, 97, 64, 1, 1, 0, 5, 32),       # one position more; a chunk of 4 channels only
+    (2, 17, 9, 11, 129, 3, 1, 1, 1, 7),       # channels past a group of 8, C's = 1
+    (3, 36, 9, 11, 40, 3, 2, 1, 4, 64),       # stride 2
+    (2, 24, 13, 12, 33, 1, 2, 0, 4, 64),      # strided 1x1: only read positions are staged
+    (2, 24, 13, 12, 33, 1, 3, 0, 8, 256),
+    (1, 40, 7, 90, 48, 3, 1, 1, 8, 128),      # column strips
+    (1, 32, 5, 130, 20, 5, 1, 2, 16, 200),    # strips, C's = 16, K > 128
+    (2, 96, 15, 14, 96, 5, 1, 2, 4, 128),
+    (4, 64, 8, 8, 130, 2, 1, 1, 4, 128),      # even kernel
+    (1, 48, 12, 12, 24, 3, 1, 2, 6, 100),     # pad 2
+    (5, 128, 7, 7, 256, 3, 1, 1, 4, 128),     # tiles across images
+    (40, 48, 13, 13, 200, 3, 1, 1, 4, 64),    # whole tiles and shared ones
+]
+
+
+@pytest.fixture(scope="module")
+def dev():
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    return torch.device("cuda:0")
+
+
+@pytest.fixture(autouse=True)
+def dense(monkeypatch):
+    monkeypatch.setenv("QCNN_CONV_KERNEL", "dense")
+
+
+def T(a, dev):
+    return None if a is None else torch.from_numpy(np.ascontiguousarray(a)).to(dev)
+
+
+def conv(dev, x, D, codes, s, p, bias=None, relu=False):
+    from paper_1512_06473_amd import api
+    return api.conv_forward(T(x, dev), T(D, dev), T(codes, dev), s, p, T(bias, dev), relu).cpu().numpy()
+
+
+@pytest.mark.parametrize("integer", [False, True])
+@pytest.mark.parametrize("shape", SHAPES, ids=str)
+def test_dense_edges(dev, oracle, shape, integer):
+    N, Cs, H, W, Ct, dk, s, p, Csp, K = shape
+    rng = np.random.Generator(np.random.PCG64(11))
+    x, D, codes = wl.random_conv(rng, N, Cs, H, W, Ct, dk, s, p, Csp, K, integer=integer)
+    bias = (rng.integers(-3, 4, Ct) if integer else rng.standard_normal(Ct)).astype(np.float32)
+    y = conv(dev, x, D, codes, s, p, bias, True)
+    ref, A = oracle.conv_lut(x, D, codes, s, p, with_bound=True)
+    ref = np.maximum(ref + bias[None, :, None, None].astype(np.float64), 0.0)
+    if integer:
+        assert np.array_equal(y.astype(np.float64), ref)
+    else:
+        A = A + np.abs(bias)[None, :, None, None]
+        assert np.all(np.abs(y - ref) <= RTOL * A + ATOL)
+
+
+def _layer(seed=5, N=2, Cs=64, H=13, Ct=96):
+    rng = np.random.Generator(np.random.PCG64(seed))
+    return rng, *wl.random_conv(rng, N, Cs, H, H, Ct, 3, 1, 1, 4, 128)
+
+
+@pytest.mark.parametrize("scale", [2.0 ** -118, 1e-30, 1e-12, 1e12, 1e30])
+def test_dense_scale(dev, oracle, scale):
+    """Results do not depend on the inputs' magnitude: each is as close as at
+    magnitude one (the bound scaled with it, no absolute part but fp32's
+    smallest normal number)."""
+    _, x, D, codes = _layer()
+    x = (x * np.float32(scale)).astype(np.float32)
+    y = conv(dev, x, D, codes, 1, 1)
+    ref, A = oracle.conv_lut(x, D, codes, 1, 1, with_bound=True)
+    assert np.all(np.abs(y.astype(np.float64) - ref) <= RTOL * A + 1.2e-38)
+
+
+@pytest.mark.parametrize("kind", ["channels", "images", "positions", "codewords", "tiny"])
+def test_dense_wide_range(dev, oracle, kind):
+    """Inputs or codewords over many orders of magnitude, each output held to
+    the bound of its own products: growing channel by channel (the scale is
+    changed between chunks), image by image, position by position (some span
+    more than the split holds: those tiles run in fp32), codeword by codeword,
+    and next to single values of 1e-25."""
+    rng, x, D, codes = _layer()
+    N, Cs, H, W = x.shape
+    if kind == "channels":
+        x *= np.float32(2.0) ** (np.arange(Cs) // 2 - 16)[None, :, None, None].astype(np.float32)
+    elif kind == "images":
+        x *= np.float32(10.0) ** (-12 * np.arange(N))[:, None, None, None].astype(np.float32)
+    elif kind == "positions":
+        x *= (np.float32(10.0) ** rng.integers(-15, 16, (H, W)).astype(np.float32))[None, None]
+    elif kind == "codewords":
+        D *= (np.float32(10.0) ** rng.integers(-15, 1, D.shape[:2]).astype(np.float32))[:, :, None]
+    else:
+        x[rng.random(x.shape) < 0.01] = 1e-25
+    y = conv(dev, x, D, codes, 1, 1)
+    ref, A = oracle.conv_lut(x, D, codes, 1, 1, with_bound=True)
+    assert np.all(np.abs(y.astype(np.float64) - ref) <= RTOL * A + 1e-30)
+
+
+@pytest.mark.parametrize("where", ["x", "D"])
+def test_dense_non_finite(dev, where, monkeypatch):
+    """Infinities and NaN reach exactly the outputs they reach through the
+    table kernel; the others stay within the bound of it."""
+    rng, x, D, codes = _layer(7)
+    if where == "x":
+        x[0, 5, 3, 4], x[0, 40, 12, 0], x[1, 63, 12, 12] = np.inf, -np.inf, np.nan
+    else:
+        D[3, 17, 1], D[9, 100, 0] = np.inf, np.nan
+    y = conv(dev, x, D, codes, 1, 1)
+    monkeypatch.setenv("QCNN_CONV_KERNEL", "flat")
+    t = conv(dev, x, D, codes, 1, 1)
+    assert np.array_equal(np.isnan(y), np.isnan(t)) and np.array_equal(np.isinf(y), np.isinf(t))
+    fin = np.isfinite(t)
+    assert fin.any() and not fin.all()
+    assert np.array_equal(np.sign(y[np.isinf(t)]), np.sign(t[np.isinf(t)]))
+    assert np.all(np.abs(y[fin] - t[fin]) <= 2e-5 * np.abs(t[fin]) + 2e-4)
+
+
+def test_dense_zero_input(dev):
+    _, x, D, codes = _layer()
+    assert not conv(dev, np.zeros_like(x), D, codes, 1, 1).any()
+    x[:, :32] = 0.0  # the first chunks hold nothing to scale by
+    y = conv(dev, x, D, codes, 1, 1)
+    assert np.isfinite(y).all() and y.any()
+
+
+@pytest.mark.parametrize("seed", range(12))
+def test_dense_random_against_generic(dev, seed, monkeypatch):
+    """Random layers of every form the dense kernel takes against the generic
+    table kernel: per call, packed, through a plan and pooled."""
+    from paper_1512_06473_amd import api
+    rng = np.random.Generator(np.random.PCG64(100 + seed))
+    dk, Csp = int(rng.choice([1, 2, 3, 5, 7])), int(rng.choice([1, 2, 3, 4, 8, 12, 16]))
+    M, K, stride = int(rng.integers(1, 12)), int(rng.integers(1, 257)), int(rng.choice([1, 1, 2, 3]))
+    pad, N, Ct = int(rng.integers(0, dk)), int(rng.integers(1, 5)), int(rng.integers(1, 180))
+    H, W = int(rng.integers(dk, 30)), int(rng.integers(dk, 40))
+    x, D, codes = wl.random_conv(rng, N, M * Csp, H, W, Ct, dk, stride, pad, Csp, K)
+    xd, Dd, cd = T(x, dev), T(D, dev), T(codes, dev)
+    y = api.conv_forward(xd, Dd, cd, stride, pad)
+    assert torch.equal(y, api.conv_forward_packed(xd, Dd, api.pack_codes(cd, K), Ct, dk, stride, pad))
+    assert torch.equal(y, api.ConvPlan(xd.shape, Dd, cd, stride, pad)(xd))
+    if min(y.shape[2:]) >= 2:
+        assert torch.equal(api.maxpool2d(y, 2, 1), api.conv_pool_forward(xd, Dd, cd, stride, pad, 2, 1))
+    A = api.conv_forward(xd.abs(), Dd.abs(), cd, stride, pad)
+    monkeypatch.setenv("QCNN_CONV_KERNEL", "generic")
+    t = api.conv_forward(xd, Dd, cd, stride, pad)
+    assert bool(((y - t).abs() <= 2 * RTOL * A + 2 * ATOL).all())
