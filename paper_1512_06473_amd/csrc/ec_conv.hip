@@ -29,14 +29,18 @@
 //
 // State, float64: the residual of the whole layer E = T - Y [N][C_t][O]
 // (O = H_o W_o), D64, G, and the codes as [M][C_t][d_k^2].  Per subspace:
-//   ecc_apply_kernel  E -= the change of the subspace fitted before (from
+//   ecc_pass_kernel   E -= the change of the subspace fitted before (from
 //                     its delta[c][p] = D_new[k_new] - D_old[k_old]); block
-//                     sums of E^2 (the objective after that step);
-//   ecc_corr_kernel   partial sum_{n,o} s_p E(c) per chunk of images;
+//                     sums of E^2 (the objective after that step); and, while
+//                     E is in registers, partial sum_{n,o} s_p E(c) of this
+//                     subspace per chunk of outputs (ecc_apply_kernel and
+//                     ecc_corr_kernel where a map does not fit);
 //   ecc_reduce_kernel H = the partials in chunk order + sum_p' G[p][p'] W(c, p')
 //                     (so H is taken against R = E + this subspace's terms);
-//   ecc_dupdate_kernel one workgroup: Eq. (17)-(19), the sub-codewords in
-//                     order;
+//   ecc_rows_kernel   one workgroup per sub-codeword k: its row of the linear
+//                     system below;
+//   ecc_solve_kernel  one workgroup: Eq. (17)-(19), the sub-codewords in
+//                     order, by substitution in those rows;
 //   ecc_bupdate_kernel one wave per channel: Eq. (20)-(21), the positions in
 //                     order; after the last of `inner` rounds, delta for the
 //                     next apply.
@@ -123,6 +127,120 @@ __global__ __launch_bounds__(kCThreads) void ecc_gram_kernel(const float* __rest
   G[i0] = s;
 }
 
+// The same blocks on v_mfma_f64_16x16x4_f64, for (p, j) up to 64: G_m = X X^T
+// with X [(p, j)][(n, o)], one lane value serving as A operand of its row tile
+// and as B operand of its column tile.  A workgroup (m, chunk) takes the chunk's
+// images with their maps in LDS, wave w every fourth 16-position tile; the
+// waves' sums are added in order into gpart[chunk][m][(p, j)][(p', i)], the
+// chunks by ecc_gram_sum_kernel.  660 us as one thread per entry at 256
+// channels, 32 x 13 x 13, 3x3, C's = 4.
+typedef double d4v __attribute__((ext_vector_type(4)));
+constexpr int kMaxGramTiles = 4;
+constexpr int kGramChunks = 8;
+
+template <int NT>
+__global__ __launch_bounds__(kCThreads) void ecc_gram_mfma_kernel(const float* __restrict__ S, EccParams q, int pw,
+                                                                int plane, double* __restrict__ gpart) {
+  extern __shared__ float smf[];
+  constexpr int NW = kCThreads / kWave;
+  const int QN = q.P * q.Csp, size = q.Csp * plane, tiles = (q.O + 15) / 16;
+  double* sums = reinterpret_cast<double*>(smf);           // [16 NT][16 NT]
+  float* map = smf + 2 * (16 * NT) * (16 * NT);            // one image's maps, zero halos, then one zero
+  int* ooff = reinterpret_cast<int*>(map + size + 1);      // [16 tiles]
+  const int tid = threadIdx.x, lane = tid & (kWave - 1), wave = tid / kWave;
+  const int m = blockIdx.x, chunk = blockIdx.y;
+  const int n0 = (int)((long long)q.N * chunk / kGramChunks), n1 = (int)((long long)q.N * (chunk + 1) / kGramChunks);
+  const size_t HW = (size_t)q.H * q.W;
+  const int col = lane & 15, quad = lane >> 4;
+  int qoff[NT];
+#pragma unroll
+  for (int t = 0; t < NT; ++t) {
+    const int i = 16 * t + col, p = i / q.Csp, j = i - p * q.Csp;
+    qoff[t] = i < QN ? j * plane + (p / q.dk) * pw + p % q.dk : -1;
+  }
+  for (int i = tid; i < 16 * tiles; i += kCThreads)
+    ooff[i] = i < q.O ? (i / q.Wo) * q.stride * pw + (i % q.Wo) * q.stride : -1;
+  d4v g[NT][NT];
+#pragma unroll
+  for (int a = 0; a < NT; ++a)
+#pragma unroll
+    for (int b = 0; b < NT; ++b) g[a][b] = d4v{0.0, 0.0, 0.0, 0.0};
+  for (int n = n0; n < n1; ++n) {
+    __syncthreads();
+    for (int i = tid; i <= size; i += kCThreads) {
+      const int j = min(i, size - 1) / plane, r = i - j * plane;
+      const int y = r / pw - q.pad, x = r % pw - q.pad;
+      const bool in = i < size && (unsigned)y < (unsigned)q.H && (unsigned)x < (unsigned)q.W;
+      map[i] = in ? S[((size_t)n * q.Cs + (size_t)m * q.Csp + j) * HW + (size_t)y * q.W + x] : 0.f;
+    }
+    __syncthreads();
+    for (int t = wave; t < tiles; t += NW)
+#pragma unroll
+      for (int kk = 0; kk < 4; ++kk) {
+        const int o = ooff[16 * t + 4 * kk + quad];
+        double v[NT];
+#pragma unroll
+        for (int a = 0; a < NT; ++a) v[a] = (double)map[o >= 0 && qoff[a] >= 0 ? o + qoff[a] : size];
+#pragma unroll
+        for (int a = 0; a < NT; ++a)
+#pragma unroll
+          for (int b = 0; b < NT; ++b) g[a][b] = __builtin_amdgcn_mfma_f64_16x16x4f64(v[a], v[b], g[a][b], 0, 0, 0);
+      }
+  }
+  for (int w = 0; w < NW; ++w) {
+    if (wave == w)
+#pragma unroll
+      for (int a = 0; a < NT; ++a)
+#pragma unroll
+        for (int b = 0; b < NT; ++b)
+#pragma unroll
+          for (int i = 0; i < 4; ++i) {
+            double* at = sums + (16 * a + 4 * i + quad) * 16 * NT + 16 * b + col;
+            *at = w == 0 ? g[a][b][i] : *at + g[a][b][i];
+          }
+    __syncthreads();
+  }
+  for (int i = tid; i < QN * QN; i += kCThreads)
+    gpart[((size_t)chunk * q.M + m) * QN * QN + i] = sums[i / QN * 16 * NT + i % QN];
+}
+
+// G[m][p][p'][i][j] = the chunks' sums in order.
+__global__ __launch_bounds__(kCThreads) void ecc_gram_sum_kernel(const double* __restrict__ gpart, EccParams q,
+                                                               double* __restrict__ G) {
+  const size_t i0 = (size_t)blockIdx.x * kCThreads + threadIdx.x, QN = (size_t)q.P * q.Csp, total = q.M * QN * QN;
+  if (i0 >= total) return;
+  double s = 0.0;
+#pragma unroll
+  for (int c = 0; c < kGramChunks; ++c) s += gpart[c * total + i0];
+  const size_t m = i0 / (QN * QN), r = i0 % (QN * QN);
+  const size_t row = r / QN, col = r % QN;  // (p, i), (p', j)
+  G[(((m * q.P + row / q.Csp) * q.P + col / q.Csp) * q.Csp + row % q.Csp) * q.Csp + col % q.Csp] = s;
+}
+
+// LDS of the MFMA form, or 0 when the (p, j) or a map does not fit it.
+size_t gram_lds_bytes(const EccParams& q) {
+  const int nt = (q.P * q.Csp + 15) / 16;
+  const long long plane = (long long)((q.Ho - 1) * q.stride + q.dk) * ((q.Wo - 1) * q.stride + q.dk);
+  if (nt > kMaxGramTiles || plane * q.Csp * 4 > 32 * 1024) return 0;
+  return (size_t)(16 * nt) * (16 * nt) * 8 + ((size_t)plane * q.Csp + 1) * 4 + (size_t)16 * ((q.O + 15) / 16) * 4;
+}
+
+hipError_t launch_gram(const float* S, const EccParams& q, size_t lds, double* gpart, double* G, hipStream_t stream) {
+  const int pw = (q.Wo - 1) * q.stride + q.dk, plane = ((q.Ho - 1) * q.stride + q.dk) * pw;
+  const dim3 grid((unsigned)q.M, kGramChunks);
+#define QCNN_GRAM(nt) \
+  case nt: hipLaunchKernelGGL(ecc_gram_mfma_kernel<nt>, grid, dim3(kCThreads), lds, stream, S, q, pw, plane, gpart); \
+    break;
+  switch ((q.P * q.Csp + 15) / 16) { QCNN_GRAM(1) QCNN_GRAM(2) QCNN_GRAM(3) QCNN_GRAM(4) }
+#undef QCNN_GRAM
+  const hipError_t e = hipGetLastError();
+  if (e != hipSuccess) return e;
+  const size_t total = (size_t)q.M * q.P * q.P * q.Csp * q.Csp;
+  hipLaunchKernelGGL(ecc_gram_sum_kernel, dim3((unsigned)ceil_div_z(total, kCThreads)), dim3(kCThreads), 0, stream,
+                     (const double*)gpart, q, G);
+  return hipGetLastError();
+}
+
 // E = T - sum_m sum_p D^(m)[k(c, p)]^T s_p as a float64 implicit GEMM on
 // MFMA (v_mfma_f64_16x16x4_f64): rows are the output channels, columns the
 // output positions of all images (g = n O + o), and the reduction runs over
@@ -139,7 +257,6 @@ __global__ __launch_bounds__(kCThreads) void ecc_gram_kernel(const float* __rest
 constexpr int kStartTile = 64;          // channels and columns per workgroup
 constexpr int kStartKB = 32;            // reduction indices per stage
 constexpr int kStartLd = kStartKB + 1;  // LDS row stride in doubles (odd: spreads the rows over the banks)
-typedef double d4v __attribute__((ext_vector_type(4)));
 
 template <int CSP>
 __global__ __launch_bounds__(kCThreads) void ecc_start_kernel(const float* __restrict__ S,
@@ -324,36 +441,209 @@ __global__ __launch_bounds__(kCThreads) void ecc_corr_kernel(const float* __rest
   for (int j = 0; j < CSP; ++j) dst[j] = acc[j];
 }
 
+// Both of the above in one pass over E, on v_mfma_f64_16x16x4_f64, with E in
+// registers between them: for 16 output positions x 16 channels,
+//   E^T -= S_ma delta^T   (positions x (p, j), times (p, j) x channels)
+//   H^T += S_m^T E^T      ((p, j) x positions, times positions x channels);
+// register i of lane l of a result holds row 4 i + l / 16, column l % 16, and
+// that is the second product's B operand of its reduction step i as it stands.
+// A workgroup is 4 waves of 16 channels each over `tiles` 16-position tiles of
+// one image (blockIdx.y = image x pass_parts + part); the two subspaces' input
+// maps sit in LDS with their zero halos, and tables give an output's and a
+// (p, j)'s offset in them.  Grid order of the sums: part[blockIdx.y][c][p][j],
+// opart[blockIdx.y gridDim.x + blockIdx.x].
+// Bound by the matrix cores' float64 rate (the residual's bytes, read and
+// written once, take a third of that); apply and correlation as kernels of
+// their own took 35 + 60 us at 384 channels, 32 x 13 x 13 outputs, 3x3, C's = 4.
+struct PassShape {
+  int parts, tiles;  // 16-position tiles per workgroup, workgroups per image and channel block
+  int pw, plane;     // staged map: columns, positions per channel
+};
+
+constexpr int kMaxPassTiles = 8;  // (p, j) in tiles of 16: up to 128
+
+template <int NT>
+__global__ __launch_bounds__(kCThreads) void ecc_pass_kernel(const float* __restrict__ S, EccParams q, PassShape ps,
+                                                           int ma, int m, const double* __restrict__ delta,
+                                                           double* __restrict__ E, double* __restrict__ opart,
+                                                           double* __restrict__ part) {
+  extern __shared__ float smf[];
+  __shared__ double red[kCThreads / kWave];
+  const int QN = q.P * q.Csp, size = q.Csp * ps.plane;
+  float* sa = smf;                                // subspace ma's maps
+  float* sm = sa + size;                          // subspace m's
+  int* qoff = reinterpret_cast<int*>(sm + size);  // [16 NT] offset of (p, j)
+  int* ooff = qoff + 16 * NT;                     // [16 tiles] offset of an output
+  const int tid = threadIdx.x, lane = tid & (kWave - 1), wave = tid / kWave;
+  const int n = blockIdx.y / ps.parts, t0 = (blockIdx.y - n * ps.parts) * ps.tiles;
+  const int ntiles = min(ps.tiles, (q.O + 15) / 16 - t0);
+  const size_t HW = (size_t)q.H * q.W;
+  for (int i = tid; i < size; i += kCThreads) {
+    const int j = i / ps.plane, r = i - j * ps.plane;
+    const int y = r / ps.pw - q.pad, x = r % ps.pw - q.pad;
+    const bool in = (unsigned)y < (unsigned)q.H && (unsigned)x < (unsigned)q.W;
+    const float* src = S + ((size_t)n * q.Cs + j) * HW + (in ? (size_t)y * q.W + x : 0);
+    sa[i] = in && ma >= 0 ? src[(size_t)ma * q.Csp * HW] : 0.f;
+    sm[i] = in && m >= 0 ? src[(size_t)m * q.Csp * HW] : 0.f;
+  }
+  for (int i = tid; i < 16 * NT; i += kCThreads) {
+    const int p = i / q.Csp, j = i - p * q.Csp;
+    qoff[i] = i < QN ? j * ps.plane + (p / q.dk) * ps.pw + p % q.dk : 0;
+  }
+  for (int i = tid; i < 16 * ps.tiles; i += kCThreads) {
+    const int o = t0 * 16 + i;
+    ooff[i] = o < q.O ? (o / q.Wo) * q.stride * ps.pw + (o % q.Wo) * q.stride : 0;
+  }
+  __syncthreads();
+  const int col = lane & 15, quad = lane >> 4;
+  const int c = (blockIdx.x * (kCThreads / kWave) + wave) * 16 + col;
+  const bool live = c < q.Ct;
+  double* er = E + ((size_t)n * q.Ct + (live ? c : 0)) * q.O;
+  // the change of ma as the first product's B operand (0 past the (p, j))
+  double db[4 * NT];
+#pragma unroll
+  for (int kk = 0; kk < 4 * NT; ++kk) {
+    const int i = 4 * kk + quad;
+    db[kk] = ma >= 0 && live && i < QN ? delta[(size_t)c * QN + i] : 0.0;
+  }
+  d4v h[NT];
+#pragma unroll
+  for (int t = 0; t < NT; ++t) h[t] = d4v{0.0, 0.0, 0.0, 0.0};
+  double sq = 0.0;
+  double e[4];
+  auto load_e = [&](int t, double (&v)[4]) {
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+      const int o = (t0 + t) * 16 + 4 * i + quad;
+      v[i] = live && o < q.O ? er[o] : 0.0;
+    }
+  };
+  if (ntiles > 0) load_e(0, e);
+  for (int t = 0; t < ntiles; ++t) {
+    double en[4] = {0.0, 0.0, 0.0, 0.0};
+    if (t + 1 < ntiles) load_e(t + 1, en);  // one tile ahead
+    if (ma >= 0) {
+      const float* base = sa + ooff[16 * t + col];
+      d4v d = {0.0, 0.0, 0.0, 0.0};
+#pragma unroll
+      for (int kk = 0; kk < 4 * NT; ++kk)
+        if (4 * kk < QN) d = __builtin_amdgcn_mfma_f64_16x16x4f64((double)base[qoff[4 * kk + quad]], db[kk], d, 0, 0, 0);
+#pragma unroll
+      for (int i = 0; i < 4; ++i) {
+        const int o = (t0 + t) * 16 + 4 * i + quad;
+        if (live && o < q.O) {
+          e[i] -= d[i];
+          er[o] = e[i];
+          sq += e[i] * e[i];
+        }
+      }
+    }
+    if (m >= 0) {
+#pragma unroll
+      for (int kk = 0; kk < 4; ++kk) {
+        const float* base = sm + ooff[16 * t + 4 * kk + quad];
+#pragma unroll
+        for (int u = 0; u < NT; ++u)
+          h[u] = __builtin_amdgcn_mfma_f64_16x16x4f64((double)base[qoff[16 * u + col]], e[kk], h[u], 0, 0, 0);
+      }
+    }
+#pragma unroll
+    for (int i = 0; i < 4; ++i) e[i] = en[i];
+  }
+  if (m >= 0 && live) {
+    double* dst = part + ((size_t)blockIdx.y * q.Ct + c) * QN;
+#pragma unroll
+    for (int u = 0; u < NT; ++u)
+#pragma unroll
+      for (int i = 0; i < 4; ++i) {
+        const int r = 16 * u + 4 * i + quad;
+        if (r < QN) dst[r] = h[u][i];
+      }
+  }
+  if (ma >= 0) {
+    for (int off = kWave / 2; off > 0; off >>= 1) sq += __shfl_down(sq, off, kWave);
+    if (lane == 0) red[wave] = sq;
+    __syncthreads();
+    if (tid == 0) {
+      double s = 0.0;
+      for (int w = 0; w < kCThreads / kWave; ++w) s += red[w];
+      opart[(size_t)blockIdx.y * gridDim.x + blockIdx.x] = s;
+    }
+  }
+}
+
+// The pass's split and LDS bytes for a layer, or 0 bytes when its (p, j) or
+// its maps do not fit (ecc_apply_kernel and ecc_corr_kernel then run).
+size_t pass_shape(const EccParams& q, PassShape* ps) {
+  if (q.P * q.Csp > 16 * kMaxPassTiles) return 0;
+  ps->pw = (q.Wo - 1) * q.stride + q.dk;
+  const long long plane = (long long)((q.Ho - 1) * q.stride + q.dk) * ps->pw;
+  if (2 * plane * q.Csp * 4 > 48 * 1024) return 0;
+  ps->plane = (int)plane;
+  // about 6 waves per SIMD's worth of 16-channel work items at the least
+  // pieces of 4 tiles: fewer, longer ones leave SIMDs idle, more add chunks
+  // to the sums
+  const int tiles = (q.O + 15) / 16, waves = ceil_div(q.Ct, 16) * q.N;
+  int parts = std::max(1, std::min(ceil_div(1536, waves), tiles / 4));
+  ps->tiles = ceil_div(tiles, parts);
+  ps->parts = ceil_div(tiles, ps->tiles);
+  return (size_t)2 * q.Csp * plane * 4 + (size_t)16 * ((q.P * q.Csp + 15) / 16) * 4 + (size_t)16 * ps->tiles * 4;
+}
+
+hipError_t launch_pass(const float* S, const EccParams& q, const PassShape& ps, size_t lds, int ma, int m,
+                       const double* delta, double* E, double* opart, double* part, hipStream_t stream) {
+  const dim3 grid((unsigned)ceil_div(q.Ct, 64), (unsigned)(q.N * ps.parts));
+#define QCNN_PASS(nt) \
+  case nt: hipLaunchKernelGGL(ecc_pass_kernel<nt>, grid, dim3(kCThreads), lds, stream, S, q, ps, ma, m, delta, E, \
+                              opart, part); break;
+  switch ((q.P * q.Csp + 15) / 16) {
+    QCNN_PASS(1) QCNN_PASS(2) QCNN_PASS(3) QCNN_PASS(4) QCNN_PASS(5) QCNN_PASS(6) QCNN_PASS(7) QCNN_PASS(8)
+  }
+#undef QCNN_PASS
+  return hipGetLastError();
+}
+
 // H[c][p][j] = sum over chunks (in order) of part + sum_p' sum_i G[p][p'][j][i] W(c, p')[i].
+// One (c, p, j) per thread, sixteen chunks' loads in flight.
 template <int CSP>
-__global__ __launch_bounds__(kCThreads) void ecc_reduce_kernel(const double* __restrict__ part, EccParams q, int m,
-                                                             const double* __restrict__ G,
+__global__ __launch_bounds__(kCThreads) void ecc_reduce_kernel(const double* __restrict__ part, EccParams q,
+                                                             int nchunks, int m, const double* __restrict__ G,
                                                              const double* __restrict__ D64,
                                                              const uint8_t* __restrict__ ct,
                                                              double* __restrict__ H) {
-  const int i = blockIdx.x * kCThreads + threadIdx.x;
-  if (i >= q.Ct * q.P) return;
-  const int c = i / q.P, p = i - c * q.P;
-  double h[CSP];
+  const int i = blockIdx.x * kCThreads + threadIdx.x, total = q.Ct * q.P * CSP;
+  if (i >= total) return;
+  const int cp = i / CSP, j = i - cp * CSP;
+  const int c = cp / q.P, p = cp - c * q.P;
+  double h = 0.0;
+  for (int ch = 0; ch < nchunks; ch += 16) {
+    double v[16];
 #pragma unroll
-  for (int j = 0; j < CSP; ++j) h[j] = 0.0;
-  for (int ch = 0; ch < q.nchunks; ++ch) {
-    const double* src = part + ((size_t)ch * q.Ct * q.P + i) * CSP;
+    for (int u = 0; u < 16; ++u) v[u] = ch + u < nchunks ? part[(size_t)(ch + u) * total + i] : 0.0;
 #pragma unroll
-    for (int j = 0; j < CSP; ++j) h[j] += src[j];
+    for (int u = 0; u < 16; ++u) h += v[u];
   }
-  const double* Gp = G + ((size_t)m * q.P + p) * q.P * CSP * CSP;
+  const double* Gp = G + (((size_t)m * q.P + p) * q.P * CSP + j) * CSP;
   const uint8_t* km = ct + ((size_t)m * q.Ct + c) * q.P;
-  for (int p2 = 0; p2 < q.P; ++p2) {
-    const double* w = D64 + ((size_t)m * q.K + km[p2]) * CSP;
-    const double* g = Gp + (size_t)p2 * CSP * CSP;
+  for (int p0 = 0; p0 < q.P; p0 += 3) {
+    double w[3][CSP], g[3][CSP];
 #pragma unroll
-    for (int j = 0; j < CSP; ++j)
+    for (int u = 0; u < 3; ++u) {
+      const int p2 = min(p0 + u, q.P - 1);
+      const double* ws = D64 + ((size_t)m * q.K + km[p2]) * CSP;
 #pragma unroll
-      for (int i2 = 0; i2 < CSP; ++i2) h[j] += g[j * CSP + i2] * w[i2];
+      for (int i2 = 0; i2 < CSP; ++i2) {
+        w[u][i2] = ws[i2];
+        g[u][i2] = Gp[(size_t)p2 * CSP * CSP + i2];
+      }
+    }
+#pragma unroll
+    for (int u = 0; u < 3; ++u)
+      if (p0 + u < q.P)
+#pragma unroll
+        for (int i2 = 0; i2 < CSP; ++i2) h += g[u][i2] * w[u][i2];
   }
-#pragma unroll
-  for (int j = 0; j < CSP; ++j) H[(size_t)i * CSP + j] = h[j];
+  H[i] = h;
 }
 
 __device__ __forceinline__ void wave_sync_lds() {
@@ -402,259 +692,372 @@ __device__ __forceinline__ void solve_rcp(const double* __restrict__ A, const do
   }
 }
 
-// Bytes of the D-update kernel's LDS, with (gl) or without the Gram blocks.
-template <int CSP> size_t solve_lds_bytes(int K, int npairs, int P, bool gl) {
-  constexpr int QS = kWave / CSP;
-  const size_t dbl = (size_t)2 * K * CSP + kCThreads + (size_t)(kCThreads / kWave) * QS * CSP * (CSP + 1) +
-                     (size_t)(kCThreads / kWave) * CSP * (CSP + 1) + (gl ? (size_t)P * P * CSP * CSP : 0);
-  const size_t ints = 3 * 256 + (kCThreads / kWave) * 256;
-  return dbl * 8 + ints * 4 + (size_t)npairs * 2 + (size_t)npairs;
+// ---- Eq. (17)-(19) as a linear system.  With the pairs (c, p) on k,
+//   A_k = B[k][k],  B[k][k'] = sum_{(c,p) on k} sum_{p': k(c,p') = k'} G[p][p'],
+//   b_k = sum_{(c,p) on k} H[c][p],
+// the update of sub-codeword k is A_k D_k = b_k - sum_{k' != k} B[k][k'] D_k'
+// with D_k' new for k' < k and old for k' > k: one Gauss-Seidel sweep over
+// the rows.  Everything but the D_k' new terms is independent of the order:
+// ecc_rows_kernel makes row k in a workgroup of its own, r0_k = b_k -
+// sum_{k'>k} B[k][k'] D_k' old included, and ecc_solve_kernel is left with
+// r_k -= B[k][k'] D_k' for k' < k and D_k = A_k^-1 r_k.  (One workgroup that
+// formed each sub-codeword's sums from its pairs in turn took 2.8 us per
+// sub-codeword, 353 us a step at 384 channels, 3x3, K = 128, C's = 4.)
+//
+// The solve goes in blocks of kColBlock / C's sub-codewords: wave 0 solves a
+// block, then every thread takes the block's new values out of its later row.  B is stored for that:
+// [column block][column pair][row][2], so that a wave's loads are whole lines.
+constexpr int kColBlock = 64;  // columns (sub-codeword entries) per block, one row of the block per lane
+constexpr int kSolveThreads = 512;
+
+template <int CSP> __host__ __device__ constexpr int block_codewords() { return kColBlock / CSP; }
+
+template <int CSP> size_t system_doubles(int K) {
+  const size_t blocks = ((size_t)K + block_codewords<CSP>() - 1) / block_codewords<CSP>();
+  return blocks * kColBlock * (size_t)K * CSP;
 }
 
-// Eq. (17)-(19), one workgroup: the sub-codewords in order.  On the first
-// round of a step (`first`) it also records the objective before the step
-// (from the apply kernel's block sums) and keeps the subspace's sub-codebook
-// and codes as they were (Dold, cold) for delta.  At the end it stores
-// qkg[p][k] = D_k^T G[p][p] D_k for the assignment kernel.  GL: the
-// subspace's Gram blocks are staged in LDS.
-template <int CSP, bool GL>
-__global__ __launch_bounds__(kCThreads) void ecc_dupdate_kernel(const double* __restrict__ H, EccParams q, int m,
-                                                              const double* __restrict__ G, double* __restrict__ D64,
-                                                              const uint8_t* __restrict__ ct, int first,
-                                                              double* __restrict__ Dold, uint8_t* __restrict__ cold,
-                                                              double* __restrict__ qkg,
-                                                              const double* __restrict__ opart, int nopart,
-                                                              double* __restrict__ objective) {
-  extern __shared__ double sh[];
-  constexpr int NW = kCThreads / kWave;
-  constexpr int QS = kWave / CSP;               // pair slots per wave
-  constexpr int NE = CSP * (CSP + 1);           // entries of [rhs | normal matrix]
-  const int K = q.K, P = q.P, Ct = q.Ct, npairs = Ct * P;
-  double* Ds = sh;                              // [K][C's] current sub-codewords
-  double* hs = Ds + K * CSP;                    // [K][C's] sums of H over each sub-codeword's pairs
-  double* red = hs + K * CSP;                   // [256]
-  double* wred = red + kCThreads;               // [4][QS][C's][C's + 1] slot partials
-  double* wpart = wred + NW * QS * NE;          // [4][C's][C's + 1] wave partials
-  double* Gl = wpart + NW * NE;                 // [P][P][C's][C's] (GL)
-  int* cnt = reinterpret_cast<int*>(Gl + (GL ? (size_t)P * P * CSP * CSP : 0));  // [256]
-  int* start = cnt + 256;                       // [256]
-  int* run = start + 256;                       // [256]
-  int* wcnt = run + 256;                        // [4][256]
-  uint16_t* list = reinterpret_cast<uint16_t*>(wcnt + NW * 256);  // pairs by code
-  uint8_t* cs = reinterpret_cast<uint8_t*>(list + npairs);        // [C_t][P] codes
-  const int tid = threadIdx.x, lane = tid & (kWave - 1), wave = tid / kWave;
-  const double* Gg = G + (size_t)m * P * P * CSP * CSP;
-  const double* Gm = GL ? Gl : Gg;
+template <int CSP> constexpr int rows_threads() { return CSP <= 4 ? 1024 : 512; }
 
-  const bool obj = first && objective;
-  double os = 0.0;
-  if (obj)
-    for (int i = tid; i < nopart; i += kCThreads) os += opart[i];
-  for (int i = tid; i < K * CSP; i += kCThreads) {
-    Ds[i] = D64[(size_t)m * K * CSP + i];
+// Row k = blockIdx.x.  LDS: the codes, the list of k's pairs in (c, p) order
+// (one run of it per wave, compacted by that wave), the Gram blocks (GL).  A
+// thread owns one column block k' and, of the `parts` threads that share it,
+// every parts-th pair: it adds the G[p][p'] of the pair's positions on k'.
+// The shares are added in order.  The kernel's time is that of the largest
+// sub-codeword (some take ten times the mean number of pairs), hence as many
+// threads per row as the sums' registers allow.
+template <int CSP, bool GL>
+__global__ __launch_bounds__(rows_threads<CSP>()) void ecc_rows_kernel(const double* __restrict__ H, EccParams q,
+                                                                     int m, const double* __restrict__ G,
+                                                                     const double* __restrict__ D64,
+                                                                     const uint8_t* __restrict__ ct,
+                                                                     double* __restrict__ B, double* __restrict__ X,
+                                                                     double* __restrict__ r0,
+                                                                     int* __restrict__ used) {
+  extern __shared__ double sh[];
+  constexpr int NT = rows_threads<CSP>(), NW = NT / kWave, SQ = CSP * CSP;
+  const int K = q.K, P = q.P, npairs = q.Ct * P;
+  const int k = blockIdx.x;
+  const int kp = (K + kWave - 1) / kWave * kWave;
+  const int parts = NT / kp;
+  double* red = sh;                      // [NT] partial sums
+  double* Al = red + NT;                 // [C's][C's]
+  double* share = Al + SQ;               // [C's^2][kp]
+  double* Gl = share + (size_t)kp * SQ;
+  int* wn = reinterpret_cast<int*>(Gl + (GL ? (size_t)P * P * SQ : 0));  // [NW] first entry of each wave's run
+  uint16_t* list = reinterpret_cast<uint16_t*>(wn + NW + 1);
+  uint8_t* cs = reinterpret_cast<uint8_t*>(list + npairs);
+  const int tid = threadIdx.x, lane = tid & (kWave - 1), wave = tid / kWave;
+  const double* Gg = G + (size_t)m * P * P * SQ;
+  const double* Gm = GL ? Gl : Gg;
+  for (int i = tid; i < npairs; i += NT) cs[i] = ct[(size_t)m * npairs + i];
+  if (GL)
+    for (int i = tid; i < P * P * SQ; i += NT) Gl[i] = Gg[i];
+  const int kc = tid % kp, part = tid / kp;  // column block and share of this thread
+  double dold[CSP];
+#pragma unroll
+  for (int j = 0; j < CSP; ++j)
+    dold[j] = part == 0 && kc > k && kc < K ? D64[((size_t)m * K + kc) * CSP + j] : 0.0;
+  __syncthreads();
+  // each wave counts, then places, the pairs on k of its share of the codes
+  const int share_n = (npairs + NW - 1) / NW;
+  const int b0 = min(npairs, wave * share_n), b1 = min(npairs, b0 + share_n);
+  int n = 0;
+  for (int i0 = b0; i0 < b1; i0 += kWave) n += __popcll(__ballot(i0 + lane < b1 && cs[i0 + lane] == k));
+  if (lane == 0) wn[wave] = n;
+  __syncthreads();
+  int at = 0, n_k = 0;
+#pragma unroll
+  for (int w = 0; w < NW; ++w) {
+    at += w < wave ? wn[w] : 0;
+    n_k += wn[w];
+  }
+  if (tid == 0) used[k] = n_k;
+  if (n_k == 0) return;  // unused: keeps its value, and its row is not read
+  for (int i0 = b0; i0 < b1; i0 += kWave) {
+    const bool on = i0 + lane < b1 && cs[i0 + lane] == k;
+    const uint64_t ones = __ballot(on);
+    if (on) list[at + __popcll(ones & ((1ull << lane) - 1ull))] = (uint16_t)(i0 + lane);
+    at += __popcll(ones);
+  }
+  __syncthreads();
+
+  // b_k: slot s = tid / C's takes pairs s, s + slots, ...; then the slots in order
+  constexpr int slots = NT / CSP;
+  {
+    const int s = tid / CSP, j = tid - s * CSP;
+    double v = 0.0;
+    if (s < slots)
+      for (int r = s; r < n_k; r += slots) v += H[(size_t)list[r] * CSP + j];
+    red[tid] = v;
+  }
+  // this thread's share of column block k'
+  const float rcp_p = 1.0f / (float)P;
+  double acc[SQ];
+#pragma unroll
+  for (int i = 0; i < SQ; ++i) acc[i] = 0.0;
+  for (int r = part < parts ? part : n_k; r < n_k; r += parts) {
+    const int pr = list[r];
+    const int c = (int)(((float)pr + 0.5f) * rcp_p), p = pr - c * P;  // exact: pr < 2^14
+    const uint8_t* kk = cs + c * P;
+    const double* grow = Gm + (size_t)p * P * SQ;
+    for (int p0 = 0; p0 < P; p0 += 9) {
+      int k2[9];
+#pragma unroll
+      for (int u = 0; u < 9; ++u) k2[u] = p0 + u < P ? kk[p0 + u] : -1;
+#pragma unroll
+      for (int u = 0; u < 9; ++u)
+        if (k2[u] == kc) {
+          const double* g = grow + (size_t)(p0 + u) * SQ;
+#pragma unroll
+          for (int i = 0; i < SQ; ++i) acc[i] += g[i];
+        }
+    }
+  }
+  __syncthreads();
+  for (int w = 1; w < min(parts, n_k); ++w) {
+    if (part == w)
+#pragma unroll
+      for (int i = 0; i < SQ; ++i) share[(size_t)i * kp + kc] = acc[i];
+    __syncthreads();
+    if (part == 0)
+#pragma unroll
+      for (int i = 0; i < SQ; ++i) acc[i] += share[(size_t)i * kp + kc];
+    __syncthreads();
+  }
+  double bk = 0.0;  // of thread j < C's
+  if (tid < CSP) {
+    const int ns = min(slots, n_k);
+    for (int s0 = 0; s0 < ns; s0 += 8) {
+      double v[8];
+#pragma unroll
+      for (int u = 0; u < 8; ++u) v[u] = s0 + u < ns ? red[(s0 + u) * CSP + tid] : 0.0;
+#pragma unroll
+      for (int u = 0; u < 8; ++u) bk += v[u];
+    }
+  }
+  // the row's columns k' < k; the old values of k' > k; A_k
+  const bool mine = part == 0 && kc < K;
+  double t[CSP];
+#pragma unroll
+  for (int i = 0; i < CSP; ++i) t[i] = 0.0;
+  if (mine && kc < k) {
+    constexpr int NB = block_codewords<CSP>();
+    const size_t R = (size_t)K * CSP;
+    const int kb = kc / NB, col0 = (kc - kb * NB) * CSP;
+    double* dst = B + (size_t)kb * kColBlock * R;
+#pragma unroll
+    for (int i = 0; i < CSP; ++i) {
+      if constexpr (CSP % 2 == 0) {
+#pragma unroll
+        for (int j = 0; j < CSP; j += 2)
+          *reinterpret_cast<double2*>(dst + ((size_t)((col0 + j) >> 1) * R + (size_t)k * CSP + i) * 2) =
+              double2{acc[i * CSP + j], acc[i * CSP + j + 1]};
+      } else {
+#pragma unroll
+        for (int j = 0; j < CSP; ++j) {
+          const int col = col0 + j;
+          dst[((size_t)(col >> 1) * R + (size_t)k * CSP + i) * 2 + (col & 1)] = acc[i * CSP + j];
+        }
+      }
+    }
+  } else if (mine && kc > k) {
+#pragma unroll
+    for (int i = 0; i < CSP; ++i)
+#pragma unroll
+      for (int j = 0; j < CSP; ++j) t[i] += acc[i * CSP + j] * dold[j];
+  } else if (mine) {
+#pragma unroll
+    for (int i = 0; i < SQ; ++i) Al[i] = acc[i];
+  }
+#pragma unroll
+  for (int i = 0; i < CSP; ++i)
+    for (int off = kWave / 2; off > 0; off >>= 1) t[i] += __shfl_down(t[i], off, kWave);
+  __syncthreads();  // the slots' sums are read; A_k
+  if (lane == 0)
+#pragma unroll
+    for (int i = 0; i < CSP; ++i) red[wave * CSP + i] = t[i];
+  __syncthreads();
+  if (tid < CSP) {
+    double v = bk;
+    for (int w = 0; w < kp / kWave; ++w) v -= red[w * CSP + tid];
+    r0[(size_t)k * CSP + tid] = v;
+    // column tid of A_k^-1 (with the dropped coordinates' rows and columns 0)
+    double unit[CSP], Aw[SQ], x[CSP];
+#pragma unroll
+    for (int i = 0; i < CSP; ++i) unit[i] = i == tid ? 1.0 : 0.0;
+    solve_rcp<CSP>(Al, unit, Aw, x);
+#pragma unroll
+    for (int i = 0; i < CSP; ++i) X[((size_t)k * CSP + i) * CSP + tid] = x[i];
+  }
+}
+
+template <int CSP, bool GL> size_t rows_lds_bytes(int K, int npairs, int P) {
+  constexpr int NT = rows_threads<CSP>();
+  const int kp = ceil_div(K, kWave) * kWave;
+  const size_t dbl = NT + CSP * CSP + (size_t)kp * CSP * CSP + (GL ? (size_t)P * P * CSP * CSP : 0);
+  return dbl * 8 + (NT / kWave + 1) * 4 + (size_t)npairs * 3;
+}
+
+// The substitution, in one workgroup.  On the first round of a step (`first`)
+// it also records the objective before the step (from the pass's block sums)
+// and keeps the subspace's sub-codebook and codes as they were (Dold, cold)
+// for delta.  At the end it stores qkg[p][k] = D_k^T G[p][p] D_k for the
+// assignment kernel.  (Having the other workgroups of its XCD read B ahead
+// into their L2 made no difference: it is not bound by B's latency.)
+template <int CSP>
+__global__ __launch_bounds__(kSolveThreads) void ecc_solve_kernel(EccParams q, int m, const double* __restrict__ G,
+                                                                double* __restrict__ D64,
+                                                                const uint8_t* __restrict__ ct, int first,
+                                                                const double* __restrict__ B,
+                                                                const double* __restrict__ X,
+                                                                const double* __restrict__ r0,
+                                                                const int* __restrict__ used,
+                                                                double* __restrict__ Dold, uint8_t* __restrict__ cold,
+                                                                double* __restrict__ qkg,
+                                                                const double* __restrict__ opart, int nopart,
+                                                                double* __restrict__ objective) {
+  extern __shared__ double sh[];
+  constexpr int NB = block_codewords<CSP>(), NC = NB * CSP;  // sub-codewords and columns of a block
+  const int K = q.K, P = q.P, npairs = q.Ct * P, R = K * CSP;
+  double* Ds = sh;              // [K][C's]
+  double* rs = Ds + R;          // [K][C's] right-hand sides
+  double* Xl2 = rs + R;         // [2][NB][C's][C's] A^-1 of a block
+  double* diag2 = Xl2 + 2 * NB * CSP * CSP;               // [2][64][66] a block's own rows
+  double* red = diag2 + 2 * kColBlock * (kColBlock + 2);  // [512]
+  int* us = reinterpret_cast<int*>(red + kSolveThreads);  // [K]
+  const int tid = threadIdx.x, lane = tid & (kWave - 1);
+  for (int i = tid; i < R; i += kSolveThreads) {
+    Ds[i] = D64[(size_t)m * R + i];
+    rs[i] = r0[i];
     if (first) Dold[i] = Ds[i];
   }
-  for (int i = tid; i < npairs; i += kCThreads) {
-    cs[i] = ct[(size_t)m * npairs + i];
-    if (first) cold[i] = cs[i];
-  }
-  if (GL)
-    for (int i = tid; i < P * P * CSP * CSP; i += kCThreads) Gl[i] = Gg[i];
-  if (obj) {
+  for (int i = tid; i < K; i += kSolveThreads) us[i] = used[i];
+  if (first)
+    for (int i = tid; i < npairs; i += kSolveThreads) cold[i] = ct[(size_t)m * npairs + i];
+  if (first && objective) {
+    double os = 0.0;
+    for (int i = tid; i < nopart; i += kSolveThreads) os += opart[i];
     red[tid] = os;
     __syncthreads();
-    for (int h = kCThreads / 2; h > 0; h >>= 1) {
+    for (int h = kSolveThreads / 2; h > 0; h >>= 1) {
       if (tid < h) red[tid] += red[tid + h];
       __syncthreads();
     }
     if (tid == 0) *objective = red[0];
   }
+
+  // Wave 0 solves block kb (its columns' own rows and A^-1 in LDS) while the
+  // others load those columns of the later rows, a row per thread, and the
+  // next block's LDS.
+  constexpr int LD = kColBlock + 2;  // doubles per row of a block's own rows
+  const int blocks = (K + NB - 1) / NB;
+  auto stage = [&](int kb, int first_thread) {  // block kb's own rows and A^-1 into buffer kb & 1
+    double* diag = diag2 + (size_t)(kb & 1) * kColBlock * LD;
+    double* Xl = Xl2 + (size_t)(kb & 1) * NB * CSP * CSP;
+    const double* src = B + (size_t)kb * kColBlock * R;
+    const int step = kSolveThreads - first_thread;
+    for (int i = tid - first_thread; i < NC * (kColBlock / 2); i += step) {
+      const int c2 = i / NC, rr = i - c2 * NC, row = kb * NC + rr;
+      if (2 * c2 < NC && row < R) {
+        const double2 v = *reinterpret_cast<const double2*>(src + ((size_t)c2 * R + row) * 2);
+        diag[rr * LD + 2 * c2] = v.x;
+        diag[rr * LD + 2 * c2 + 1] = v.y;
+      }
+    }
+    for (int i = tid - first_thread; i < NB * CSP * CSP; i += step) {
+      const size_t at = (size_t)kb * NB * CSP * CSP + i;
+      if (at < (size_t)R * CSP) Xl[i] = X[at];
+    }
+  };
+  stage(0, 0);
+  for (int kb = 0; kb < blocks; ++kb) {
+    __syncthreads();  // right-hand sides; the block's LDS
+    const double* src = B + (size_t)kb * kColBlock * R;
+    const int row0 = (kb + 1) * NC + tid - kWave;  // first later row of a thread past wave 0
+    double bv[kColBlock];
+    auto load_cols = [&](int row) {
+#pragma unroll
+      for (int c = 0; c < NC; c += 2) {
+        const double2 v = *reinterpret_cast<const double2*>(src + ((size_t)(c >> 1) * R + row) * 2);
+        bv[c] = v.x;
+        bv[c + 1] = v.y;
+      }
+    };
+    if (tid < kWave) {
+      const double* diag = diag2 + (size_t)(kb & 1) * kColBlock * LD + lane * LD;
+      const double* Xl = Xl2 + (size_t)(kb & 1) * NB * CSP * CSP;
+      const int row = kb * NC + lane;
+      double r = lane < NC && row < R ? rs[row] : 0.0;
+      // Unrolled, with the operands of the next sub-codeword (which do not
+      // wait for r) in registers of their own; lane l forms entry l % C's of
+      // A_k^-1 r, broadcast through scalar registers.
+      const int li = lane % CSP;
+      double bq[2][CSP], aq[2][CSP];
+      const uint64_t live = __ballot(lane < NB && kb * NB + lane < K && us[min(kb * NB + lane, K - 1)] > 0);
+      auto fetch = [&](int kk, int slot) {
+#pragma unroll
+        for (int j = 0; j < CSP; ++j) {
+          bq[slot][j] = diag[kk * CSP + j];
+          aq[slot][j] = Xl[(kk * CSP + li) * CSP + j];
+        }
+      };
+      auto spread = [&](double v, int first, double (&out)[CSP]) {
+#pragma unroll
+        for (int j = 0; j < CSP; ++j) {
+          const long long bits = __double_as_longlong(v);
+          const int lo = __builtin_amdgcn_readlane((int)bits, first + j);
+          const int hi = __builtin_amdgcn_readlane((int)(bits >> 32), first + j);
+          out[j] = __longlong_as_double(((long long)hi << 32) | (unsigned)lo);
+        }
+      };
+      auto dot = [&](const double (&u)[CSP], const double (&v)[CSP]) {
+        double even = u[0] * v[0], odd = CSP > 1 ? u[CSP > 1] * v[CSP > 1] : 0.0;
+#pragma unroll
+        for (int j = 2; j < CSP; j += 2) even += u[j] * v[j];
+#pragma unroll
+        for (int j = 3; j < CSP; j += 2) odd += u[j] * v[j];
+        return even + odd;
+      };
+      fetch(0, 0);
+#pragma unroll
+      for (int kk = 0; kk < NB; ++kk) {
+        if (kk + 1 < NB) fetch(kk + 1, (kk + 1) & 1);
+        __builtin_amdgcn_sched_barrier(0);
+        if ((live >> kk) & 1) {  // uniform
+          double g[CSP], x[CSP];
+          spread(r, kk * CSP, g);
+          const double own = dot(aq[kk & 1], g);
+          spread(own, 0, x);
+          const double d = dot(bq[kk & 1], x);
+          if (lane >= (kk + 1) * CSP) r -= d;
+          if (lane < CSP) Ds[(kb * NB + kk) * CSP + lane] = own;
+        }
+        __builtin_amdgcn_sched_barrier(0);
+      }
+    } else {
+      if (row0 < R) load_cols(row0);
+      if (kb + 1 < blocks) stage(kb + 1, kWave);
+    }
+    __syncthreads();  // the block's new values
+    // ... taken out of the later rows (unused sub-codewords' columns are 0)
+    if (tid >= kWave) {
+      for (int row = row0; row < R; row += kSolveThreads - kWave) {
+        if (row != row0) load_cols(row);
+        double s4[4] = {0.0, 0.0, 0.0, 0.0};
+#pragma unroll
+        for (int c = 0; c < NC; ++c) s4[c & 3] += bv[c] * Ds[kb * NC + c];
+        rs[row] -= (s4[0] + s4[1]) + (s4[2] + s4[3]);
+      }
+    }
+  }
   __syncthreads();
 
-  {
-    // ---- the (c, p) pairs sorted stably by code: list[start[k] ..]
-    for (int k = tid; k < 256; k += kCThreads) cnt[k] = run[k] = 0;
-    for (int k = tid; k < NW * 256; k += kCThreads) wcnt[k] = 0;
-    __syncthreads();
-    for (int i = tid; i < npairs; i += kCThreads) atomicAdd(&cnt[cs[i]], 1);  // counts: order-free
-    __syncthreads();
-    if (tid == 0) {
-      int s = 0;
-      for (int k = 0; k < 256; ++k) {
-        start[k] = s;
-        s += cnt[k];
-      }
-    }
-    __syncthreads();
-    for (int r0 = 0; r0 < npairs; r0 += kCThreads) {
-      const int i = r0 + tid;
-      const bool valid = i < npairs;
-      const uint32_t c = valid ? cs[i] : 0u;
-      uint64_t same = __ballot(valid);
-#pragma unroll
-      for (int b = 0; b < 8; ++b) {
-        const uint64_t ones = __ballot(valid && ((c >> b) & 1u));
-        same &= ((c >> b) & 1u) ? ones : ~ones;
-      }
-      const int below = __popcll(same & ((1ull << lane) - 1ull));
-      if (valid && below == 0) wcnt[wave * 256 + c] = __popcll(same);
-      __syncthreads();
-      if (valid) {
-        int off = start[c] + run[c] + below;
-        for (int w = 0; w < wave; ++w) off += wcnt[w * 256 + c];
-        list[off] = (uint16_t)i;
-      }
-      __syncthreads();
-      for (int k = tid; k < 256; k += kCThreads) {
-        int add = 0;
-        for (int w = 0; w < NW; ++w) {
-          add += wcnt[w * 256 + k];
-          wcnt[w * 256 + k] = 0;
-        }
-        run[k] += add;
-      }
-      __syncthreads();
-    }
-
-    // the H part of each sub-codeword's right-hand side (it does not depend
-    // on the sub-codewords), its pairs in list order
-    for (int e = tid; e < K * CSP; e += kCThreads) {
-      const int k = e / CSP, j = e - k * CSP;
-      const int s0 = start[k], n_k = cnt[k];
-      double v = 0.0;
-      for (int r0 = 0; r0 < n_k; r0 += 4) {
-        double h[4];
-#pragma unroll
-        for (int u = 0; u < 4; ++u) h[u] = r0 + u < n_k ? H[(size_t)list[s0 + r0 + u] * CSP + j] : 0.0;
-#pragma unroll
-        for (int u = 0; u < 4; ++u)
-          if (r0 + u < n_k) v += h[u];
-      }
-      hs[e] = v;
-    }
-    __syncthreads();
-
-    // ---- Eq. (17)-(19): sub-codewords in order.  Pair slot g = wave QS +
-    // lane / C's takes pairs g, g + 4 QS, ... of the sub-codeword's list;
-    // lane % C's is its row j of [rhs | normal matrix].  Slot sums are added
-    // within each wave (a fixed shuffle tree, or in slot order when C's does
-    // not divide 64), then the waves in order.
-    {
-      const int slot = lane / CSP, j = lane - slot * CSP;
-      const bool act = slot < QS;
-      const int g0 = wave * QS + slot;
-      for (int k = 0; k < K; ++k) {
-        const int n_k = cnt[k];  // uniform
-        if (n_k == 0) continue;  // unused: keeps its value
-        double rhs = 0.0, mat[CSP];
-#pragma unroll
-        for (int i = 0; i < CSP; ++i) mat[i] = 0.0;
-        if (act) {
-          for (int r = g0; r < n_k; r += NW * QS) {
-            const int pr = list[start[k] + r];
-            const int c = pr / P, p = pr - c * P;
-            const uint8_t* kc = cs + c * P;
-            const double* grow = Gm + ((size_t)p * P * CSP + j) * CSP;  // G[p][p2][j][.] at p2 * C's^2
-            constexpr int PB = CSP <= 4 ? 9 : 5;  // positions whose loads are in flight together
-            for (int p0 = 0; p0 < P; p0 += PB) {
-              int k2[PB];
-#pragma unroll
-              for (int u = 0; u < PB; ++u) k2[u] = p0 + u < P ? kc[p0 + u] : 0;
-              double gv[PB][CSP], dv[PB][CSP];
-#pragma unroll
-              for (int u = 0; u < PB; ++u)
-#pragma unroll
-                for (int i = 0; i < CSP; ++i) {
-                  gv[u][i] = p0 + u < P ? grow[(size_t)(p0 + u) * CSP * CSP + i] : 0.0;
-                  dv[u][i] = Ds[k2[u] * CSP + i];
-                }
-#pragma unroll
-              for (int u = 0; u < PB; ++u) {
-                if (p0 + u < P) {
-                  const bool on = k2[u] == k;
-                  double t = 0.0;
-#pragma unroll
-                  for (int i = 0; i < CSP; ++i) {
-                    t += gv[u][i] * dv[u][i];
-                    mat[i] += on ? gv[u][i] : 0.0;
-                  }
-                  rhs -= on ? 0.0 : t;
-                }
-              }
-            }
-          }
-          if constexpr (QS * CSP != kWave) {
-            double* w = wred + ((size_t)(wave * QS + slot) * CSP + j) * (CSP + 1);
-            w[0] = rhs;
-#pragma unroll
-            for (int i = 0; i < CSP; ++i) w[1 + i] = mat[i];
-          }
-        }
-        if constexpr (QS * CSP == kWave) {
-          // C's divides 64: the slots' sums by a fixed shuffle tree over the
-          // lanes of one row (stride C's); slot 0 then holds the wave's sums
-          double vals[CSP + 1];
-          vals[0] = rhs;
-#pragma unroll
-          for (int i = 0; i < CSP; ++i) vals[1 + i] = mat[i];
-#pragma unroll
-          for (int off = kWave / 2; off >= CSP; off >>= 1)
-#pragma unroll
-            for (int e = 0; e <= CSP; ++e) vals[e] += __shfl_down(vals[e], off, kWave);
-          if (slot == 0)
-#pragma unroll
-            for (int e = 0; e <= CSP; ++e) wpart[wave * NE + j * (CSP + 1) + e] = vals[e];
-        } else {
-          wave_sync_lds();
-          // this wave's slots, in order
-          const int used = max(0, min(QS, n_k - wave * QS));
-          for (int e = lane; e < NE; e += kWave) {
-            double v = 0.0;
-            for (int s0 = 0; s0 < used; s0 += 4) {
-              double w4[4];
-#pragma unroll
-              for (int u = 0; u < 4; ++u) w4[u] = s0 + u < used ? wred[(size_t)(wave * QS + s0 + u) * NE + e] : 0.0;
-#pragma unroll
-              for (int u = 0; u < 4; ++u)
-                if (s0 + u < used) v += w4[u];
-            }
-            wpart[wave * NE + e] = v;
-          }
-        }
-        __syncthreads();
-        if (wave == 0) {
-          double* rb = red;        // [C's] rhs
-          double* rA = red + CSP;  // [C's][C's] normal matrix
-          for (int e = lane; e < NE; e += kWave) {
-            double v = 0.0;
-#pragma unroll
-            for (int w = 0; w < NW; ++w) v += wpart[w * NE + e];
-            const int jr = e / (CSP + 1), col = e - jr * (CSP + 1);
-            if (col == 0)
-              rb[jr] = v;
-            else
-              rA[jr * CSP + col - 1] = v;
-          }
-          wave_sync_lds();
-          if (lane == 0) {
-            double b[CSP], x[CSP], Aw[CSP * CSP];
-#pragma unroll
-            for (int r = 0; r < CSP; ++r) b[r] = hs[k * CSP + r] + rb[r];
-            solve_rcp<CSP>(rA, b, Aw, x);
-#pragma unroll
-            for (int r = 0; r < CSP; ++r) Ds[k * CSP + r] = x[r];
-          }
-        }
-        __syncthreads();
-      }
-    }
-
-  }
-
-  for (int i = tid; i < K * CSP; i += kCThreads) D64[(size_t)m * K * CSP + i] = Ds[i];
-  for (int e = tid; e < P * K; e += kCThreads) {  // D_k^T G[p][p] D_k
+  for (int i = tid; i < R; i += kSolveThreads) D64[(size_t)m * R + i] = Ds[i];
+  const double* Gg = G + (size_t)m * P * P * CSP * CSP;
+  for (int e = tid; e < P * K; e += kSolveThreads) {  // D_k^T G[p][p] D_k
     const int p = e / K, k = e - p * K;
-    const double* Gpp = Gm + ((size_t)p * P + p) * CSP * CSP;
+    const double* Gpp = Gg + ((size_t)p * P + p) * CSP * CSP;
     double s2 = 0.0;
 #pragma unroll
     for (int r = 0; r < CSP; ++r) {
@@ -665,6 +1068,11 @@ __global__ __launch_bounds__(kCThreads) void ecc_dupdate_kernel(const double* __
     }
     qkg[e] = s2;
   }
+}
+
+template <int CSP> size_t solve_lds_bytes(int K) {
+  return ((size_t)2 * K * CSP + 2 * block_codewords<CSP>() * CSP * CSP + 2 * kColBlock * (kColBlock + 2) +
+          kSolveThreads) * 8 + (size_t)K * 4;
 }
 
 // Eq. (20)-(21): one wave per output channel c, the kernel positions in
@@ -813,23 +1221,32 @@ hipError_t launch_ecc_csp(const EccParams& q, const float* S, const float* T, fl
   const int sblocks = (int)(sbx * sby);  // the starting residual's block sums
   const int pblocks = ceil_div(npairs, kCThreads);
   // the Gram blocks go to LDS when they fit beside the rest
-  const bool gl = solve_lds_bytes<CSP>(q.K, npairs, q.P, true) <= kLdsBytes;
-  const size_t slds = solve_lds_bytes<CSP>(q.K, npairs, q.P, gl);
+  const bool gl = rows_lds_bytes<CSP, true>(q.K, npairs, q.P) <= kLdsBytes;
+  const size_t rlds = gl ? rows_lds_bytes<CSP, true>(q.K, npairs, q.P) : rows_lds_bytes<CSP, false>(q.K, npairs, q.P);
+  const size_t slds = solve_lds_bytes<CSP>(q.K);
   constexpr int NW = kCThreads / kWave;
   const size_t blds = ((size_t)q.K * CSP + NW * (kWave / CSP) * CSP + NW * CSP) * 8 + (size_t)NW * q.P;
-  if (slds > kLdsBytes || blds > kLdsBytes) return hipErrorInvalidValue;
-  auto dupdate = gl ? ecc_dupdate_kernel<CSP, true> : ecc_dupdate_kernel<CSP, false>;
+  if (rlds > kLdsBytes || slds > kLdsBytes || blds > kLdsBytes) return hipErrorInvalidValue;
+  auto rows = gl ? ecc_rows_kernel<CSP, true> : ecc_rows_kernel<CSP, false>;
+  auto solve = ecc_solve_kernel<CSP>;
   auto bupdate = ecc_bupdate_kernel<CSP>;
-  hipError_t e = allow_max_lds((const void*)dupdate);
+  hipError_t e = allow_max_lds((const void*)rows);
   if (e != hipSuccess) return e;
+  if ((e = allow_max_lds((const void*)solve)) != hipSuccess) return e;
   if ((e = allow_max_lds((const void*)bupdate)) != hipSuccess) return e;
   Scratch scratch;
   size_t bytes = 0;
-  const size_t szE = total * 8, szPart = (size_t)q.nchunks * npairs * CSP * 8, szH = (size_t)npairs * CSP * 8;
+  PassShape ps{};
+  const size_t pass_lds = pass_shape(q, &ps);
+  const int nchunks = pass_lds ? q.N * ps.parts : q.nchunks;
+  const int ablocks = pass_lds ? ceil_div(q.Ct, 64) * q.N * ps.parts : eblocks;  // block sums of a step's E^2
+  const size_t szE = total * 8, szPart = (size_t)nchunks * npairs * CSP * 8, szH = (size_t)npairs * CSP * 8;
   const size_t szG = (size_t)q.M * q.P * q.P * CSP * CSP * 8, szD = (size_t)q.M * q.K * CSP * 8;
-  const size_t szDelta = (size_t)npairs * CSP * 8, szOp = (size_t)std::max(eblocks, sblocks) * 8, szCt = (size_t)q.M * npairs;
+  const size_t szDelta = (size_t)npairs * CSP * 8, szOp = (size_t)std::max(std::max(eblocks, ablocks), sblocks) * 8, szCt = (size_t)q.M * npairs;
   const size_t szDold = (size_t)q.K * CSP * 8, szCold = (size_t)npairs, szQk = (size_t)q.P * q.K * 8;
-  for (size_t b : {szE, szPart, szH, szG, szD, szDelta, szOp, szCt, szDold, szCold, szQk})
+  const size_t szB = system_doubles<CSP>(q.K) * 8, szX = (size_t)q.K * CSP * CSP * 8, szUsed = (size_t)q.K * 4;
+  const size_t gram_lds = gram_lds_bytes(q), szGp = gram_lds ? kGramChunks * szG : 0;
+  for (size_t b : {szE, szPart, szH, szG, szD, szDelta, szOp, szCt, szDold, szCold, szQk, szB, szX, szDold, szUsed, szGp})
     bytes += (b + 255) & ~(size_t)255;
   if ((e = scratch.acquire(stream, bytes)) != hipSuccess) return e;
   char* w = scratch.get();
@@ -849,16 +1266,25 @@ hipError_t launch_ecc_csp(const EccParams& q, const float* S, const float* T, fl
   double* Dold = reinterpret_cast<double*>(take(szDold));
   uint8_t* cold = reinterpret_cast<uint8_t*>(take(szCold));
   double* qkg = reinterpret_cast<double*>(take(szQk));
+  double* B = reinterpret_cast<double*>(take(szB));
+  double* X = reinterpret_cast<double*>(take(szX));
+  double* r0 = reinterpret_cast<double*>(take(szDold));
+  int* used = reinterpret_cast<int*>(take(szUsed));
+  double* gpart = reinterpret_cast<double*>(take(szGp));
 
   const size_t ninit = std::max((size_t)q.M * q.K * CSP, (size_t)q.M * npairs);
   const unsigned iblocks = (unsigned)std::min<size_t>(8192, std::max<size_t>(1, ceil_div_z(ninit, kCThreads)));
   hipLaunchKernelGGL(ecc_init_kernel, dim3(iblocks), dim3(kCThreads), 0, stream, D, (const uint8_t*)codes, q, D64,
                      ct);
   if ((e = hipGetLastError()) != hipSuccess) return e;
-  const size_t ng = (size_t)q.M * q.P * q.P * CSP * CSP;
-  hipLaunchKernelGGL(ecc_gram_kernel, dim3((unsigned)ceil_div_z(ng, kCThreads)), dim3(kCThreads), 0, stream, S, q,
-                     G);
-  if ((e = hipGetLastError()) != hipSuccess) return e;
+  if (gram_lds) {
+    if ((e = launch_gram(S, q, gram_lds, gpart, G, stream)) != hipSuccess) return e;
+  } else {
+    const size_t ng = (size_t)q.M * q.P * q.P * CSP * CSP;
+    hipLaunchKernelGGL(ecc_gram_kernel, dim3((unsigned)ceil_div_z(ng, kCThreads)), dim3(kCThreads), 0, stream, S, q,
+                       G);
+    if ((e = hipGetLastError()) != hipSuccess) return e;
+  }
   hipLaunchKernelGGL(ecc_start_kernel<CSP>, dim3(sbx, sby), dim3(kCThreads), 0, stream, S, T, q,
                      (const double*)D64, (const uint8_t*)ct, E, opart);
   if ((e = hipGetLastError()) != hipSuccess) return e;
@@ -866,22 +1292,30 @@ hipError_t launch_ecc_csp(const EccParams& q, const float* S, const float* T, fl
   int ma = -1;
   for (int s = 0; s < sweeps; ++s) {
     for (int m = 0; m < q.M; ++m, ++nstep) {
-      if (ma >= 0) {
-        hipLaunchKernelGGL(ecc_apply_kernel<CSP>, dim3((unsigned)eblocks), dim3(kCThreads), 0, stream, S, q, ma,
-                           (const double*)delta, E, opart);
+      if (pass_lds) {
+        if ((e = launch_pass(S, q, ps, pass_lds, ma, m, delta, E, opart, part, stream)) != hipSuccess) return e;
+      } else {
+        if (ma >= 0) {
+          hipLaunchKernelGGL(ecc_apply_kernel<CSP>, dim3((unsigned)eblocks), dim3(kCThreads), 0, stream, S, q, ma,
+                             (const double*)delta, E, opart);
+          if ((e = hipGetLastError()) != hipSuccess) return e;
+        }
+        hipLaunchKernelGGL(ecc_corr_kernel<CSP>, dim3((unsigned)pblocks, (unsigned)q.nchunks), dim3(kCThreads), 0,
+                           stream, S, q, m, (const double*)E, part);
         if ((e = hipGetLastError()) != hipSuccess) return e;
       }
-      hipLaunchKernelGGL(ecc_corr_kernel<CSP>, dim3((unsigned)pblocks, (unsigned)q.nchunks), dim3(kCThreads), 0,
-                         stream, S, q, m, (const double*)E, part);
-      if ((e = hipGetLastError()) != hipSuccess) return e;
-      hipLaunchKernelGGL(ecc_reduce_kernel<CSP>, dim3((unsigned)pblocks), dim3(kCThreads), 0, stream,
-                         (const double*)part, q, m, (const double*)G, (const double*)D64, (const uint8_t*)ct, Hs);
+      hipLaunchKernelGGL(ecc_reduce_kernel<CSP>, dim3((unsigned)ceil_div(npairs * CSP, kCThreads)), dim3(kCThreads), 0,
+                         stream, (const double*)part, q, nchunks, m, (const double*)G, (const double*)D64,
+                         (const uint8_t*)ct, Hs);
       if ((e = hipGetLastError()) != hipSuccess) return e;
       for (int it = 0; it < inner; ++it) {
-        hipLaunchKernelGGL(dupdate, dim3(1), dim3(kCThreads), slds, stream, (const double*)Hs, q, m,
-                           (const double*)G, D64, (const uint8_t*)ct, it == 0 ? 1 : 0, Dold, cold, qkg,
-                           (const double*)opart, nstep == 0 ? sblocks : eblocks,
-                           objective ? objective + nstep : nullptr);
+        hipLaunchKernelGGL(rows, dim3((unsigned)q.K), dim3(rows_threads<CSP>()), rlds, stream, (const double*)Hs, q, m,
+                           (const double*)G, (const double*)D64, (const uint8_t*)ct, B, X, r0, used);
+        if ((e = hipGetLastError()) != hipSuccess) return e;
+        hipLaunchKernelGGL(solve, dim3(1), dim3(kSolveThreads), slds, stream, q, m, (const double*)G, D64,
+                           (const uint8_t*)ct, it == 0 ? 1 : 0, (const double*)B, (const double*)X,
+                           (const double*)r0, (const int*)used, Dold, cold, qkg, (const double*)opart,
+                           nstep == 0 ? sblocks : ablocks, objective ? objective + nstep : nullptr);
         if ((e = hipGetLastError()) != hipSuccess) return e;
         hipLaunchKernelGGL(bupdate, dim3((unsigned)ceil_div(q.Ct, NW)), dim3(kCThreads), blds, stream,
                            (const double*)Hs, q, m, (const double*)G, (const double*)D64, (const double*)qkg, ct,
@@ -891,13 +1325,15 @@ hipError_t launch_ecc_csp(const EccParams& q, const float* S, const float* T, fl
       ma = m;
     }
   }
-  if (ma >= 0) {
+  if (ma >= 0 && pass_lds) {
+    if ((e = launch_pass(S, q, ps, pass_lds, ma, -1, delta, E, opart, part, stream)) != hipSuccess) return e;
+  } else if (ma >= 0) {
     hipLaunchKernelGGL(ecc_apply_kernel<CSP>, dim3((unsigned)eblocks), dim3(kCThreads), 0, stream, S, q, ma,
                        (const double*)delta, E, opart);
     if ((e = hipGetLastError()) != hipSuccess) return e;
   }
   hipLaunchKernelGGL(ecc_finish_kernel, dim3(iblocks), dim3(kCThreads), 0, stream, (const double*)D64, q,
-                     (const uint8_t*)ct, D, codes, (const double*)opart, ma >= 0 ? eblocks : sblocks,
+                     (const uint8_t*)ct, D, codes, (const double*)opart, ma >= 0 ? ablocks : sblocks,
                      objective ? objective + nstep : nullptr);
   return hipGetLastError();
 }
