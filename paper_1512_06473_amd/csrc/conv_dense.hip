@@ -77,18 +77,22 @@ struct DenseParams {
   int N, Cs, H, W, M, K, Csp, Ct, dk, stride, pad, Ho, Wo;
   int S, sw;        // column strips per image, output columns per strip
   int PW, PH;       // staged grid: positions per row, rows per (image, strip)
-  int ss, gs;       // grid positions per output step, input positions per grid step
+  int ssx, ssy;     // grid positions per output step
+  int gsx, gsy;     // input positions per grid step
+  int xpack;        // the kernel's columns are channels of the staged positions
+  int kw;           // kernel columns that are taps: d_k, or 1 when packed
+  int VC;           // channels of a staged position: C_s, or C_s d_k when packed
   int Q;            // output slots N S Ho sw
   int SUB;          // 16-channel groups per chunk
   int chunks, taps, upt;  // chunks and units (chunk, tap, 16 channels) of a tile
   int tblocks, tiles, groups;
   int whole, shared0;  // tiles that each run makes alone; first of the shared tiles, cut at any unit
   int sruns;           // runs that take a piece of the shared tiles' units
-  int rows;         // staged grid positions per tile, a multiple of 64
+  int rows;         // staged grid positions per tile, a multiple of 16
   int pitch;        // bytes per staged position
   int relu;
   int per_run, extra;  // shared units per run; the first `extra` runs have one more
-  FastDiv d_sw, d_Ho, d_S, d_PW, d_PH, d_upt, d_upc, d_SUB, d_dk, d_tb;
+  FastDiv d_sw, d_Ho, d_S, d_PW, d_PH, d_upt, d_upc, d_SUB, d_kw, d_tb, d_Cs;
 };
 
 namespace {
@@ -171,15 +175,28 @@ struct Acc {
   f16v sum[kCF];        // a folded
 };
 
+// Channel v of a staged position at unit tap `tap`: input channel and tap of
+// the kernel (packed: v = kx C_s + c, tap = ky).
+__device__ __forceinline__ void channel_of(const DenseParams& p, int v, int tap, int& c, int& ktap) {
+  c = v;
+  ktap = tap;
+  if (p.xpack) {
+    const int kx = p.d_Cs.div(v);
+    c = v - kx * p.Cs;
+    ktap = tap * p.dk + kx;
+  }
+}
+
 // The weights of 8 channels for the fp32 form, decoded from the codes.
 __device__ __forceinline__ void decode8(const Ptrs& g, const DenseParams& p, int t, int tap, int ch0, float (&v)[8]) {
 #pragma unroll
   for (int j = 0; j < 8; ++j) {
-    const int ch = ch0 + j;
     v[j] = 0.f;
-    if (t < p.Ct && ch < p.Cs) {
+    if (t < p.Ct && ch0 + j < p.VC) {
+      int ch, ktap;
+      channel_of(p, ch0 + j, tap, ch, ktap);
       const int m = ch / p.Csp;
-      uint32_t code = code_at(g.codes, ((size_t)t * p.taps + tap) * p.M + m);
+      uint32_t code = code_at(g.codes, ((size_t)t * p.dk * p.dk + ktap) * p.M + m);
       code = min(code, (uint32_t)(p.K - 1));
       v[j] = g.D[((size_t)m * p.K + code) * p.Csp + (ch - m * p.Csp)];
     }
@@ -187,16 +204,17 @@ __device__ __forceinline__ void decode8(const Ptrs& g, const DenseParams& p, int
 }
 
 // Everything a workgroup keeps for one tile.
-template <int IT>
+template <int IT, bool XP>
 struct TileState {
   uint32_t voff[IT];    // byte offset in x of this lane's staged position (channel 0), or past the end
+  int ix[XP ? IT : 1];  // packed: its input column at kernel column 0
   int rowb[kCF];        // LDS byte offset of the lane's output position in each 32-column group, tap (0, 0)
 };
 
 // The products of units [u0, u1) of one tile in split form.  Returns false
 // when that form does not hold the inputs' range.
-template <int TW, int IT>
-__device__ __forceinline__ bool products(const TileState<IT>& ts, int tgrp, int u0, int u1, char* lds,
+template <int TW, int IT, bool XP>
+__device__ __forceinline__ bool products(const TileState<IT, XP>& ts, int tgrp, int u0, int u1, char* lds,
                                          uint32_t* exch, Acc& acc, int& x_exp) {
   const Args& args = args_again();
   const Ptrs& g = args.g;
@@ -208,7 +226,7 @@ __device__ __forceinline__ bool products(const TileState<IT>& ts, int tgrp, int 
   const int HW4 = p.H * p.W * 4;
   const int upc = p.taps * p.SUB;  // units per chunk
   const int buf_bytes = p.rows * p.pitch;
-  const int wgroups = p.rows >> 6;
+  const int wgroups = (p.rows + 63) >> 6;
   const int vecs = 2 * p.SUB;
   const __amdgpu_buffer_rsrc_t xres = __builtin_amdgcn_make_buffer_rsrc(
       const_cast<float*>(g.x), 0, (int)((size_t)p.N * p.Cs * HW4), 0x00020000);
@@ -233,6 +251,22 @@ __device__ __forceinline__ bool products(const TileState<IT>& ts, int tgrp, int 
 #pragma unroll
     for (int k = 0; k < IT; ++k) {
       const int ch0 = chunk * 16 * p.SUB + ivec[k] * 8;
+      if constexpr (XP) {
+        int kx = p.d_Cs.div(ch0), c = ch0 - kx * p.Cs;  // wave-uniform
+#pragma unroll
+        for (int j = 0; j < 8; ++j) {
+          const bool in = ivec[k] < vecs && kx < p.dk && (unsigned)(ts.ix[k] + kx) < (unsigned)p.W;
+          // a position outside the image has an offset past the buffer's end
+          // that no channel or column brings back into it
+          xv[k][j] = __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(
+              xres, in ? ts.voff[k] + (uint32_t)(c * HW4 + kx * 4) : kOOB, 0, 0));
+          if (++c == p.Cs) {
+            c = 0;
+            ++kx;
+          }
+        }
+        continue;
+      }
       const uint32_t off = ivec[k] < vecs && ch0 < p.Cs ? ts.voff[k] + (uint32_t)(ch0 * HW4) : kOOB;
 #pragma unroll
       for (int j = 0; j < 8; ++j)
@@ -248,7 +282,7 @@ __device__ __forceinline__ bool products(const TileState<IT>& ts, int tgrp, int 
     const float s = __uint_as_float((uint32_t)(e + 127) << 23);
 #pragma unroll
     for (int k = 0; k < IT; ++k) {
-      if (ivec[k] >= vecs) continue;  // wave-uniform
+      if (ivec[k] >= vecs || igrp[k] * 64 + lane >= p.rows) continue;
       h8 hi, lo;
 #pragma unroll
       for (int j = 0; j < 8; ++j) {
@@ -336,12 +370,12 @@ __device__ __forceinline__ bool products(const TileState<IT>& ts, int tgrp, int 
     const int v = u - c_first * upc;
     const int tap = p.d_SUB.div(v);
     sub = v - tap * p.SUB;
-    const int ky = p.d_dk.div(tap);
-    kx = tap - ky * p.dk;
+    const int ky = p.d_kw.div(tap);
+    kx = tap - ky * p.kw;
     off = (ky * p.PW + kx) * p.pitch + sub * 64;
   }
   const int lane_k = (lane >> 5) * 16;
-  const int tap_step = p.pitch - p.SUB * 64, row_step = (p.PW - p.dk) * p.pitch;
+  const int tap_step = p.pitch - p.SUB * 64, row_step = (p.PW - p.kw) * p.pitch;
   int parity = 0;  // LDS buffer of the current chunk
   int folded = 0;  // steps since the last fold
 
@@ -372,7 +406,7 @@ __device__ __forceinline__ bool products(const TileState<IT>& ts, int tgrp, int 
       if (++sub == p.SUB) {
         sub = 0;
         off += tap_step;
-        if (++kx == p.dk) {
+        if (++kx == p.kw) {
           kx = 0;
           off += row_step;
         }
@@ -460,14 +494,17 @@ __device__ __forceinline__ f16v products_f32(int tgrp, int u0, int u1, int n, in
   for (int u = u0; u < u1; ++u) {
     const int c = p.d_upc.div(u), v = u - c * upc;
     const int tap = p.d_SUB.div(v), sub = v - tap * p.SUB;
-    const int yy = iy + tap / p.dk, xx = ix + tap % p.dk;
     const int ch0 = (c * p.SUB + sub) * 16 + (lane >> 5) * 8;
-    const bool in = yy >= 0 && yy < p.H && xx >= 0 && xx < p.W;
     float av[8], bv[8];
     decode8(g, p, tgrp * 32 + (lane & 31), tap, ch0, av);
 #pragma unroll
-    for (int j = 0; j < 8; ++j)
-      bv[j] = in && ch0 + j < p.Cs ? g.x[(((size_t)n * p.Cs + ch0 + j) * p.H + yy) * p.W + xx] : 0.f;
+    for (int j = 0; j < 8; ++j) {
+      int ch, ktap;
+      channel_of(p, ch0 + j, tap, ch, ktap);
+      const int yy = iy + ktap / p.dk, xx = ix + ktap % p.dk;
+      const bool in = ch0 + j < p.VC && yy >= 0 && yy < p.H && xx >= 0 && xx < p.W;
+      bv[j] = in ? g.x[(((size_t)n * p.Cs + ch) * p.H + yy) * p.W + xx] : 0.f;
+    }
 #pragma unroll
     for (int j = 0; j < 8; ++j) acc = __builtin_amdgcn_mfma_f32_32x32x2f32(av[j], bv[j], acc, 0, 0, 0);
   }
@@ -483,10 +520,10 @@ __device__ __forceinline__ Slot slot_of(const DenseParams& p, int q) {
   const int row = p.d_sw.div(q), xl = q - row * p.sw;
   const int pl = p.d_Ho.div(row), yo = row - pl * p.Ho;
   const int n = p.d_S.div(pl);
-  return {n, yo, (pl - n * p.S) * p.sw + xl, (pl * p.PH + yo * p.ss) * p.PW + xl * p.ss};
+  return {n, yo, (pl - n * p.S) * p.sw + xl, (pl * p.PH + yo * p.ssy) * p.PW + xl * p.ssx};
 }
 
-template <int TW, int IT>
+template <int TW, int IT, bool XP>
 __global__ __launch_bounds__(kThreads, 2) void conv_dense_kernel(Args unused) {
   extern __shared__ float4 smem4[];
   constexpr int KG = kWaves / TW;
@@ -523,17 +560,18 @@ __global__ __launch_bounds__(kThreads, 2) void conv_dense_kernel(Args unused) {
     const int tb = tile - ptile * p.tblocks, q0 = ptile * kNT;
 
     const int g0 = slot_of(p, q0).grid;
-    TileState<IT> ts;
+    TileState<IT, XP> ts;
 #pragma unroll
     for (int j = 0; j < kCF; ++j) ts.rowb[j] = (slot_of(p, min(q0 + 32 * j + (lane & 31), p.Q - 1)).grid - g0) * p.pitch;
-    const int wgroups = p.rows >> 6;
+    const int wgroups = (p.rows + 63) >> 6;
 #pragma unroll
     for (int k = 0; k < IT; ++k) {
       const int f = g0 + ((wave + kWaves * k) % wgroups) * 64 + lane;
       const int row = p.d_PW.div(f), c = f - row * p.PW;
       const int pl = p.d_PH.div(row), n = p.d_S.div(pl);
-      const int iy = (row - pl * p.PH) * p.gs - p.pad, ix = (pl - n * p.S) * p.sw * p.stride + c * p.gs - p.pad;
-      const bool in = n < p.N && iy >= 0 && iy < p.H && ix >= 0 && ix < p.W;
+      const int iy = (row - pl * p.PH) * p.gsy - p.pad, ix = (pl - n * p.S) * p.sw * p.stride + c * p.gsx - p.pad;
+      const bool in = n < p.N && iy >= 0 && iy < p.H && (XP || (ix >= 0 && ix < p.W));
+      if constexpr (XP) ts.ix[k] = in ? ix : -(1 << 30);
       ts.voff[k] = in ? (uint32_t)(n * p.Cs * p.H * p.W + iy * p.W + ix) * 4u : kOOB;
     }
 
@@ -547,7 +585,7 @@ __global__ __launch_bounds__(kThreads, 2) void conv_dense_kernel(Args unused) {
     if (split_form) {
       Acc acc;
       int x_exp;
-      split_form = products<TW, IT>(ts, tgrp, a0, a1, lds, exch, acc, x_exp);
+      split_form = products<TW, IT, XP>(ts, tgrp, a0, a1, lds, exch, acc, x_exp);
       // The reduction groups' sums, added in group order.
       const int ue = -(x_exp + head.scale_exp);
       for (int k = 0; k < KG; ++k) {
@@ -704,17 +742,18 @@ __global__ __launch_bounds__(256) void dense_weights_kernel(const float* __restr
     const int t = tg * 32 + (lane & 31);
     const int ch0 = (chunk * p.SUB + sub) * 16 + (lane >> 5) * 8;
     h8 hi, lo;
-    int m_prev = -1;
+    int at = -1;  // the code last read
     uint32_t code = 0;
 #pragma unroll
     for (int j = 0; j < 8; ++j) {
-      const int ch = ch0 + j;
       float x = 0.f;
-      if (t < p.Ct && ch < p.Cs) {
+      if (t < p.Ct && ch0 + j < p.VC) {
+        int ch, ktap;
+        channel_of(p, ch0 + j, tap, ch, ktap);
         const int m = ch / p.Csp;
-        if (m != m_prev) {
-          code = min(code_at(codes, ((size_t)t * p.taps + tap) * p.M + m), (uint32_t)(p.K - 1));
-          m_prev = m;
+        if (ktap * p.M + m != at) {
+          at = ktap * p.M + m;
+          code = min(code_at(codes, (size_t)t * p.dk * p.dk * p.M + at), (uint32_t)(p.K - 1));
         }
         x = D[((size_t)m * p.K + code) * p.Csp + (ch - m * p.Csp)] * sc;
       }
@@ -746,21 +785,21 @@ bool set_window(const ConvShape& s, DenseParams* p) {
   for (int S = 1; S <= 16 && S <= s.Wo; ++S) {
     const int sw = ceil_div(s.Wo, S);
     if ((S - 1) * sw >= s.Wo) continue;
-    int PH = (s.Ho - 1) * p->ss + s.dk, PW = (sw - 1) * p->ss + s.dk;
-    if (S == 1 && p->gs == 1) {  // neighbouring rows and images share their zero halos
-      PW -= std::min(s.pad, std::max(0, PW - s.pad - s.W));
+    int PH = (s.Ho - 1) * p->ssy + s.dk, PW = (sw - 1) * p->ssx + p->kw;
+    if (S == 1 && p->gsy == 1) {  // neighbouring rows and images share their zero halos
+      if (!p->xpack) PW -= std::min(s.pad, std::max(0, PW - s.pad - s.W));
       PH -= std::min(s.pad, std::max(0, PH - s.pad - s.H));
     }
-    // The grid span of kNT consecutive output slots: steps of `ss`, plus what
+    // The grid span of kNT consecutive output slots: steps of `ssx`, plus what
     // a row end and an image end add.
     const long long rc = (kNT - 1 + sw - 1) / sw, ic = (kNT - 1 + (long long)sw * s.Ho - 1) / ((long long)sw * s.Ho);
-    const long long span = (kNT - 1) * (long long)p->ss + rc * std::max(0, p->ss * PW - sw * p->ss) +
-                           ic * std::max(0, (PH - s.Ho * p->ss) * PW) + (long long)(s.dk - 1) * (PW + 1) + 1;
+    const long long span = (kNT - 1) * (long long)p->ssx + rc * std::max(0, p->ssy * PW - sw * p->ssx) +
+                           ic * std::max(0, (PH - s.Ho * p->ssy) * PW) + (long long)(s.dk - 1) * PW + p->kw;
     if (span > 4096) continue;
-    const int rows = (int)(span + 63) / 64 * 64;
+    const int rows = (int)(span + 15) / 16 * 16;
     const size_t bytes = (size_t)2 * rows * p->pitch;
     if (bytes > kLdsBytes - 256) continue;
-    const double score = (double)S * sw / s.Wo * (1.0 + rows / 2560.0) * (bytes > kLdsBytes / 2 - 256 ? 1.5 : 1.0);
+    const double score = (double)S * sw / s.Wo * (1.0 + ceil_div(rows, 64) / 40.0) * (bytes > kLdsBytes / 2 - 256 ? 1.5 : 1.0);
     if (p->rows && score >= best) continue;
     best = score;
     p->S = S; p->sw = sw; p->PW = PW; p->PH = PH; p->rows = rows;
@@ -773,24 +812,32 @@ bool make_plan(const ConvShape& s, DensePlan* out) {
   DenseParams p{};
   p.N = s.N; p.Cs = s.Cs; p.H = s.H; p.W = s.W; p.M = s.M; p.K = s.K; p.Csp = s.Csp; p.Ct = s.Ct;
   p.dk = s.dk; p.stride = s.stride; p.pad = s.pad; p.Ho = s.Ho; p.Wo = s.Wo;
-  p.taps = s.dk * s.dk;
   if (s.dk > 15 || s.pad >= s.dk) return false;
-  // The staged grid is the input's, or for 1x1 kernels only the positions that
-  // outputs read.
-  p.ss = s.dk == 1 ? 1 : s.stride;
-  p.gs = s.dk == 1 ? s.stride : 1;
+  // The staged grid is the input's; for 1x1 kernels only the positions that
+  // outputs read; with few input channels a staged position holds the whole
+  // kernel row at its output column (d_k C_s channels), so that the 16-channel
+  // units are not mostly padding (AlexNet conv1, 3 channels, 11 x 11: 33 units
+  // of 16 instead of 121).
+  p.xpack = s.dk > 1 && s.Cs < 8;
+  p.kw = p.xpack ? 1 : s.dk;
+  p.VC = p.xpack ? s.Cs * s.dk : s.Cs;
+  p.taps = s.dk * p.kw;
+  p.ssx = s.dk == 1 || p.xpack ? 1 : s.stride;
+  p.ssy = s.dk == 1 ? 1 : s.stride;
+  p.gsx = s.dk == 1 || p.xpack ? s.stride : 1;
+  p.gsy = s.dk == 1 ? s.stride : 1;
   // Chunks of more channels where there are few taps to reuse a staged row;
   // fewer where the window's rows would not fit a thread's staging registers.
   int items = 0;
   for (p.SUB = p.taps == 1 ? 4 : p.taps <= 4 ? 2 : 1; p.SUB > 0; --p.SUB) {
-    if (p.SUB > 1 && 16 * (p.SUB - 1) >= s.Cs) continue;
+    if (p.SUB > 1 && 16 * (p.SUB - 1) >= p.VC) continue;
     p.pitch = 64 * p.SUB + 16;
     if (!set_window(s, &p)) continue;
-    items = ceil_div(p.rows / 64 * 2 * p.SUB, kWaves);
+    items = ceil_div(ceil_div(p.rows, 64) * 2 * p.SUB, kWaves);
     if (items <= 4) break;
   }
   if (p.SUB == 0) return false;
-  p.chunks = ceil_div(s.Cs, 16 * p.SUB);
+  p.chunks = ceil_div(p.VC, 16 * p.SUB);
   p.upt = p.chunks * p.taps * p.SUB;
   const int TW = s.Ct <= 64 ? 2 : 4;
   const size_t sums = (size_t)32 * TW * kSumStride * 4;
@@ -825,7 +872,7 @@ bool make_plan(const ConvShape& s, DensePlan* out) {
   p.extra = pieces ? (int)(left * p.upt % pieces) : 0;
   out->partial_bytes = (size_t)(pieces + left) * tile_bytes;
   p.d_sw = FastDiv(p.sw); p.d_Ho = FastDiv(p.Ho); p.d_S = FastDiv(p.S); p.d_PW = FastDiv(p.PW); p.d_PH = FastDiv(p.PH);
-  p.d_upt = FastDiv(p.upt); p.d_upc = FastDiv(p.taps * p.SUB); p.d_SUB = FastDiv(p.SUB); p.d_dk = FastDiv(p.dk);
+  p.d_upt = FastDiv(p.upt); p.d_upc = FastDiv(p.taps * p.SUB); p.d_SUB = FastDiv(p.SUB); p.d_kw = FastDiv(p.kw); p.d_Cs = FastDiv(p.Cs);
   p.d_tb = FastDiv(p.tblocks);
   out->p = p;
   out->TW = TW;
@@ -835,7 +882,7 @@ bool make_plan(const ConvShape& s, DensePlan* out) {
 
 template <int TW, int IT>
 hipError_t launch_one(const DensePlan& pl, const Ptrs& g, hipStream_t stream, LaunchTimer* timer) {
-  auto k = conv_dense_kernel<TW, IT>;
+  auto k = pl.p.xpack ? conv_dense_kernel<TW, IT, true> : conv_dense_kernel<TW, IT, false>;
   hipError_t e = allow_max_lds((const void*)k);
   if (e != hipSuccess) return e;
   return timed_launch(timer, k, dim3((pl.p.groups + 7) / 8 * 8), dim3(kThreads), (uint32_t)pl.lds, stream, Args{g, pl.p});
@@ -905,12 +952,16 @@ bool conv_dense_supported(const ConvShape& s) {
 //     for its first and last microseconds: 256 products per output, with
 //     64 output channels or fewer 512 (a tile then stages twice the input per
 //     product: 32 -> 64 channels on 28 x 28, 64 images: 33 us against 35 us).
+//     A packed kernel row (fewer than 8 input channels) is padded to whole
+//     units and stages several rows per output row: from 1e9 multiply-adds on
+//     (AlexNet conv1: 38 us against 44 us for 4 images, 71 against 60 us for
+//     16, 263 against 182 us for 64).
 bool conv_dense_better(const ConvShape& s, int table_chain) {
   if (!conv_dense_supported(s)) return false;
   const int products = s.Cs * s.dk * s.dk, entries = s.M * s.dk * s.dk;
   if (table_chain == 0) return entries >= 48;
   const double macs = (double)s.N * s.Ho * s.Wo * s.Ct * products;
-  return table_chain >= 48 && products >= (s.Ct <= 64 ? 512 : 256) && macs >= (s.Csp <= 4 ? 1.5e8 : 3e8);
+  return table_chain >= 48 && products >= (s.Ct <= 64 ? 512 : 256) && macs >= (s.dk > 1 && s.Cs < 8 ? 1e9 : s.Csp <= 4 ? 1.5e8 : 3e8);
 }
 
 size_t conv_dense_workspace(const ConvShape& s) {

@@ -33,6 +33,10 @@ SHAPES = [
     (1, 48, 12, 12, 24, 3, 1, 2, 6, 100),     # pad 2
     (5, 128, 7, 7, 256, 3, 1, 1, 4, 128),     # tiles across images
     (40, 48, 13, 13, 200, 3, 1, 1, 4, 64),    # whole tiles and shared ones
+    (2, 3, 45, 47, 97, 11, 4, 2, 3, 64),      # few input channels: kernel rows packed into positions
+    (3, 4, 20, 23, 40, 5, 1, 2, 4, 32),
+    (1, 6, 17, 19, 33, 3, 2, 1, 2, 50),
+    (1, 1, 9, 120, 5, 3, 1, 1, 1, 9),
 ]
 
 
@@ -115,12 +119,15 @@ def test_dense_wide_range(dev, oracle, kind):
     assert np.all(np.abs(y.astype(np.float64) - ref) <= RTOL * A + 1e-30)
 
 
-@pytest.mark.parametrize("where", ["x", "D"])
+@pytest.mark.parametrize("where", ["x", "D", "packed rows"])
 def test_dense_non_finite(dev, where, monkeypatch):
     """Infinities and NaN reach exactly the outputs they reach through the
     table kernel; the others stay within the bound of it."""
     rng, x, D, codes = _layer(7)
-    if where == "x":
+    if where == "packed rows":
+        x, D, codes = wl.random_conv(rng, 2, 4, 21, 22, 70, 3, 1, 1, 4, 128)
+        x[0, 1, 3, 4], x[0, 3, 20, 0], x[1, 2, 20, 21] = np.inf, -np.inf, np.nan
+    elif where == "x":
         x[0, 5, 3, 4], x[0, 40, 12, 0], x[1, 63, 12, 12] = np.inf, -np.inf, np.nan
     else:
         D[3, 17, 1], D[9, 100, 0] = np.inf, np.nan
