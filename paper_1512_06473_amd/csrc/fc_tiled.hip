@@ -482,6 +482,11 @@ bool fc_tiled_supported(int N, int Cs, int M, int K, int Csp, int Ct) {
   return make_fc_plan(N, Cs, M, K, Csp, Ct, &pl);
 }
 
+int fc_tiled_splits(int N, int Cs, int M, int K, int Csp, int Ct) {
+  FcPlan pl;
+  return make_fc_plan(N, Cs, M, K, Csp, Ct, &pl) ? pl.p.splits : 0;
+}
+
 namespace {
 
 bool fc_plan(int N, int Cs, int M, int K, int Csp, int Ct, int relu, FcPlan* pl) {

@@ -520,7 +520,7 @@ qcnn_status qcnn_fc_plan_create(int N, int C_s, const float* codebooks, int M, i
   proto.fc = true;
   proto.sh = ConvShape{N, C_s, 1, 1, M, K, Csp, C_t, 1, 1, 0, 1, 1};
   proto.relu = relu ? 1 : 0;
-  proto.relaid = qcnn::fc_tiled_supported(N, C_s, M, K, Csp, C_t);
+  proto.relaid = qcnn::fc_relays(N, C_s, M, K, Csp, C_t);
   proto.bits = bits;
   proto.nx = nx;
   proto.ny = ny;

@@ -222,6 +222,8 @@ hipError_t timed_launch(LaunchTimer* t, F kernel, const dim3& grid, const dim3& 
 // FC layer with tables of 4 subspaces per phase and 128-bit gathers over
 // images (fc_tiled.hip): K <= 64, C's <= 8.
 bool fc_tiled_supported(int N, int Cs, int M, int K, int Csp, int Ct);
+// Workgroups its subspaces are split over (1: no partial sums), 0 if unsupported.
+int fc_tiled_splits(int N, int Cs, int M, int K, int Csp, int Ct);
 hipError_t launch_fc_tiled(int N, int Cs, int M, int K, int Csp, int Ct, const float* x, const float* D,
                            CodeStream codes, const float* bias, int relu, float* y, hipStream_t stream);
 // The same call in two parts (as for the flat conv kernel): the re-laid
@@ -233,6 +235,14 @@ hipError_t launch_fc_tiled_codes(int N, int Cs, int M, int K, int Csp, int Ct, C
 hipError_t launch_fc_tiled_relaid(int N, int Cs, int M, int K, int Csp, int Ct, const float* x, const float* D,
                                   const uint32_t* codes4, const float* bias, int relu, float* y,
                                   hipStream_t stream);
+
+// FC layer straight from the code stream (fc_few.hip): few images, or K or C's
+// past fc_tiled's.  fc_relays: the layer's codes are re-laid for fc_tiled, else
+// fc_few reads the code stream itself.
+bool fc_few_better(int N, int Cs, int M, int K, int Csp, int Ct);
+hipError_t launch_fc_few(int N, int Cs, int M, int K, int Csp, int Ct, const float* x, const float* D,
+                         CodeStream codes, const float* bias, int relu, float* y, hipStream_t stream);
+bool fc_relays(int N, int Cs, int M, int K, int Csp, int Ct);
 
 // Parameter quantization (quantize.hip); objective arrays are device float64.
 hipError_t launch_pq_assign(int Ct, int Cs, int dk, const float* W, const float* D, int M, int K, int Csp,
