@@ -21,7 +21,9 @@
 //   staged in LDS with coalesced loads and sorted stably by code; thread k
 //   adds the sub-vectors coded k in float64 in sub-vector order, so each mean
 //   is summed in a fixed order and rounded once to fp32.  A sub-codeword that
-//   no sub-vector chose keeps its value.
+//   no sub-vector chose keeps its value.  Fully-connected layers of many
+//   subspaces take four of them per workgroup (pq_update_fc_kernel), with the
+//   same order of every sum.
 #include "qcnn_internal.h"
 
 namespace qcnn {
@@ -394,6 +396,194 @@ __global__ __launch_bounds__(kQThreads) void pq_update_kernel(const float* __res
   }
 }
 
+// Orders a wave's LDS accesses for the compiler: the wave's own are carried out
+// in order.
+__device__ __forceinline__ void wave_order() { __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront"); }
+
+// Update of a fully-connected layer: a workgroup takes four neighbouring
+// subspaces, a wave each.  The four waves stage a chunk of weight rows together
+// (lanes four by four read the 4 C'_s contiguous floats of a row, so a cache
+// line is fetched for four subspaces at once; the next chunk's loads are in
+// flight meanwhile), then each wave sorts and sums its own subspace without
+// meeting the others: a sub-vector's rank among those of its code comes from
+// ballots and the running count, one scan over the codes gives each its first
+// place, the sub-vectors are put in that order in place, and lane l adds the pairs (k, j) l, l + 64, ... in sub-vector order,
+// float64, as pq_update_kernel does and with the same bits.
+// Bound by the ranks and sums of a chunk's chain (8 chunks for fc6; without the
+// sums 53 us) with 2 to 3 workgroups per CU.
+// fc6 of AlexNet (9216 to 4096, C's = 4, K = 32, 151 MB of weights): 112 us in
+// pq_update_kernel, where a workgroup's single subspace used 16 of every 128
+// bytes and 1 code of every 128 that it fetched, 68 us here.
+constexpr int kUpSubs = 4;
+typedef float f4v __attribute__((ext_vector_type(4)));  // (an array of float4 goes to memory across the fences)
+
+// BITS: of a code, K <= 2^BITS.
+template <int CSP, int BITS>
+__global__ __launch_bounds__(kQThreads) void pq_update_fc_kernel(const float* __restrict__ W,
+                                                               const uint8_t* __restrict__ codes, QShape q,
+                                                               float* __restrict__ D, int* __restrict__ counts) {
+  constexpr int ROWS = 2048 / CSP;               // rows per chunk
+  constexpr int Q = CSP / 4;                     // 16-byte loads per sub-vector
+  constexpr int RPP = kQThreads / (kUpSubs * Q); // rows per pass of the workgroup's loads
+  constexpr int NL = ROWS / RPP;                 // loads per thread and chunk
+  constexpr int NC = ROWS / kQThreads;           // code rows per thread and chunk
+  constexpr int NG = ROWS / kWave;               // ballot groups per wave and chunk
+  static_assert(kQThreads / kWave == kUpSubs, "a wave per subspace");
+  // nine rows past the chunk: a sum's last eight reads may pass its list's end,
+  // and the four subspaces' rows lie on different banks
+  __shared__ __attribute__((aligned(16))) float sv[kUpSubs][(ROWS + 9) * CSP];
+  __shared__ uint32_t sc[ROWS];                  // the four codes of a row
+  __shared__ uint16_t place[kUpSubs][256];       // counts, then first places, of the codes
+  __shared__ uint16_t count[kUpSubs][256];
+  const int sets = (q.M + kUpSubs - 1) / kUpSubs, per_xcd = (sets + 7) / 8;
+  const int set = (int)(blockIdx.x & 7) * per_xcd + (int)(blockIdx.x >> 3);
+  if (set >= sets) return;  // whole workgroup, before any barrier
+  const int tid = threadIdx.x, lane = tid & (kWave - 1), wave = tid / kWave;
+  const int m0 = set * kUpSubs, m = m0 + wave;
+  const int npairs = q.K * CSP;
+  constexpr int NREG = 4;                        // pairs per lane held in registers: K C'_s <= 256
+  double sum[NREG];
+  int total[NREG];
+#pragma unroll
+  for (int u = 0; u < NREG; ++u) {
+    sum[u] = 0.0;
+    total[u] = 0;
+  }
+  // this thread's place in the loads: 16 bytes of row lrow, subspace lsub
+  const int lq = tid % Q, lsub = tid / Q % kUpSubs, lrow = tid / (Q * kUpSubs);
+  const float* src = W + (size_t)min(m0 + lsub, q.M - 1) * CSP + 4 * lq;
+  const bool whole = (q.M & 3) == 0;             // a row's four codes are one aligned dword
+  f4v v[NL];
+  uint32_t cw[NC];
+  auto load = [&](int base) {  // rows past C_t read the last one
+#pragma unroll
+    for (int u = 0; u < NL; ++u)
+      v[u] = *reinterpret_cast<const f4v*>(src + (size_t)min(base + lrow + u * RPP, q.n - 1) * q.Cs);
+#pragma unroll
+    for (int u = 0; u < NC; ++u) {
+      const uint8_t* at = codes + (size_t)min(base + tid + u * kQThreads, q.n - 1) * q.M + m0;
+      if (whole) {
+        cw[u] = *reinterpret_cast<const uint32_t*>(at);
+      } else {
+        cw[u] = 0;
+#pragma unroll
+        for (int b = 0; b < kUpSubs; ++b)
+          if (m0 + b < q.M) cw[u] |= (uint32_t)at[b] << (8 * b);
+      }
+    }
+  };
+  load(0);
+  for (int base = 0; base < q.n; base += ROWS) {
+    const int len = min(ROWS, q.n - base);
+    __syncthreads();  // the previous chunk is done
+#pragma unroll
+    for (int u = 0; u < NL; ++u)
+      *reinterpret_cast<f4v*>(&sv[lsub][(lrow + u * RPP) * CSP + 4 * lq]) = v[u];
+#pragma unroll
+    for (int u = 0; u < NC; ++u) sc[tid + u * kQThreads] = cw[u];
+    for (int k = lane; k < q.K; k += kWave) place[wave][k] = 0;
+    __syncthreads();
+    if (base + ROWS < q.n) load(base + ROWS);
+    // from here on each wave works on its own rows of LDS, in order
+    uint32_t mine[NG];  // code << 16 | rank, ~0: in no sum
+    int below[NG], group[NG];
+#pragma unroll
+    for (int g = 0; g < NG; ++g) {
+      const uint32_t c = (sc[g * kWave + lane] >> (8 * wave)) & 0xffu;
+      const bool valid = g * kWave + lane < len && (int)c < q.K;
+      const uint64_t in = __ballot(valid);
+      uint32_t lo = (uint32_t)in, hi = (uint32_t)(in >> 32);  // the lanes that hold this lane's code
+#pragma unroll
+      for (int b = 0; b < BITS; ++b) {
+        const int bit = (int)(c << (31 - b)) >> 31;  // 0 or -1
+        const uint64_t ones = __ballot(bit != 0);
+        lo &= ~((uint32_t)ones ^ (uint32_t)bit);
+        hi &= ~((uint32_t)(ones >> 32) ^ (uint32_t)bit);
+      }
+      below[g] = (int)__builtin_amdgcn_mbcnt_hi(hi, __builtin_amdgcn_mbcnt_lo(lo, 0));
+      group[g] = __popc(lo) + __popc(hi);
+      mine[g] = valid ? c : ~0u;
+    }
+    f4v row[NG][Q];
+#pragma unroll
+    for (int g = 0; g < NG; ++g) {
+      const bool valid = mine[g] != ~0u;
+      const uint32_t c = mine[g];
+      wave_order();
+      const int before = valid ? place[wave][c] : 0;
+      wave_order();
+      if (valid && below[g] == 0) place[wave][c] = (uint16_t)(before + group[g]);  // the group's lowest lane
+      if (valid) mine[g] = c << 16 | (uint32_t)(before + below[g]);
+#pragma unroll
+      for (int x = 0; x < Q; ++x)
+        row[g][x] = *reinterpret_cast<const f4v*>(&sv[wave][(g * kWave + lane) * CSP + 4 * x]);
+    }
+    wave_order();
+    // first places: an exclusive scan of the counts, 64 codes at a time
+    int at = 0;
+    for (int k0 = 0; k0 < q.K; k0 += kWave) {
+      const int k = k0 + lane, own = k < q.K ? place[wave][k] : 0;
+      int incl = own;
+#pragma unroll
+      for (int off = 1; off < kWave; off <<= 1) {
+        const int o = __shfl_up(incl, off, kWave);
+        if (lane >= off) incl += o;
+      }
+      if (k < q.K) {
+        place[wave][k] = (uint16_t)(at + incl - own);
+        count[wave][k] = (uint16_t)own;
+      }
+      at += __shfl(incl, kWave - 1, kWave);
+    }
+    wave_order();
+    // the chunk's sub-vectors in the order of their codes, in place
+#pragma unroll
+    for (int g = 0; g < NG; ++g)
+      if (mine[g] != ~0u)
+#pragma unroll
+        for (int x = 0; x < Q; ++x)
+          *reinterpret_cast<f4v*>(
+              &sv[wave][(place[wave][mine[g] >> 16] + (mine[g] & 0xffffu)) * CSP + 4 * x]) = row[g][x];
+    wave_order();
+#pragma unroll
+    for (int u = 0; u < NREG; ++u) {
+      const int pr = lane + u * kWave;
+      if (pr < npairs) {
+        const int k = pr / CSP, n_k = count[wave][k];
+        const float* list = &sv[wave][place[wave][k] * CSP + pr % CSP];
+        double acc = sum[u];
+        int r = 0;
+        for (; r + 8 <= n_k; r += 8) {  // eight members' reads first, then the adds in order
+          float x8[8];
+#pragma unroll
+          for (int x = 0; x < 8; ++x) x8[x] = list[(r + x) * CSP];
+#pragma unroll
+          for (int x = 0; x < 8; ++x) acc += (double)x8[x];
+        }
+        if (r < n_k) {  // the last ones; adding +0 leaves a sum that began at +0 as it is
+          float x8[8];
+#pragma unroll
+          for (int x = 0; x < 7; ++x) x8[x] = list[(r + x) * CSP];
+#pragma unroll
+          for (int x = 0; x < 7; ++x) acc += (double)(r + x < n_k ? x8[x] : 0.f);
+        }
+        sum[u] = acc;
+        total[u] += n_k;
+      }
+    }
+  }
+  if (m >= q.M) return;
+#pragma unroll
+  for (int u = 0; u < NREG; ++u) {
+    const int pr = lane + u * kWave;
+    if (pr < npairs) {
+      const int k = pr / CSP, j = pr % CSP;
+      if (total[u]) D[((size_t)m * q.K + k) * CSP + j] = (float)(sum[u] / (double)total[u]);
+      if (counts && j == 0) counts[(size_t)m * q.K + k] = total[u];
+    }
+  }
+}
+
 QShape make_shape(int Ct, int Cs, int dk, int M, int K, int Csp) {
   return QShape{Ct, Cs, dk * dk, M, K, Csp, Ct * dk * dk};
 }
@@ -440,6 +630,18 @@ hipError_t assign(const QShape& q, const float* W, const float* D, uint8_t* code
 
 hipError_t update(const QShape& q, const float* W, const uint8_t* codes, float* D, int* counts,
                   hipStream_t stream) {
+  // Four subspaces per workgroup: whole 16-byte loads of contiguous, 16-byte
+  // aligned sub-vectors, at most four sums per lane, and subspaces for three
+  // workgroups on every four CUs.  us, 4096 rows, K = 32, one subspace per
+  // workgroup -> four: C's = 4, 512 subspaces 42.8 -> 41.3, 256 35 -> 39; 768
+  // 51 -> 42; 2304 119 -> 69; C's = 8, 512 61 -> 64, 1024 83 -> 66.
+  if (q.P == 1 && (q.Csp == 4 || q.Csp == 8) && q.M >= 768 && q.Cs % 4 == 0 && q.K * q.Csp <= 256 &&
+      ((uintptr_t)W & 15) == 0 && ((uintptr_t)codes & 3) == 0) {
+    auto f = q.Csp == 8 ? pq_update_fc_kernel<8, 5> : q.K <= 32 ? pq_update_fc_kernel<4, 5> : pq_update_fc_kernel<4, 6>;
+    const int sets = ceil_div(q.M, kUpSubs);
+    hipLaunchKernelGGL(f, dim3((unsigned)(ceil_div(sets, 8) * 8)), dim3(kQThreads), 0, stream, W, codes, q, D, counts);
+    return hipGetLastError();
+  }
   auto k = pq_update_kernel<0>;
   if (q.Csp == 4) k = pq_update_kernel<4>;
   else if (q.Csp == 8) k = pq_update_kernel<8>;
