@@ -456,7 +456,7 @@ __global__ __launch_bounds__(kCThreads) void ecc_corr_kernel(const float* __rest
 // written once, take a third of that); apply and correlation as kernels of
 // their own took 35 + 60 us at 384 channels, 32 x 13 x 13 outputs, 3x3, C's = 4.
 struct PassShape {
-  int parts, tiles;  // 16-position tiles per workgroup, workgroups per image and channel block
+  int parts, tiles;  // workgroups per image and channel block, 16-position tiles of each
   int pw, plane;     // staged map: columns, positions per channel
 };
 
@@ -580,9 +580,9 @@ size_t pass_shape(const EccParams& q, PassShape* ps) {
   const long long plane = (long long)((q.Ho - 1) * q.stride + q.dk) * ps->pw;
   if (2 * plane * q.Csp * 4 > 48 * 1024) return 0;
   ps->plane = (int)plane;
-  // about 6 waves per SIMD's worth of 16-channel work items at the least
-  // pieces of 4 tiles: fewer, longer ones leave SIMDs idle, more add chunks
-  // to the sums
+  // at least 1536 waves of 16 channels (1.5 per SIMD) as long as a piece keeps
+  // 4 tiles: with fewer, SIMDs stay idle; with more, the sums over the pieces
+  // grow
   const int tiles = (q.O + 15) / 16, waves = ceil_div(q.Ct, 16) * q.N;
   int parts = std::max(1, std::min(ceil_div(1536, waves), tiles / 4));
   ps->tiles = ceil_div(tiles, parts);

@@ -1,0 +1,47 @@
+"""The kernels of the conv error correction at the edges of their dispatch: the
+matrix form of the Gram blocks (d_k^2 C's <= 64 in tiles of 16, maps up to 32
+KB), the fused pass (<= 128, maps up to 48 KB for both sub-spaces) and the
+kernels behind them, channel blocks of 64, more images than Gram chunks, and
+the solve's sizes in K.  Against the float64 oracle with the bounds of
+test_gpu_ec_conv.py (both sides are float64; codes must be equal).
+"""
+import numpy as np
+import pytest
+import torch
+
+from paper_1512_06473_amd import api as api_mod
+from test_gpu_ec_conv import problem, run_gpu
+
+pytestmark = pytest.mark.gpu
+
+# N, C_s, H, W, C_t, d_k, stride, pad, C's, K
+CASES = [
+    (1, 2, 3, 3, 5, 1, 1, 0, 1, 2),       # one (p, j)
+    (2, 16, 5, 6, 65, 1, 1, 0, 8, 7),     # a channel past a block of 64
+    (9, 4, 5, 5, 17, 3, 1, 1, 2, 64),     # 2 tiles; more images than chunks; K a whole wave
+    (3, 8, 7, 5, 33, 4, 2, 1, 4, 65),     # 64: the Gram tiles' limit; K one past a wave
+    (2, 16, 6, 6, 40, 3, 1, 1, 8, 128),   # 72: past it, fused pass of 5 tiles
+    (2, 8, 8, 8, 64, 5, 1, 2, 4, 130),    # 100: 7 tiles
+    (2, 16, 6, 7, 24, 4, 1, 1, 8, 50),    # 128: the pass's limit
+    (2, 10, 6, 7, 24, 5, 1, 2, 5, 200),   # 125, ragged; K = 200
+    (2, 12, 7, 7, 24, 5, 1, 2, 6, 40),    # 150: past it
+    (1, 8, 36, 36, 20, 3, 1, 1, 4, 32),   # map of 23 KB: fused
+    (1, 8, 40, 40, 20, 3, 1, 1, 4, 32),   # 28 KB: past the pass's
+    (1, 8, 48, 44, 20, 3, 1, 1, 4, 32),   # 37 KB: past the Gram's as well
+]
+
+
+@pytest.mark.parametrize("case", CASES, ids=[str(c) for c in CASES])
+def test_ec_conv_edges(case):
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    from oracle import ec_conv
+    N, Cs, H, W, Ct, dk, st, pd, Csp, K = case
+    print("ec_conv edge", case, flush=True)
+    rng = np.random.Generator(np.random.PCG64(9400 + CASES.index(case)))
+    S, T, D0, c0 = problem(rng, N, Cs, H, W, Ct, dk, st, pd, Csp, K)
+    D, c, obj = run_gpu(api_mod, torch.device("cuda:0"), S, T, D0, c0, st, pd, 1, 1)
+    Dr, cr, hr = ec_conv.ec_conv(S, T, D0, c0, st, pd, 1, 1)
+    assert np.array_equal(c, cr), int((c != cr).sum())
+    assert np.allclose(D, Dr, rtol=1e-6, atol=1e-7 * float(np.abs(Dr).max())), float(np.abs(D - Dr).max())
+    assert np.allclose(obj, hr, rtol=1e-9, atol=1e-9 * hr[0])
