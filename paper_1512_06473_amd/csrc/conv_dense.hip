@@ -958,10 +958,15 @@ bool conv_dense_supported(const ConvShape& s) {
 //     16, 263 against 182 us for 64).
 bool conv_dense_better(const ConvShape& s, int table_chain) {
   if (!conv_dense_supported(s)) return false;
-  const int products = s.Cs * s.dk * s.dk, entries = s.M * s.dk * s.dk;
-  if (table_chain == 0) return entries >= 48;
+  if (table_chain == 0) return s.M * s.dk * s.dk >= 48;
+  return table_chain >= 48 && conv_dense_large(s);
+}
+
+// The rule's sizes alone (no plan).
+bool conv_dense_large(const ConvShape& s) {
+  const int products = s.Cs * s.dk * s.dk;
   const double macs = (double)s.N * s.Ho * s.Wo * s.Ct * products;
-  return table_chain >= 48 && products >= (s.Ct <= 64 ? 512 : 256) && macs >= (s.dk > 1 && s.Cs < 8 ? 1e9 : s.Csp <= 4 ? 1.5e8 : 3e8);
+  return products >= (s.Ct <= 64 ? 512 : 256) && macs >= (s.dk > 1 && s.Cs < 8 ? 1e9 : s.Csp <= 4 ? 1.5e8 : 3e8);
 }
 
 size_t conv_dense_workspace(const ConvShape& s) {

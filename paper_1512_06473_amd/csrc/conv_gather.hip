@@ -234,14 +234,18 @@ ConvKernel pick_conv_kernel(const ConvShape& s) {
   if (v && strcmp(v, "dense") == 0 && conv_dense_supported(s)) return ConvKernel::kDense;
   if (v && (strcmp(v, "flat") == 0 || strcmp(v, "half") == 0)) return pick_table_kernel(s);
   if (getenv("QCNN_TABLE_BUILD")) return pick_table_kernel(s);  // a comparison of the table builds
-  const int flat = conv_flat_chain(s);
-  if (conv_dense_better(s, flat || !conv_half_supported(s) ? flat : s.M * s.dk * s.dk)) {
+  const ConvKernel table = pick_table_kernel(s);
+  // (a small layer's chain is not asked for: that plans the layer once more,
+  // 1.4 us of a 23 us call)
+  if (table != ConvKernel::kGeneric && !conv_dense_large(s)) return table;
+  const int chain = table == ConvKernel::kFlat ? conv_flat_chain(s) : table == ConvKernel::kHalf ? s.M * s.dk * s.dk : 0;
+  if (conv_dense_better(s, chain)) {
     // A layer that fits the allocation-free entry point's scratch with its
     // table kernel keeps fitting it.
     const size_t room = noalloc_scratch_bytes() - 256, need = conv_dense_workspace(s);
-    if (need <= room || table_workspace(s, pick_table_kernel(s)) > room) return ConvKernel::kDense;
+    if (need <= room || table_workspace(s, table) > room) return ConvKernel::kDense;
   }
-  return pick_table_kernel(s);
+  return table;
 }
 
 }  // namespace

@@ -161,6 +161,7 @@ bool conv_dense_supported(const ConvShape& s);
 // Supported, and better than the layer's table kernel, which adds up
 // `table_chain` table entries in a row (0: only the generic kernel tiles it).
 bool conv_dense_better(const ConvShape& s, int table_chain);
+bool conv_dense_large(const ConvShape& s);  // the sizes that this asks for, whatever the chain
 size_t conv_dense_workspace(const ConvShape& s);
 size_t conv_dense_weight_bytes(const ConvShape& s);
 hipError_t launch_conv_dense_weights(const ConvShape& s, const float* D, CodeStream codes, char* w,
