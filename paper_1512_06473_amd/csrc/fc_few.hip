@@ -242,20 +242,22 @@ FewParams few_plan(int N, int Cs, int M, int K, int Csp, int Ct) {
 
 }  // namespace
 
-// A group costs a workgroup 3 us at K = 32, C's = 4 and four images, of which
-// the table is a third, next to fc_tiled's 25-50 us however few its images
-// are.  The line lies at 12 such groups one after another on a CU.  us, plan
-// call, fc_tiled -> this kernel: fc6 (9216 to 4096) with 8 images, 9 groups,
-// 60 -> 36; 12 images, 15 groups, 60 -> 58; 16 images, 18 groups, 60 -> 66.
-// 4096 to 1000: 48 images, 7 groups, 39 -> 31; 64, 8 groups, 40 -> 34; 128,
-// 16 groups, 41 -> 60.  2048 to 512, C's = 8, K = 64, 128 images: 2 groups,
+// A group of 32 subspaces costs a workgroup 3 us at K = 32, C's = 4 and four
+// images (5 us with its codes and codebooks not in the caches, as between the
+// layers of a network), of which the table is a third, on top of 10 us;
+// fc_tiled takes 28 us and 1 us more per 75 subspaces however few its images
+// are.  The line lies where the dearer of the two figures meets it.  us, plan
+// call, fc_tiled -> this kernel: fc6 (9216 to 4096) with 8 images, 9 groups in a
+// row, 60 -> 36; 12 images, 15 groups, 60 -> 58.  4096 to 1000: 32 images, 4
+// groups, 39 -> 21; 64, 8 groups, 40 -> 33 when repeated but 40 -> 50 in a
+// network, so fc_tiled's.  2048 to 512, C's = 8, K = 64, 128 images: 2 groups,
 // 29 -> 21.  Where fc_tiled does not go (K > 64 or C's > 8) this is the only
 // kernel.
 bool fc_few_better(int N, int Cs, int M, int K, int Csp, int Ct) {
   if (!fc_tiled_supported(N, Cs, M, K, Csp, Ct)) return true;
   const FewParams p = few_plan(N, Cs, M, K, Csp, Ct);
   const double rounds = (double)((p.blocks * p.splits + 255) / 256);
-  return rounds * p.groups * (2.0 + (double)(Csp << p.lb) / 128.0) / 3.0 <= 12.0;
+  return rounds * p.groups * (2.0 + (double)(Csp << p.lb) / 128.0) / 3.0 <= 3.5 + M / 400.0;
 }
 
 hipError_t launch_fc_few(int N, int Cs, int M, int K, int Csp, int Ct, const float* x, const float* D,
