@@ -96,7 +96,9 @@ qcnn_status qcnn_lut_build(const float* x, int N, int C_s, int H, int W,
  *                     (+ bias[t]) (ReLU)
  * x: [N][C_s][H][W]; codebooks: [M][K][C'_s]; codes: uint8 [C_t][d_k][d_k][M];
  * bias: [C_t] or NULL; y (output): [N][C_t][H_o][W_o].
- * The table is built tile by tile in LDS and never written to memory. */
+ * The table is built tile by tile in LDS and never written to memory; a large
+ * layer's sums are formed as products with the weights that the codebooks and
+ * codes stand for (the same responses, without a table). */
 qcnn_status qcnn_conv_forward(const float* x, int N, int C_s, int H, int W,
                               const float* codebooks, int M, int K, int Csp,
                               const uint8_t* codes, int C_t, int d_k, int stride, int pad,
@@ -153,8 +155,9 @@ qcnn_status qcnn_conv_forward_noalloc(const float* x, int N, int C_s, int H, int
  * indices are stored, and each forward only builds the table and gathers,
  * Eq. (5) / (7)).  A plan takes them once for one input shape: it verifies
  * every code (< K), keeps its own device copies of the codebooks and the
- * bias, and stores the codes in the order the layer's kernel reads them, so
- * that a forward runs only the table build and gather (and, for a layer
+ * bias, and stores the codes (or, for a large conv layer, the weights that they
+ * stand for, 4 bytes each) in the order the layer's kernel reads them, so that
+ * a forward runs only the table build and gather, or the products (and, for a layer
  * split over workgroups, the sum of the splits' partial sums);
  * qcnn_conv_forward and qcnn_fc_forward re-lay the codes on every call.
  * Results are those of qcnn_conv_forward (pool_k = pool_s = 0),
@@ -337,8 +340,9 @@ qcnn_status qcnn_ec_fc(const float* S, int N, int C_s, const float* T, int C_t,
  * C_t d_k^2 <= 16384, N C_t H_o W_o <= 2^31; codes >= K are read, and
  * written back, as K - 1 (checked with QCNN_CHECK_CODES=1).  Cost per call:
  * M d_k^4 C'_s^2 N H_o W_o multiply-adds once for the input Gram blocks,
- * then per subspace step two passes over the residual and a one-workgroup
- * solve that is sequential over the K sub-codewords. */
+ * then per subspace step one pass over the residual (two where d_k^2 C'_s > 128
+ * or the input maps are large) and a one-workgroup substitution over the K
+ * sub-codewords. */
 qcnn_status qcnn_ec_conv(const float* S, int N, int C_s, int H, int W,
                          const float* T, int C_t, int d_k, int stride, int pad,
                          float* codebooks, int M, int K, int Csp, uint8_t* codes,
@@ -361,7 +365,7 @@ const char* qcnn_status_string(qcnn_status s);
 int qcnn_version(void);
 
 /* Kernel timing, for benchmarks and profiling.  While enabled, every
- * compute call above times its main kernel (the gather kernel of
+ * compute call above times its main kernel (the gather or product kernel of
  * qcnn_conv_forward and qcnn_fc_forward, the table kernel of
  * qcnn_lut_build) with a pair of HIP events that the kernel's dispatch
  * stamps at the start and the end of its execution (hipExtLaunchKernelGGL),
