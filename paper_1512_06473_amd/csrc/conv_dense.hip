@@ -18,12 +18,11 @@
 // MFMA adds the exact fp16 products in fp32.  h h' and the cross terms have
 // accumulators of their own, so that scaling l by 2^11 keeps it out of the
 // fp16 subnormals: a factor keeps its 22 bits down to 2^-28 of the largest
-// one, and its absolute error below that is 2^-51 of the largest one.  A
-// workgroup whose inputs (or a layer whose codewords) span more than that --
-// the largest of 8 neighbouring channels, or of a codeword, below 2^-26 to
-// 2^-29 of the largest value -- or hold an infinity, a NaN or values near the
-// ends of the fp32 range repeats its tile with fp32 MFMA on the unsplit
-// values.
+// one (weights; inputs, which are scaled lower, to 2^-26).  A workgroup whose
+// inputs, or a layer whose codewords, hold a smaller non-zero value -- any one:
+// the weights on the large values beside it may be zero, and the result is then
+// its products alone -- or an infinity, a NaN or values near the ends of the
+// fp32 range repeats its tile with fp32 MFMA on the unsplit values.
 //
 // Work.  A tile is 128 output channels (64 where the layer has no more) x 96
 // output positions; its reduction runs over units (chunk of 16 SUB input
@@ -295,24 +294,24 @@ __device__ __forceinline__ bool products(const TileState<IT, XP>& ts, int tgrp, 
       *reinterpret_cast<h8*>(dst + 32) = lo;
     }
   };
-  // Largest magnitude of the loaded values, and the smallest non-zero one of
-  // the per-thread maxima over 8 channels, exchanged over the workgroup.
+  // Largest and smallest non-zero magnitude of the loaded values, exchanged
+  // over the workgroup.
   // Two exchange buffers: a wave may publish again before the slowest one
   // has read the last exchange.
   int xb = 0;
   auto publish = [&]() {
     xb ^= 2 * kWaves;
-    uint32_t mx = 0, inv = 0;  // inv: ~(smallest non-zero maximum - 1)
+    uint32_t mx = 0, below = ~0u;  // below: smallest non-zero magnitude - 1
 #pragma unroll
-    for (int k = 0; k < IT; ++k) {
-      uint32_t v = 0;
+    for (int k = 0; k < IT; ++k)
 #pragma unroll
-      for (int j = 0; j < 8; ++j) v = max(v, __float_as_uint(xv[k][j]) & 0x7fffffffu);
-      mx = max(mx, v);
-      inv = max(inv, ~(v - 1u));  // v = 0 gives 0
-    }
+      for (int j = 0; j < 8; ++j) {
+        const uint32_t v = __float_as_uint(xv[k][j]) & 0x7fffffffu;
+        mx = max(mx, v);
+        below = min(below, v - 1u);  // v = 0 gives ~0
+      }
     mx = wave_max(mx);
-    inv = wave_max(inv);
+    const uint32_t inv = wave_max(~below);
     if (lane == 0) {
       exch[xb + wave] = mx;
       exch[xb + kWaves + wave] = inv;
@@ -681,7 +680,7 @@ __global__ __launch_bounds__(2 * kNT) void dense_reduce_kernel(const float* __re
 }
 
 // Scale and form of a layer's weights: one workgroup over the codebooks.
-__global__ __launch_bounds__(1024) void dense_head_kernel(const float* __restrict__ D, int codewords, int Csp,
+__global__ __launch_bounds__(1024) void dense_head_kernel(const float* __restrict__ D, int n,
                                                           DenseHead* __restrict__ head) {
   __shared__ uint32_t sm[2][16];
   uint32_t mx = 0, inv = 0;
@@ -690,23 +689,15 @@ __global__ __launch_bounds__(1024) void dense_head_kernel(const float* __restric
     mx = max(mx, v);
     inv = max(inv, ~(v - 1u));
   };
-  if (Csp % 4 == 0 && (reinterpret_cast<uintptr_t>(D) & 15) == 0) {  // a codeword is whole 16-byte loads
-    const int q = Csp >> 2;
+  if (n % 4 == 0 && (reinterpret_cast<uintptr_t>(D) & 15) == 0) {
 #pragma unroll 4
-    for (int i = threadIdx.x; i < codewords; i += 1024) {
-      uint32_t v = 0;
-      for (int j = 0; j < q; ++j) {
-        const f4v d = reinterpret_cast<const f4v*>(D)[(size_t)i * q + j];
-        v = max(max(v, max(mag(d[0]), mag(d[1]))), max(mag(d[2]), mag(d[3])));
-      }
-      take(v);
+    for (int i = threadIdx.x; i < n / 4; i += 1024) {
+      const f4v d = reinterpret_cast<const f4v*>(D)[i];
+#pragma unroll
+      for (int j = 0; j < 4; ++j) take(mag(d[j]));
     }
   } else {
-    for (int i = threadIdx.x; i < codewords; i += 1024) {
-      uint32_t v = 0;
-      for (int j = 0; j < Csp; ++j) v = max(v, mag(D[(size_t)i * Csp + j]));
-      take(v);
-    }
+    for (int i = threadIdx.x; i < n; i += 1024) take(mag(D[i]));
   }
   mx = wave_max(mx);
   inv = wave_max(inv);
@@ -901,7 +892,7 @@ hipError_t launch_main(const DensePlan& pl, const Ptrs& g, hipStream_t stream, L
 
 hipError_t launch_weights(const DensePlan& pl, const float* D, CodeStream codes, char* w, hipStream_t stream) {
   const DenseParams& p = pl.p;
-  hipLaunchKernelGGL(dense_head_kernel, dim3(1), dim3(1024), 0, stream, D, p.M * p.K, p.Csp,
+  hipLaunchKernelGGL(dense_head_kernel, dim3(1), dim3(1024), 0, stream, D, p.M * p.K * p.Csp,
                      reinterpret_cast<DenseHead*>(w));
   const long long threads = (long long)p.tblocks * pl.TW * p.upt * kWave;
   hipLaunchKernelGGL(dense_weights_kernel, dim3((unsigned)std::min<long long>(4096, (threads + 255) / 256)), dim3(256),

@@ -119,6 +119,30 @@ def test_dense_wide_range(dev, oracle, kind):
     assert np.all(np.abs(y.astype(np.float64) - ref) <= RTOL * A + 1e-30)
 
 
+@pytest.mark.parametrize("ratio", [1e6, 1e8, 1e10, 1e12, 1e15, 1e20])
+@pytest.mark.parametrize("where", ["x", "D", "packed rows"])
+def test_dense_small_beside_large(dev, oracle, where, ratio):
+    """A small value beside a large one, of which the result is made alone
+    because the other factor is zero on the large one: channel by channel,
+    within a codeword, and column by column where kernel rows are packed (the 8
+    values of a staged group are neighbouring channels, or columns)."""
+    rng, x, D, codes = _layer(21)
+    if where == "packed rows":
+        x, D, codes = wl.random_conv(rng, 2, 4, 21, 22, 70, 3, 1, 1, 4, 128)
+        x[:, :, ::3, ::4] *= np.float32(ratio)
+        D[:, :, :2] = 0.0
+        x[:, 2:] /= np.float32(ratio)
+    elif where == "x":
+        x[:, np.arange(64) % 8 < 4] *= np.float32(ratio)
+        D[::2] = 0.0            # the subspaces on the large channels
+    else:
+        D[:, :, :2] *= np.float32(ratio)
+        x[:, np.arange(64) % 4 < 2] = 0.0
+    y = conv(dev, x, D, codes, 1, 1)
+    ref, A = oracle.conv_lut(x, D, codes, 1, 1, with_bound=True)
+    assert np.all(np.abs(y.astype(np.float64) - ref) <= RTOL * A + 1e-30)
+
+
 @pytest.mark.parametrize("where", ["x", "D", "packed rows"])
 def test_dense_non_finite(dev, where, monkeypatch):
     """Infinities and NaN reach exactly the outputs they reach through the
