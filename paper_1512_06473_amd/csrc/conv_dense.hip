@@ -17,12 +17,16 @@
 // h h' + (h l' + l h') 2^-11, the left-out l l' being below 2^-24 of it; the
 // MFMA adds the exact fp16 products in fp32.  h h' and the cross terms have
 // accumulators of their own, so that scaling l by 2^11 keeps it out of the
-// fp16 subnormals: a factor keeps its 22 bits down to 2^-28 of the largest
-// one (weights; inputs, which are scaled lower, to 2^-26).  A workgroup whose
-// inputs, or a layer whose codewords, hold a smaller non-zero value -- any one:
-// the weights on the large values beside it may be zero, and the result is then
-// its products alone -- or an infinity, a NaN or values near the ends of the
-// fp32 range repeats its tile with fp32 MFMA on the unsplit values.
+// fp16 subnormals: a factor keeps its 22 bits down to 2^-28 of the largest one.
+// Smaller inputs -- any one: the weights on the large values beside it may be
+// zero, and the result is then its products alone -- are left to passes of their
+// own over the tile (its chunks that hold any), one per 28 binades, whose sums
+// are added to the first's.  An input more than two such bands down, an
+// infinity, a NaN or values near the ends of the fp32 range send the tile, and
+// codewords that span more than 2^28 the layer, to fp32 MFMA on the unsplit
+// values.  conv3, 32 images, and VGG conv3 per call, us: ordinary inputs 53 and
+// 214; one value of 1e-9 54 and 247; one in 1009, in every tile, 94 and 415; in
+// fp32 135 and 710 (with weights decoded lane by lane 710 and 4350).
 //
 // Work.  A tile is 128 output channels (64 where the layer has no more) x 96
 // output positions; its reduction runs over units (chunk of 16 SUB input
@@ -103,6 +107,8 @@ constexpr int kCF = kNT / 32;
 constexpr int kSumStride = kNT + 8;  // floats per channel of a tile's sums in LDS
 constexpr int kCUs = 256;
 constexpr int kFold = 9;
+constexpr int kBand = 28;     // binades of one range band: scaled magnitudes 2^-14 .. 2^14 (2^15 in band 0)
+constexpr int kMaxBands = 2;  // bands after the first that a tile takes in split form
 constexpr uint32_t kOOB = 0x80000000u;  // buffer offset past every input: reads 0
 
 typedef _Float16 h8 __attribute__((ext_vector_type(8)));
@@ -135,9 +141,14 @@ __device__ __forceinline__ uint32_t wave_max(uint32_t v) {
   return (uint32_t)__builtin_amdgcn_readlane((int)v, 63);
 }
 
-// Exponent that brings a largest magnitude (fp32 bits of |v|) to 2^12 .. 2^13,
-// leaving two bits for later chunks to grow; 0 for an all-zero input.
-__device__ __forceinline__ int scale_for(uint32_t maxbits) { return maxbits ? 12 - ((int)(maxbits >> 23) - 127) : 0; }
+// Exponent that brings a largest magnitude (fp32 bits of |v|) to 2^14 .. 2^15;
+// 0 for an all-zero input.
+__device__ __forceinline__ int scale_for(uint32_t maxbits) { return maxbits ? 14 - ((int)(maxbits >> 23) - 127) : 0; }
+
+// fp32 bits of 2^q, q <= 127 (0 below the smallest subnormal).
+__device__ __forceinline__ uint32_t pow2_bits(int q) {
+  return q >= -126 ? (uint32_t)(q + 127) << 23 : q >= -149 ? 1u << (q + 149) : 0u;
+}
 
 // Magnitudes whose scaling stays inside the normal fp32 range.
 __device__ __forceinline__ bool scalable(uint32_t maxbits) {
@@ -146,9 +157,7 @@ __device__ __forceinline__ bool scalable(uint32_t maxbits) {
 
 struct Ptrs {
   const float* x;
-  const float* D;
-  const char* w;      // head, then weights [channel group of 32][unit][step 2][hi, lo][lane][8] fp16
-  CodeStream codes;   // for the fp32 form
+  const char* w;      // head, then weights [channel group of 32][unit][hi, lo][lane][8] fp16, or fp32 [..][2][lane][4]
   const float* bias;
   float* y;
   float* partial;     // [2 per run][MT][kNT]
@@ -168,7 +177,7 @@ __device__ __forceinline__ const Args& args_again() {
   return *(const Args*)a;
 }
 
-// One wave-wide set of 8 fp32 accumulator groups.
+// A wave's fp32 accumulators.
 struct Acc {
   f16v a[kCF], c[kCF];  // h h' and cross terms since the last fold of a
   f16v sum[kCF];        // a folded
@@ -186,22 +195,6 @@ __device__ __forceinline__ void channel_of(const DenseParams& p, int v, int tap,
   }
 }
 
-// The weights of 8 channels for the fp32 form, decoded from the codes.
-__device__ __forceinline__ void decode8(const Ptrs& g, const DenseParams& p, int t, int tap, int ch0, float (&v)[8]) {
-#pragma unroll
-  for (int j = 0; j < 8; ++j) {
-    v[j] = 0.f;
-    if (t < p.Ct && ch0 + j < p.VC) {
-      int ch, ktap;
-      channel_of(p, ch0 + j, tap, ch, ktap);
-      const int m = ch / p.Csp;
-      uint32_t code = code_at(g.codes, ((size_t)t * p.dk * p.dk + ktap) * p.M + m);
-      code = min(code, (uint32_t)(p.K - 1));
-      v[j] = g.D[((size_t)m * p.K + code) * p.Csp + (ch - m * p.Csp)];
-    }
-  }
-}
-
 // Everything a workgroup keeps for one tile.
 template <int IT, bool XP>
 struct TileState {
@@ -210,11 +203,23 @@ struct TileState {
   int rowb[kCF];        // LDS byte offset of the lane's output position in each 32-column group, tap (0, 0)
 };
 
-// The products of units [u0, u1) of one tile in split form.  Returns false
-// when that form does not hold the inputs' range.
+// What a tile's later passes take: the last band that holds a value, the chunks
+// that hold any past band 0, and the scale before the first of them.
+struct Bands {
+  int last, from, to, e;
+};
+constexpr int kUnset = 1 << 20;  // the scale before the first non-zero chunk
+
+// The products of units [u0, u1) of one tile in split form, of the inputs of
+// one range band: those of scaled magnitude 2^-14 and more (band 0), or of the
+// b-th 2^kBand below that, scaled 2^(kBand b) more.  The scale follows the
+// largest input so far, chunk by chunk, and is the same in every band's pass.
+// Returns false when the form does not hold the inputs
+// (band 0 only: an infinity, a NaN, the ends of the fp32 range, more bands
+// than kMaxBands).
 template <int TW, int IT, bool XP>
 __device__ __forceinline__ bool products(const TileState<IT, XP>& ts, int tgrp, int u0, int u1, char* lds,
-                                         uint32_t* exch, Acc& acc, int& x_exp) {
+                                         uint32_t* exch, int band, Bands& bands, Acc& acc, int& x_exp) {
   const Args& args = args_again();
   const Ptrs& g = args.g;
   const DenseParams& p = args.p;
@@ -235,7 +240,7 @@ __device__ __forceinline__ bool products(const TileState<IT, XP>& ts, int tgrp, 
 #pragma unroll
     for (int r = 0; r < 16; ++r) acc.a[j][r] = acc.c[j][r] = acc.sum[j][r] = 0.f;
 
-  // ---- input staging: wave item i = wave + 8 k is (64 positions, 8 channels):
+  // ---- input staging: wave item i = wave + kWaves k is (64 positions, 8 channels):
   // position group i % wgroups, channel group i / wgroups of the chunk.
   // Channels past C_s hold 0: whole groups by an offset past the buffer, the
   // rest of a last group after its load.
@@ -277,7 +282,18 @@ __device__ __forceinline__ bool products(const TileState<IT, XP>& ts, int tgrp, 
       }
     }
   };
-  auto store_chunk = [&](char* buf, int e) {
+  auto store_chunk = [&](char* buf, int e, int low) {
+    if (band | low) {  // the chunk's values of this band
+      const int q = -14 - e - kBand * band;
+      const uint32_t from = pow2_bits(q), to = band ? pow2_bits(q + kBand) : ~0u;
+#pragma unroll
+      for (int k = 0; k < IT; ++k)
+#pragma unroll
+        for (int j = 0; j < 8; ++j) {
+          const uint32_t v = __float_as_uint(xv[k][j]) & 0x7fffffffu;
+          xv[k][j] = v >= from && v < to ? ldexpf(xv[k][j], kBand * band) : 0.f;
+        }
+    }
     const float s = __uint_as_float((uint32_t)(e + 127) << 23);
 #pragma unroll
     for (int k = 0; k < IT; ++k) {
@@ -318,10 +334,9 @@ __device__ __forceinline__ bool products(const TileState<IT, XP>& ts, int tgrp, 
     }
   };
   // After the barrier that follows publish(): the scale for that chunk given
-  // the current one (kUnset before the first non-zero chunk); false when the
-  // split form does not hold it.
-  constexpr int kUnset = 1 << 20;
-  auto agree = [&](int& e) -> bool {
+  // the current one (kUnset before the first non-zero chunk).  Returns the band
+  // of the chunk's smallest value, -1 when the split form does not hold it.
+  auto agree = [&](int& e) -> int {
     uint32_t mx = 0, inv = 0;
 #pragma unroll
     for (int i = 0; i < kWaves; ++i) {
@@ -330,53 +345,84 @@ __device__ __forceinline__ bool products(const TileState<IT, XP>& ts, int tgrp, 
     }
     mx = __builtin_amdgcn_readfirstlane(mx);
     inv = __builtin_amdgcn_readfirstlane(inv);
-    if (mx == 0) return true;
-    if (!scalable(mx)) return false;
+    if (mx == 0) return 0;
+    if (!scalable(mx)) return -1;
     if ((int)(mx >> 23) - 127 + e > 14) e = scale_for(mx);
-    return (int)((~inv + 1u) >> 23) - 127 + e >= -14;
+    int low = 0;
+    while (~inv + 1u < pow2_bits(-14 - e - kBand * low)) ++low;  // ends: the last bound is 0
+    return low;
   };
 
-  const int c_first = p.d_upc.div(u0), c_last = p.d_upc.div(u1 - 1);
-  int e = kUnset;
-  bool ok = true;
+  const int c_first = band ? bands.from : p.d_upc.div(u0), c_last = band ? bands.to : p.d_upc.div(u1 - 1);
+  int e = band ? bands.e : kUnset;
   load_chunk(c_first);
 
   // ---- weight operands: unit u of the tile at 2048 u, three of this wave's
   // units in flight.  The loads run past the tile's last unit into the next
   // group's weights or the padding after them.
-  int u = u0 + kg;  // this wave's next unit
-  const char* wp = g.w + kHeadBytes + ((size_t)tgrp * p.upt + u) * 2048;
+  int u;  // this wave's next unit
+  const char* wp;
   h8 wh[3], wl[3];
   auto load_w = [&](int slot) {
     wh[slot] = *reinterpret_cast<const h8*>(wp + lane * 16);
     wl[slot] = *reinterpret_cast<const h8*>(wp + lane * 16 + 1024);
     wp += KG * 2048;
   };
-  load_w(0);
-  load_w(1);
-  load_w(2);
-
-  publish();
-  __syncthreads();
-  ok = agree(e);
-  store_chunk(lds, e == kUnset ? 0 : e);
-  if (c_first < c_last) load_chunk(c_first + 1);
-
-  // The LDS rows of the wave's unit: (ky PW + kx) pitch + sub 64, kept by
-  // increments.
+  // The wave's first unit of a chunk, its weights, and its LDS rows
+  // ((ky PW + kx) pitch + sub 64), which step() keeps by increments.
   int sub, kx, off;
-  {
-    const int v = u - c_first * upc;
+  auto seek = [&](int c) {
+    u = max(u0, c * upc);
+    u += (kg - (u - u0)) & (KG - 1);
+    wp = g.w + kHeadBytes + ((size_t)tgrp * p.upt + u) * 2048;
+    load_w(0);
+    load_w(1);
+    load_w(2);
+    const int v = u - c * upc;
     const int tap = p.d_SUB.div(v);
     sub = v - tap * p.SUB;
     const int ky = p.d_kw.div(tap);
     kx = tap - ky * p.kw;
     off = (ky * p.PW + kx) * p.pitch + sub * 64;
-  }
+  };
+  bool placed = band == 0;  // u, the weights and the rows are the next chunk's
+  if (placed) seek(c_first);
+
+  publish();
+  __syncthreads();
+  auto note = [&](int c, int e_before, int low) {
+    if (band || low <= 0) return;
+    if (bands.last == 0) {
+      bands.from = c;
+      bands.e = e_before;
+    }
+    bands.to = c;
+    bands.last = max(bands.last, low);
+  };
+  const int e0 = e;
+  int low = agree(e);
+  bool ok = (unsigned)low <= kMaxBands;
+  note(c_first, e0, low);
+  store_chunk(lds, e == kUnset ? 0 : e, low);
+  if (c_first < c_last) load_chunk(c_first + 1);
+
   const int lane_k = (lane >> 5) * 16;
   const int tap_step = p.pitch - p.SUB * 64, row_step = (p.PW - p.kw) * p.pitch;
   int parity = 0;  // LDS buffer of the current chunk
   int folded = 0;  // steps since the last fold
+  // The MFMA adds 8 products at a time: the running sum is rounded K / 8
+  // times.  Folding it into a second one every kFold units or more keeps the
+  // chains short (96 -> 256 channels, 5x5, 64 images, relative error against
+  // float64: 2.8e-7 -> 1.5e-7; the table kernel's is 2.1e-7).
+  auto fold = [&]() {
+#pragma unroll
+    for (int j = 0; j < kCF; ++j)
+#pragma unroll
+      for (int r = 0; r < 16; ++r) {
+        acc.sum[j][r] += acc.a[j][r];
+        acc.a[j][r] = 0.f;
+      }
+  };
 
   auto step = [&](int slot) {
     const char* base = lds + parity * buf_bytes + off + lane_k;
@@ -414,48 +460,49 @@ __device__ __forceinline__ bool products(const TileState<IT, XP>& ts, int tgrp, 
     __builtin_amdgcn_sched_barrier(0);
   };
 
-  for (int c = c_first; c <= c_last; ++c) {
+  int c_end = ok ? c_last : c_first;  // (a return from inside the loop spills the sums)
+  for (int c = c_first; c <= c_end; ++c) {
     // Loaded: chunk c + 1, one chunk ahead of its products.  Its scale is
     // agreed on across the barrier that also hands over chunk c's LDS rows.
-    const bool more = c < c_last;
+    const bool more = c < c_end;
     if (more) publish();
     __syncthreads();
-    int e_next = e;
+    int e_next = e, low_next = 0;
     if (more) {
-      ok &= agree(e_next);
-      store_chunk(lds + (parity ^ 1) * buf_bytes, e_next == kUnset ? 0 : e_next);
+      low_next = agree(e_next);
+      ok &= (unsigned)low_next <= kMaxBands;
+      if (!ok) c_end = c;
+      note(c + 1, e, low_next);
+      store_chunk(lds + (parity ^ 1) * buf_bytes, e_next == kUnset ? 0 : e_next, low_next);
       if (c + 1 < c_last) load_chunk(c + 2);
     }
-    const int u_end = min(u1, (c + 1) * upc);
-    while (u + 2 * KG < u_end) {
-      step(0);
-      step(1);
-      step(2);
-    }
-    while (u < u_end) {  // at most two
-      step(0);
-      const h8 th = wh[0], tl = wl[0];
-      wh[0] = wh[1];
-      wl[0] = wl[1];
-      wh[1] = wh[2];
-      wl[1] = wl[2];
-      wh[2] = th;
-      wl[2] = tl;
-    }
-    // The MFMA adds 8 products at a time: the running sum is rounded K / 8
-    // times.  Folding it into a second one every kFold units or more keeps the
-    // chains short (96 -> 256 channels, 5x5, 64 images, relative error against
-    // float64: 2.8e-7 -> 1.5e-7; the table kernel's is 2.1e-7).
-    folded += u_end - c * upc;
-    if (folded >= kFold * KG || c == c_last) {
-      folded = 0;
-#pragma unroll
-      for (int j = 0; j < kCF; ++j)
-#pragma unroll
-        for (int r = 0; r < 16; ++r) {
-          acc.sum[j][r] += acc.a[j][r];
-          acc.a[j][r] = 0.f;
-        }
+    if (low >= band) {
+      if (!placed) seek(c);
+      const int u_end = min(u1, (c + 1) * upc);
+      while (u + 2 * KG < u_end) {
+        step(0);
+        step(1);
+        step(2);
+      }
+      while (u < u_end) {  // at most two
+        step(0);
+        const h8 th = wh[0], tl = wl[0];
+        wh[0] = wh[1];
+        wl[0] = wl[1];
+        wh[1] = wh[2];
+        wl[1] = wl[2];
+        wh[2] = th;
+        wl[2] = tl;
+      }
+      off -= p.dk * p.PW * p.pitch;  // from past the last tap to the next chunk's first
+      folded += u_end - c * upc;
+      if (folded >= kFold * KG) {
+        folded = 0;
+        fold();
+      }
+      placed = true;
+    } else {
+      placed = false;
     }
     if (e_next < e && e != kUnset) {  // larger inputs ahead: the sums take their scale
       const float f = __uint_as_float((uint32_t)max(1, e_next - e + 127) << 23);
@@ -469,45 +516,13 @@ __device__ __forceinline__ bool products(const TileState<IT, XP>& ts, int tgrp, 
         }
     }
     e = e_next;
-    off -= p.dk * p.PW * p.pitch;  // from past the last tap to the next chunk's first
+    low = low_next;
     parity ^= 1;
   }
+  fold();
   __syncthreads();  // the sums overwrite the staged rows
-  x_exp = e == kUnset ? 0 : e;
+  x_exp = (e == kUnset ? 0 : e) + kBand * band;
   return ok;
-}
-
-// The sums of units [u0, u1) of 32 channels x 32 positions in fp32, operands
-// straight from memory: the form for inputs or codewords whose range the
-// split one does not hold.  `plane0`, iy, ix: the lane's output position's
-// image plane and input coordinates at tap (0, 0); iy < -2^20: no position.
-__device__ __forceinline__ f16v products_f32(int tgrp, int u0, int u1, int n, int iy, int ix) {
-  const Args& args = args_again();
-  const Ptrs& g = args.g;
-  const DenseParams& p = args.p;
-  const int lane = threadIdx.x & (kWave - 1);
-  const int upc = p.taps * p.SUB;
-  f16v acc;
-#pragma unroll
-  for (int r = 0; r < 16; ++r) acc[r] = 0.f;
-  for (int u = u0; u < u1; ++u) {
-    const int c = p.d_upc.div(u), v = u - c * upc;
-    const int tap = p.d_SUB.div(v), sub = v - tap * p.SUB;
-    const int ch0 = (c * p.SUB + sub) * 16 + (lane >> 5) * 8;
-    float av[8], bv[8];
-    decode8(g, p, tgrp * 32 + (lane & 31), tap, ch0, av);
-#pragma unroll
-    for (int j = 0; j < 8; ++j) {
-      int ch, ktap;
-      channel_of(p, ch0 + j, tap, ch, ktap);
-      const int yy = iy + ktap / p.dk, xx = ix + ktap % p.dk;
-      const bool in = ch0 + j < p.VC && yy >= 0 && yy < p.H && xx >= 0 && xx < p.W;
-      bv[j] = in ? g.x[(((size_t)n * p.Cs + ch) * p.H + yy) * p.W + xx] : 0.f;
-    }
-#pragma unroll
-    for (int j = 0; j < 8; ++j) acc = __builtin_amdgcn_mfma_f32_32x32x2f32(av[j], bv[j], acc, 0, 0, 0);
-  }
-  return acc;
 }
 
 // Output slot q is (n, strip, yo, xl).
@@ -520,6 +535,86 @@ __device__ __forceinline__ Slot slot_of(const DenseParams& p, int q) {
   const int pl = p.d_Ho.div(row), yo = row - pl * p.Ho;
   const int n = p.d_S.div(pl);
   return {n, yo, (pl - n * p.S) * p.sw + xl, (pl * p.PH + yo * p.ssy) * p.PW + xl * p.ssx};
+}
+
+// The sums of units [u0, u1) in fp32 for a wave's 32 channels and its 32-position
+// groups (kg, kg + KG, ..), operands straight from memory: the form for inputs
+// or codewords that the split one does not hold.  Bound by the fp32 matrix rate
+// (1/16 of fp16's): the two waves of a SIMD take turns loading.
+template <int TW, bool XP>
+__device__ __forceinline__ void products_f32(int tgrp, int u0, int u1, int q0, int kg,
+                                             f16v (&acc)[ceil_div(kCF, kWaves / TW)]) {
+  const Args& args = args_again();
+  const Ptrs& g = args.g;
+  const DenseParams& p = args.p;
+  constexpr int KG = kWaves / TW, NJ = ceil_div(kCF, KG);
+  const int lane = threadIdx.x & (kWave - 1);
+  const int upc = p.taps * p.SUB;
+  const int HW4 = p.H * p.W * 4;
+  const __amdgpu_buffer_rsrc_t xres = __builtin_amdgcn_make_buffer_rsrc(
+      const_cast<float*>(g.x), 0, (int)((size_t)p.N * p.Cs * HW4), 0x00020000);
+  const DenseHead head = *reinterpret_cast<const DenseHead*>(g.w);
+  int iy[NJ], ix[NJ];    // the lane's output positions' input coordinates at tap (0, 0)
+  uint32_t plane[NJ];    // byte offset of their images
+#pragma unroll
+  for (int i = 0; i < NJ; ++i) {
+    const int q = q0 + 32 * (kg + KG * i) + (lane & 31);
+    const Slot o = slot_of(p, min(q, p.Q - 1));
+    iy[i] = q < p.Q ? o.yo * p.stride - p.pad : -(1 << 24);  // no position: outside the input
+    ix[i] = o.xo * p.stride - p.pad;
+    plane[i] = (uint32_t)(o.n * p.Cs) * (uint32_t)HW4;
+#pragma unroll
+    for (int r = 0; r < 16; ++r) acc[i][r] = 0.f;
+  }
+  const char* wp = g.w + kHeadBytes + ((size_t)tgrp * p.upt + u0) * 2048 + lane * 16;
+  for (int u = u0; u < u1; ++u, wp += 2048) {
+    const int c = p.d_upc.div(u), v = u - c * upc;
+    const int tap = p.d_SUB.div(v), sub = v - tap * p.SUB;
+    const int ch0 = (c * p.SUB + sub) * 16 + (lane >> 5) * 8;
+    const int ky = p.d_kw.div(tap), kx = tap - ky * p.kw;
+    float av[8], bv[NJ][8];
+    if (head.f32) {
+      const f4v w0 = *reinterpret_cast<const f4v*>(wp), w1 = *reinterpret_cast<const f4v*>(wp + 1024);
+#pragma unroll
+      for (int j = 0; j < 4; ++j) av[j] = w0[j], av[4 + j] = w1[j];
+    } else {
+      const h8 hi = *reinterpret_cast<const h8*>(wp), lo = *reinterpret_cast<const h8*>(wp + 1024);
+#pragma unroll
+      for (int j = 0; j < 8; ++j) av[j] = ldexpf((float)hi[j] + (float)lo[j] * (1.f / 2048.f), -head.scale_exp);
+    }
+#pragma unroll
+    for (int i = 0; i < NJ; ++i) {
+      const int yy = iy[i] + ky;
+      if constexpr (XP) {
+#pragma unroll
+        for (int j = 0; j < 8; ++j) {
+          const int kc = p.d_Cs.div(ch0 + j), xx = ix[i] + kc;
+          const bool in = kc < p.dk && (unsigned)yy < (unsigned)p.H && (unsigned)xx < (unsigned)p.W;
+          bv[i][j] = __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(
+              xres, in ? plane[i] + (uint32_t)((ch0 + j - kc * p.Cs) * HW4 + (yy * p.W + xx) * 4) : kOOB, 0, 0));
+        }
+      } else {
+        const int xx = ix[i] + kx;
+        const bool in = ch0 < p.Cs && (unsigned)yy < (unsigned)p.H && (unsigned)xx < (unsigned)p.W;
+        const uint32_t at = in ? plane[i] + (uint32_t)(ch0 * HW4 + (yy * p.W + xx) * 4) : kOOB;
+#pragma unroll
+        for (int j = 0; j < 8; ++j)
+          bv[i][j] = __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(xres, at + (uint32_t)(j * HW4), 0, 0));
+      }
+    }
+    if constexpr (!XP) {
+#pragma unroll
+      for (int j = 1; j < 8; ++j)
+#pragma unroll
+        for (int i = 0; i < NJ; ++i)
+          if (ch0 + j >= p.Cs) bv[i][j] = 0.f;  // (its weight is 0, but the value may be an infinity)
+    }
+#pragma unroll
+    for (int j = 0; j < 8; ++j)
+#pragma unroll
+      for (int i = 0; i < NJ; ++i)
+        if (i * KG + kg < kCF) acc[i] = __builtin_amdgcn_mfma_f32_32x32x2f32(av[j], bv[i][j], acc[i], 0, 0, 0);
+  }
 }
 
 template <int TW, int IT, bool XP>
@@ -581,66 +676,78 @@ __global__ __launch_bounds__(kThreads, 2) void conv_dense_kernel(Args unused) {
     // different halves of the banks.
     float* own = sums + (32 * tw + 4 * (lane >> 5)) * kSumStride + (lane & 31);
     bool split_form = head.f32 == 0;
-    if (split_form) {
-      Acc acc;
-      int x_exp;
-      split_form = products<TW, IT, XP>(ts, tgrp, a0, a1, lds, exch, acc, x_exp);
-      // The reduction groups' sums, added in group order.
-      const int ue = -(x_exp + head.scale_exp);
-      for (int k = 0; k < KG; ++k) {
-        if (k == kg) {
+    Bands bands{0, 0, 0, 0};
+    for (int band = 0; band <= bands.last; ++band) {
+      if (split_form) {
+        Acc acc;
+        int x_exp;
+        split_form = products<TW, IT, XP>(ts, tgrp, a0, a1, lds, exch, band, bands, acc, x_exp);
+        // The reduction groups' sums, added in group order.
+        const int ue = -(x_exp + head.scale_exp);
+        for (int k = 0; k < KG && split_form; ++k) {
+          if (k == kg) {
 #pragma unroll
-          for (int j = 0; j < kCF; ++j)
+            for (int j = 0; j < kCF; ++j)
 #pragma unroll
-            for (int r = 0; r < 16; ++r) {
-              float* at = own + ((r & 3) + 8 * (r >> 2)) * kSumStride + 32 * j;
-              const float v = ldexpf(acc.sum[j][r] + acc.c[j][r] * (1.f / 2048.f), ue);
-              *at = k == 0 ? v : *at + v;
-            }
+              for (int r = 0; r < 16; ++r) {
+                float* at = own + ((r & 3) + 8 * (r >> 2)) * kSumStride + 32 * j;
+                const float v = ldexpf(acc.sum[j][r] + acc.c[j][r] * (1.f / 2048.f), ue);
+                *at = k == 0 ? v : *at + v;
+              }
+          }
+          __syncthreads();
         }
+      }
+      if (!split_form) {
+        bands.last = 0;
+        constexpr int NJ = ceil_div(kCF, KG);
+        f16v sum[NJ];
+        products_f32<TW, XP>(tgrp, a0, a1, q0, kg, sum);
+        __syncthreads();  // the sums overwrite the staged rows
+#pragma unroll
+        for (int i = 0; i < NJ; ++i)
+          if (kg + KG * i < kCF)
+#pragma unroll
+            for (int r = 0; r < 16; ++r)
+              own[((r & 3) + 8 * (r >> 2)) * kSumStride + 32 * (kg + KG * i)] = sum[i][r];
         __syncthreads();
       }
-    }
-    if (!split_form) {
-      __syncthreads();
-      for (int j = kg; j < kCF; j += KG) {
-        const int q = q0 + 32 * j + (lane & 31);
-        const DenseParams& p = args_again().p;
-        const Slot o = slot_of(p, q);
-        const f16v sum = products_f32(tgrp, a0, a1, o.n, q < p.Q ? o.yo * p.stride - p.pad : -(1 << 24),
-                                      o.xo * p.stride - p.pad);
-#pragma unroll
-        for (int r = 0; r < 16; ++r) own[((r & 3) + 8 * (r >> 2)) * kSumStride + 32 * j] = sum[r];
-      }
-      __syncthreads();
-    }
-    // ---- the tile, or this run's share of its sums, to memory
-    const Args& after = args_again();
-    const Ptrs& g = after.g;
-    const DenseParams& pe = after.p;
-    if (a0 != 0 || a1 != pe.upt) {
-      // A run and its shared tile both only grow along the units: their sum is
-      // a place of its own.
-      float* part = g.partial + (size_t)(w + tile - pe.shared0) * (MT * kNT);
-      for (int i = threadIdx.x; i < MT * kNT / 4; i += kThreads)
-        reinterpret_cast<f4v*>(part)[i] =
-            *reinterpret_cast<const f4v*>(sums + i / (kNT / 4) * kSumStride + i % (kNT / 4) * 4);
-    } else {
-      constexpr int kRows = kThreads / kNT;  // channels at a time
-      const int ql = threadIdx.x % kNT;
-      const Slot o = slot_of(pe, q0 + ql);
-      if (threadIdx.x < kRows * kNT && q0 + ql < pe.Q && o.xo < pe.Wo) {
-        const int t_end = min(pe.Ct - tb * MT, MT), HoWo = pe.Ho * pe.Wo;
-        float* dst = g.y + ((size_t)o.n * pe.Ct + tb * MT) * HoWo + o.yo * pe.Wo + o.xo;
+      // ---- the tile, or this run's share of its sums, to memory; a later band
+      // adds to what the ones before it stored (the same thread, the same place)
+      const Args& after = args_again();
+      const Ptrs& g = after.g;
+      const DenseParams& pe = after.p;
+      if (a0 != 0 || a1 != pe.upt) {
+        // A run and its shared tile both only grow along the units: their sum is
+        // a place of its own.
+        f4v* part = reinterpret_cast<f4v*>(g.partial + (size_t)(w + tile - pe.shared0) * (MT * kNT));
+        for (int i = threadIdx.x; i < MT * kNT / 4; i += kThreads) {
+          f4v v = *reinterpret_cast<const f4v*>(sums + i / (kNT / 4) * kSumStride + i % (kNT / 4) * 4);
+          if (band > 0) v += part[i];
+          part[i] = v;
+        }
+      } else {
+        constexpr int kRows = kThreads / kNT;  // channels at a time
+        const int ql = threadIdx.x % kNT;
+        const Slot o = slot_of(pe, q0 + ql);
+        if (threadIdx.x < kRows * kNT && q0 + ql < pe.Q && o.xo < pe.Wo) {
+          const int t_end = min(pe.Ct - tb * MT, MT), HoWo = pe.Ho * pe.Wo;
+          const bool last = band == bands.last;
+          const float* bias = last ? g.bias : nullptr;
+          const bool relu = last && pe.relu;
+          float* dst = g.y + ((size_t)o.n * pe.Ct + tb * MT) * HoWo + o.yo * pe.Wo + o.xo;
 #pragma unroll 4
-        for (int t = threadIdx.x / kNT; t < t_end; t += kRows) {
-          float v = sums[t * kSumStride + ql] + (g.bias ? g.bias[tb * MT + t] : 0.f);
-          if (pe.relu) v = fmaxf(v, 0.f);
-          dst[(size_t)t * HoWo] = v;
+          for (int t = threadIdx.x / kNT; t < t_end; t += kRows) {
+            float v = sums[t * kSumStride + ql];
+            if (band > 0) v += dst[(size_t)t * HoWo];
+            v += bias ? bias[tb * MT + t] : 0.f;
+            if (relu) v = fmaxf(v, 0.f);
+            dst[(size_t)t * HoWo] = v;
+          }
         }
       }
+      __syncthreads();  // the next pass's or tile's staging overwrites the sums
     }
-    __syncthreads();  // the next tile's staging overwrites the sums
   }
 }
 
@@ -711,19 +818,19 @@ __global__ __launch_bounds__(1024) void dense_head_kernel(const float* __restric
       mx = max(mx, sm[0][i]);
       inv = max(inv, sm[1][i]);
     }
-    const int e = mx ? scale_for(mx) + 2 : 0;
+    const int e = scale_for(mx);
     head->scale_exp = e;
     head->f32 = !scalable(mx) || (mx && (int)((~inv + 1u) >> 23) - 127 + e < -14);
   }
 }
 
-// The split weights in operand order: one thread writes the 8 channels of one
-// lane, hi and lo.
+// The weights in operand order, split or (head.f32) as they are: one thread
+// writes the 8 channels of one lane.
 __global__ __launch_bounds__(256) void dense_weights_kernel(const float* __restrict__ D, CodeStream codes,
                                                             DenseParams p, int tgroups, char* __restrict__ w) {
   const int total = tgroups * p.upt * kWave;  // < 2^31: kMaxWeights
-  const int e = reinterpret_cast<const DenseHead*>(w)->scale_exp;
-  const float sc = __uint_as_float((uint32_t)min(254, max(1, e + 127)) << 23);  // only used when it is exact
+  const DenseHead head = *reinterpret_cast<const DenseHead*>(w);
+  const float sc = head.f32 ? 1.f : __uint_as_float((uint32_t)(head.scale_exp + 127) << 23);
   const int upc = p.taps * p.SUB;
   for (int i = blockIdx.x * 256 + threadIdx.x; i < total; i += gridDim.x * 256) {
     const int lane = i & 63, r = i >> 6;
@@ -732,7 +839,7 @@ __global__ __launch_bounds__(256) void dense_weights_kernel(const float* __restr
     const int tap = p.d_SUB.div(v), sub = v - tap * p.SUB;
     const int t = tg * 32 + (lane & 31);
     const int ch0 = (chunk * p.SUB + sub) * 16 + (lane >> 5) * 8;
-    h8 hi, lo;
+    float v8[8];
     int at = -1;  // the code last read
     uint32_t code = 0;
 #pragma unroll
@@ -748,12 +855,22 @@ __global__ __launch_bounds__(256) void dense_weights_kernel(const float* __restr
         }
         x = D[((size_t)m * p.K + code) * p.Csp + (ch - m * p.Csp)] * sc;
       }
-      hi[j] = (_Float16)x;
-      lo[j] = (_Float16)((x - (float)hi[j]) * 2048.f);
+      v8[j] = x;
     }
-    h8* dst = reinterpret_cast<h8*>(w + kHeadBytes + (size_t)r * 2048 + lane * 16);
-    dst[0] = hi;
-    dst[64] = lo;
+    char* dst = w + kHeadBytes + (size_t)r * 2048 + lane * 16;
+    if (head.f32) {
+      *reinterpret_cast<f4v*>(dst) = f4v{v8[0], v8[1], v8[2], v8[3]};
+      *reinterpret_cast<f4v*>(dst + 1024) = f4v{v8[4], v8[5], v8[6], v8[7]};
+      continue;
+    }
+    h8 hi, lo;
+#pragma unroll
+    for (int j = 0; j < 8; ++j) {
+      hi[j] = (_Float16)v8[j];
+      lo[j] = (_Float16)((v8[j] - (float)hi[j]) * 2048.f);
+    }
+    *reinterpret_cast<h8*>(dst) = hi;
+    *reinterpret_cast<h8*>(dst + 1024) = lo;
   }
 }
 
@@ -763,7 +880,8 @@ struct DensePlan {
   size_t lds, weight_bytes, partial_bytes;
 };
 
-// Weights read ahead of a tile's last step: two steps of 4 groups.
+// Weights read ahead past a tile's last unit: three steps of up to 2 groups
+// (and one unit where the last chunk has none for a group).
 constexpr size_t kWeightTail = 8 * 2048;
 constexpr size_t kMaxWeights = (size_t)32 << 20;
 
@@ -995,7 +1113,7 @@ hipError_t launch_conv_dense(const ConvShape& s, const float* x, const float* D,
     w = base;
   }
   float* ymap = pool ? reinterpret_cast<float*>(base + wb + pb) : y;
-  const Ptrs g{x, D, w, codes, bias, ymap, reinterpret_cast<float*>(base + wb)};
+  const Ptrs g{x, w, bias, ymap, reinterpret_cast<float*>(base + wb)};
   e = run_dense(pl, g, stream, ws == nullptr || ws->timed);
   if (e != hipSuccess || !pool) return e;
   return launch_maxpool(ymap, s.N, s.Ct, s.Ho, s.Wo, pool->k, pool->s, pool->Hp, pool->Wp, y, stream);

@@ -488,16 +488,13 @@ qcnn_status qcnn_conv_plan_create(int N, int C_s, int H, int W, const float* cod
   proto.nx = c.nx;
   proto.ny = c.ny;
   const ConvShape sh = c.sh;
-  if (dense) {  // the rebuilt weights, then the code stream
-    const size_t wb = qcnn::conv_dense_weight_bytes(sh);
+  if (dense)  // the rebuilt weights
     return make_plan(
-        proto, codebooks, c.nd, codes, c.nc, c.cb, wb + (c.cb + 3) / 4 * 4,
+        proto, codebooks, c.nd, codes, c.nc, c.cb, qcnn::conv_dense_weight_bytes(sh),
         [&](const qcnn::CodeStream& cs, uint8_t* out) {
-          const hipError_t e = qcnn::launch_conv_dense_weights(sh, codebooks, cs, reinterpret_cast<char*>(out), st);
-          return e != hipSuccess ? e : hipMemcpyAsync(out + wb, codes, c.cb, hipMemcpyDeviceToDevice, st);
+          return qcnn::launch_conv_dense_weights(sh, codebooks, cs, reinterpret_cast<char*>(out), st);
         },
         bias, plan, st);
-  }
   return make_plan(
       proto, codebooks, c.nd, codes, c.nc, c.cb, proto.relaid ? qcnn::conv_flat_code_bytes(sh) : 0,
       [&](const qcnn::CodeStream& cs, uint8_t* out) { return qcnn::launch_conv_flat_codes(sh, cs, out, st); }, bias,
@@ -552,11 +549,9 @@ qcnn_status qcnn_plan_forward(const qcnn_plan* plan, const float* x, float* y, v
         qcnn::launch_fc_forward(sh.N, sh.Cs, sh.M, sh.K, sh.Csp, sh.Ct, x, plan->D, cs, plan->bias, plan->relu, y, st));
   }
   const qcnn::PoolSpec* pool = plan->pooled ? &plan->pool : nullptr;
-  if (plan->kind == 3) {
-    const qcnn::CodeStream copy{plan->codes + qcnn::conv_dense_weight_bytes(sh), plan->bits};
-    return hip_status(qcnn::launch_conv_dense(sh, x, plan->D, copy, reinterpret_cast<const char*>(plan->codes),
+  if (plan->kind == 3)
+    return hip_status(qcnn::launch_conv_dense(sh, x, plan->D, cs, reinterpret_cast<const char*>(plan->codes),
                                               plan->bias, plan->relu, y, st, nullptr, pool));
-  }
   if (plan->relaid)
     return hip_status(qcnn::launch_conv_flat_relaid(sh, x, plan->D, plan->codes, plan->bias, plan->relu, y, st, pool));
   if (pool)

@@ -14,7 +14,7 @@ namespace qcnn {
 
 constexpr int kWave = 64;  // CDNA wavefront width
 
-inline int ceil_div(int a, int b) { return (a + b - 1) / b; }
+constexpr int ceil_div(int a, int b) { return (a + b - 1) / b; }
 inline size_t ceil_div_z(size_t a, size_t b) { return (a + b - 1) / b; }
 
 // The caller's codes as a stream of `bits` bits per code, base 4-byte
@@ -166,8 +166,7 @@ size_t conv_dense_workspace(const ConvShape& s);
 size_t conv_dense_weight_bytes(const ConvShape& s);
 hipError_t launch_conv_dense_weights(const ConvShape& s, const float* D, CodeStream codes, char* w,
                                      hipStream_t stream);
-// D and codes are read by the fp32 form of the kernel.  With `pool`, y is the
-// pooled map.
+// D and codes are only read when w is null.  With `pool`, y is the pooled map.
 hipError_t launch_conv_dense(const ConvShape& s, const float* x, const float* D, CodeStream codes, const char* w,
                              const float* bias, int relu, float* y, hipStream_t stream, const Workspace* ws,
                              const PoolSpec* pool = nullptr);

@@ -143,6 +143,42 @@ def test_dense_small_beside_large(dev, oracle, where, ratio):
     assert np.all(np.abs(y.astype(np.float64) - ref) <= RTOL * A + 1e-30)
 
 
+@pytest.mark.parametrize("what", ["all chunks", "last subspace", "codewords"])
+@pytest.mark.parametrize("power", [-20, -40, -70, -100])
+@pytest.mark.parametrize("shape", [SHAPES[i] for i in (0, 2, 3, 4, 6, 8, 10, 13, 14, 15, 17)], ids=str)
+def test_dense_range_bands(dev, oracle, shape, power, what):
+    """Results made only of inputs far below the largest, small integers times
+    2^power, equal bit for bit, bias and ReLU included: the first pass alone, in
+    a second and a third pass over all chunks or over the last one, and past
+    those, or with codewords of that range, the fp32 form; per call and through
+    a plan, with tiles of one run and of several."""
+    from paper_1512_06473_amd import api
+    N, Cs, H, W, Ct, dk, s, p, Csp, K = shape
+    rng = np.random.Generator(np.random.PCG64(31))
+    x, D, codes = wl.random_conv(rng, N, Cs, H, W, Ct, dk, s, p, Csp, K, integer=True)
+    M, f = Cs // Csp, np.float32(2.0 ** power)
+    bias = rng.integers(-3, 4, Ct).astype(np.float32) * f
+    if what == "codewords":
+        if M == 1:
+            pytest.skip("one subspace")
+        D[M - 1] *= f
+        x[:, :(M - 1) * Csp] = 0.0
+    else:
+        # the small channels: within each subspace, so that both lie side by side, or the last one's
+        small = np.arange(Cs) % 2 == 1 if what == "all chunks" else np.arange(Cs) >= Cs - Csp
+        if small.all() or not small.any():
+            pytest.skip("no channels of both kinds")
+        x[:, small] *= f
+        for m in range(M):
+            D[m][:, ~small[m * Csp:(m + 1) * Csp]] = 0.0
+    y = conv(dev, x, D, codes, s, p, bias, True)
+    ref = np.maximum(oracle.conv_lut(x, D, codes, s, p) + bias[None, :, None, None].astype(np.float64), 0.0)
+    assert ref.any()
+    assert np.array_equal(y.astype(np.float64), ref), float(np.abs(y - ref).max() / float(f))
+    plan = api.ConvPlan(x.shape, T(D, dev), T(codes, dev), s, p, T(bias, dev), True)
+    assert np.array_equal(plan(T(x, dev)).cpu().numpy(), y)
+
+
 @pytest.mark.parametrize("where", ["x", "D", "packed rows"])
 def test_dense_non_finite(dev, where, monkeypatch):
     """Infinities and NaN reach exactly the outputs they reach through the
