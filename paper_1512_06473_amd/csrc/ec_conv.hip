@@ -719,6 +719,11 @@ template <int CSP> size_t system_doubles(int K) {
 
 template <int CSP> constexpr int rows_threads() { return CSP <= 4 ? 1024 : 512; }
 
+// Entries of a column block whose shares are added at a time: 32 KB of LDS,
+// whatever K (all C's^2 of them at once took 128 KB at K = 256, C's = 8, and
+// with the codes and the list of 9375 pairs or more did not fit).
+template <int CSP> constexpr int rows_slice() { return std::min(CSP * CSP, 4096 / rows_threads<CSP>()); }
+
 // Row k = blockIdx.x.  LDS: the codes, the list of k's pairs in (c, p) order
 // (one run of it per wave, compacted by that wave), the Gram blocks (GL).  A
 // thread owns one column block k' and, of the `parts` threads that share it,
@@ -735,15 +740,15 @@ __global__ __launch_bounds__(rows_threads<CSP>()) void ecc_rows_kernel(const dou
                                                                      double* __restrict__ r0,
                                                                      int* __restrict__ used) {
   extern __shared__ double sh[];
-  constexpr int NT = rows_threads<CSP>(), NW = NT / kWave, SQ = CSP * CSP;
+  constexpr int NT = rows_threads<CSP>(), NW = NT / kWave, SQ = CSP * CSP, SE = rows_slice<CSP>();
   const int K = q.K, P = q.P, npairs = q.Ct * P;
   const int k = blockIdx.x;
   const int kp = (K + kWave - 1) / kWave * kWave;
   const int parts = NT / kp;
   double* red = sh;                      // [NT] partial sums
   double* Al = red + NT;                 // [C's][C's]
-  double* share = Al + SQ;               // [C's^2][kp]
-  double* Gl = share + (size_t)kp * SQ;
+  double* share = Al + SQ;               // [SE][NT]
+  double* Gl = share + SE * NT;
   int* wn = reinterpret_cast<int*>(Gl + (GL ? (size_t)P * P * SQ : 0));  // [NW] first entry of each wave's run
   uint16_t* list = reinterpret_cast<uint16_t*>(wn + NW + 1);
   uint8_t* cs = reinterpret_cast<uint8_t*>(list + npairs);
@@ -815,15 +820,19 @@ __global__ __launch_bounds__(rows_threads<CSP>()) void ecc_rows_kernel(const dou
     }
   }
   __syncthreads();
-  for (int w = 1; w < min(parts, n_k); ++w) {
-    if (part == w)
+  if (min(parts, n_k) > 1) {
 #pragma unroll
-      for (int i = 0; i < SQ; ++i) share[(size_t)i * kp + kc] = acc[i];
-    __syncthreads();
-    if (part == 0)
+    for (int i0 = 0; i0 < SQ; i0 += SE) {
+      if (i0 > 0) __syncthreads();
+      if (part > 0)
 #pragma unroll
-      for (int i = 0; i < SQ; ++i) acc[i] += share[(size_t)i * kp + kc];
-    __syncthreads();
+        for (int i = i0; i < i0 + SE && i < SQ; ++i) share[(i - i0) * NT + tid] = acc[i];
+      __syncthreads();
+      if (part == 0)
+        for (int w = 1; w < min(parts, n_k); ++w)
+#pragma unroll
+          for (int i = i0; i < i0 + SE && i < SQ; ++i) acc[i] += share[(i - i0) * NT + w * kp + kc];
+    }
   }
   double bk = 0.0;  // of thread j < C's
   if (tid < CSP) {
@@ -892,10 +901,9 @@ __global__ __launch_bounds__(rows_threads<CSP>()) void ecc_rows_kernel(const dou
   }
 }
 
-template <int CSP, bool GL> size_t rows_lds_bytes(int K, int npairs, int P) {
+template <int CSP, bool GL> size_t rows_lds_bytes(int npairs, int P) {
   constexpr int NT = rows_threads<CSP>();
-  const int kp = ceil_div(K, kWave) * kWave;
-  const size_t dbl = NT + CSP * CSP + (size_t)kp * CSP * CSP + (GL ? (size_t)P * P * CSP * CSP : 0);
+  const size_t dbl = NT + CSP * CSP + rows_slice<CSP>() * NT + (GL ? (size_t)P * P * CSP * CSP : 0);
   return dbl * 8 + (NT / kWave + 1) * 4 + (size_t)npairs * 3;
 }
 
@@ -1221,8 +1229,8 @@ hipError_t launch_ecc_csp(const EccParams& q, const float* S, const float* T, fl
   const int sblocks = (int)(sbx * sby);  // the starting residual's block sums
   const int pblocks = ceil_div(npairs, kCThreads);
   // the Gram blocks go to LDS when they fit beside the rest
-  const bool gl = rows_lds_bytes<CSP, true>(q.K, npairs, q.P) <= kLdsBytes;
-  const size_t rlds = gl ? rows_lds_bytes<CSP, true>(q.K, npairs, q.P) : rows_lds_bytes<CSP, false>(q.K, npairs, q.P);
+  const bool gl = rows_lds_bytes<CSP, true>(npairs, q.P) <= kLdsBytes;
+  const size_t rlds = gl ? rows_lds_bytes<CSP, true>(npairs, q.P) : rows_lds_bytes<CSP, false>(npairs, q.P);
   const size_t slds = solve_lds_bytes<CSP>(q.K);
   constexpr int NW = kCThreads / kWave;
   const size_t blds = ((size_t)q.K * CSP + NW * (kWave / CSP) * CSP + NW * CSP) * 8 + (size_t)NW * q.P;

@@ -28,6 +28,7 @@ CASES = [
     (1, 8, 36, 36, 20, 3, 1, 1, 4, 32),   # map of 23 KB: fused
     (1, 8, 40, 40, 20, 3, 1, 1, 4, 32),   # 28 KB: past the pass's
     (1, 8, 48, 44, 20, 3, 1, 1, 4, 32),   # 37 KB: past the Gram's as well
+    (2, 8, 4, 4, 1050, 3, 1, 0, 8, 256),  # 9450 pairs at the largest K and C's
 ]
 
 
@@ -45,3 +46,24 @@ def test_ec_conv_edges(case):
     assert np.array_equal(c, cr), int((c != cr).sum())
     assert np.allclose(D, Dr, rtol=1e-6, atol=1e-7 * float(np.abs(Dr).max())), float(np.abs(D - Dr).max())
     assert np.allclose(obj, hr, rtol=1e-9, atol=1e-9 * hr[0])
+
+
+@pytest.mark.parametrize("case", [(1, 16, 5, 5, 655, 5, 1, 2, 8, 193), (2, 16, 4, 4, 1820, 3, 1, 1, 8, 256),
+                                  (1, 7, 4, 4, 16384, 1, 1, 0, 7, 256)], ids=str)
+def test_ec_conv_largest(case):
+    """The largest pair counts (C_t d_k^2 up to 16384) with K and C's at their
+    largest: the objective falls step by step and ends at the error of the
+    sub-codebooks and codes that were returned (float64, on sub-codebooks
+    rounded to fp32)."""
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    from oracle import oracle
+    N, Cs, H, W, Ct, dk, st, pd, Csp, K = case
+    print("ec_conv largest", case, flush=True)
+    rng = np.random.Generator(np.random.PCG64(9500 + Ct))
+    S, T, D0, c0 = problem(rng, N, Cs, H, W, Ct, dk, st, pd, Csp, K)
+    D, c, obj = run_gpu(api_mod, torch.device("cuda:0"), S, T, D0, c0, st, pd, 1, 1)
+    assert np.all(np.diff(obj) <= 1e-9 * obj[0])
+    for Dx, cx, want in ((D0, c0, obj[0]), (D, c, obj[-1])):
+        err = ((T - oracle.conv_direct(S, Dx, cx, st, pd)) ** 2).sum()
+        assert abs(err - want) <= 1e-5 * obj[0], (err, want)
