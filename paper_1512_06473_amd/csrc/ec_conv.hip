@@ -719,10 +719,26 @@ template <int CSP> size_t system_doubles(int K) {
 
 template <int CSP> constexpr int rows_threads() { return CSP <= 4 ? 1024 : 512; }
 
-// Entries of a column block whose shares are added at a time: 32 KB of LDS,
+// Entries of a column block whose shares are added at a time: 16 KB of LDS,
 // whatever K (all C's^2 of them at once took 128 KB at K = 256, C's = 8, and
 // with the codes and the list of 9375 pairs or more did not fit).
-template <int CSP> constexpr int rows_slice() { return std::min(CSP * CSP, 4096 / rows_threads<CSP>()); }
+template <int CSP> constexpr int rows_slice() { return std::min(CSP * CSP, 2048 / rows_threads<CSP>()); }
+
+// Counts of (k', p') for one p: kCountP positions p' at a time, rows of an odd
+// number of words.
+constexpr int kCountP = 16, kCountLd = kCountP + 1;
+
+// Pairs of a sub-codeword up to which its row is made from the list: a count
+// takes P ceil(P / kCountP) steps whatever the pairs.  us a sweep, list ->
+// counts: 3x3, 24 channels, all 216 pairs on one of 16 codes 469 -> 280; 256
+// channels, 288 a code 1220 -> 640; all 4608 on one of 256, C's = 8, 139000 ->
+// 4030; 11x11, 40 channels, 151 pairs a code 19000 -> 27700.
+__device__ __forceinline__ int list_pairs(int P) { return 128 * ((P + kCountP - 1) / kCountP); }
+
+// LDS of the shares, and of the counts before them.
+template <int CSP> __host__ __device__ constexpr size_t rows_area(int K) {
+  return std::max((size_t)rows_slice<CSP>() * rows_threads<CSP>() * 8, ((size_t)K * kCountLd * 4 + 7) / 8 * 8);
+}
 
 // Row k = blockIdx.x.  LDS: the codes, the list of k's pairs in (c, p) order
 // (one run of it per wave, compacted by that wave), the Gram blocks (GL).  A
@@ -730,7 +746,11 @@ template <int CSP> constexpr int rows_slice() { return std::min(CSP * CSP, 4096 
 // every parts-th pair: it adds the G[p][p'] of the pair's positions on k'.
 // The shares are added in order.  The kernel's time is that of the largest
 // sub-codeword (some take ten times the mean number of pairs), hence as many
-// threads per row as the sums' registers allow.
+// threads per row as the sums' registers allow.  A sub-codeword of more than
+// list_pairs is counted instead: per p, how many of its channels have k'
+// at p' (integer counts, whatever their order), times G[p][p'], so that neither
+// the number of its pairs nor how many share one k' makes a thread's chain
+// longer.
 template <int CSP, bool GL>
 __global__ __launch_bounds__(rows_threads<CSP>()) void ecc_rows_kernel(const double* __restrict__ H, EccParams q,
                                                                      int m, const double* __restrict__ G,
@@ -747,8 +767,9 @@ __global__ __launch_bounds__(rows_threads<CSP>()) void ecc_rows_kernel(const dou
   const int parts = NT / kp;
   double* red = sh;                      // [NT] partial sums
   double* Al = red + NT;                 // [C's][C's]
-  double* share = Al + SQ;               // [SE][NT]
-  double* Gl = share + SE * NT;
+  double* share = Al + SQ;               // [SE][NT], before that the counts
+  uint32_t* cnt = reinterpret_cast<uint32_t*>(share);
+  double* Gl = share + rows_area<CSP>(K) / 8;
   int* wn = reinterpret_cast<int*>(Gl + (GL ? (size_t)P * P * SQ : 0));  // [NW] first entry of each wave's run
   uint16_t* list = reinterpret_cast<uint16_t*>(wn + NW + 1);
   uint8_t* cs = reinterpret_cast<uint8_t*>(list + npairs);
@@ -801,7 +822,30 @@ __global__ __launch_bounds__(rows_threads<CSP>()) void ecc_rows_kernel(const dou
   double acc[SQ];
 #pragma unroll
   for (int i = 0; i < SQ; ++i) acc[i] = 0.0;
-  for (int r = part < parts ? part : n_k; r < n_k; r += parts) {
+  const bool counted = n_k > list_pairs(P);
+  if (counted) {
+    for (int p = 0; p < P; ++p)
+      for (int p0 = 0; p0 < P; p0 += kCountP) {
+        __syncthreads();  // the counts before these are used
+        for (int i = tid; i < K * kCountLd; i += NT) cnt[i] = 0;
+        __syncthreads();
+        for (int i = tid; i < q.Ct * kCountP; i += NT) {
+          const int u = i % kCountP;
+          const uint8_t* kk = cs + i / kCountP * P;
+          if (p0 + u < P && kk[p] == k) atomicAdd(&cnt[kk[p0 + u] * kCountLd + u], 1u);
+        }
+        __syncthreads();
+        if (part < parts && kc < K)
+          for (int u = part; u < min(kCountP, P - p0); u += parts) {
+            const uint32_t times = cnt[kc * kCountLd + u];
+            if (times == 0) continue;
+            const double* g = Gm + ((size_t)p * P + p0 + u) * SQ;
+#pragma unroll
+            for (int i = 0; i < SQ; ++i) acc[i] += (double)times * g[i];
+          }
+      }
+  }
+  for (int r = part < parts && !counted ? part : n_k; r < n_k; r += parts) {
     const int pr = list[r];
     const int c = (int)(((float)pr + 0.5f) * rcp_p), p = pr - c * P;  // exact: pr < 2^14
     const uint8_t* kk = cs + c * P;
@@ -901,9 +945,9 @@ __global__ __launch_bounds__(rows_threads<CSP>()) void ecc_rows_kernel(const dou
   }
 }
 
-template <int CSP, bool GL> size_t rows_lds_bytes(int npairs, int P) {
+template <int CSP, bool GL> size_t rows_lds_bytes(int K, int npairs, int P) {
   constexpr int NT = rows_threads<CSP>();
-  const size_t dbl = NT + CSP * CSP + rows_slice<CSP>() * NT + (GL ? (size_t)P * P * CSP * CSP : 0);
+  const size_t dbl = NT + CSP * CSP + rows_area<CSP>(K) / 8 + (GL ? (size_t)P * P * CSP * CSP : 0);
   return dbl * 8 + (NT / kWave + 1) * 4 + (size_t)npairs * 3;
 }
 
@@ -1229,8 +1273,8 @@ hipError_t launch_ecc_csp(const EccParams& q, const float* S, const float* T, fl
   const int sblocks = (int)(sbx * sby);  // the starting residual's block sums
   const int pblocks = ceil_div(npairs, kCThreads);
   // the Gram blocks go to LDS when they fit beside the rest
-  const bool gl = rows_lds_bytes<CSP, true>(npairs, q.P) <= kLdsBytes;
-  const size_t rlds = gl ? rows_lds_bytes<CSP, true>(npairs, q.P) : rows_lds_bytes<CSP, false>(npairs, q.P);
+  const bool gl = rows_lds_bytes<CSP, true>(q.K, npairs, q.P) <= kLdsBytes;
+  const size_t rlds = gl ? rows_lds_bytes<CSP, true>(q.K, npairs, q.P) : rows_lds_bytes<CSP, false>(q.K, npairs, q.P);
   const size_t slds = solve_lds_bytes<CSP>(q.K);
   constexpr int NW = kCThreads / kWave;
   const size_t blds = ((size_t)q.K * CSP + NW * (kWave / CSP) * CSP + NW * CSP) * 8 + (size_t)NW * q.P;

@@ -28,12 +28,17 @@ CASES = [
     (1, 8, 36, 36, 20, 3, 1, 1, 4, 32),   # map of 23 KB: fused
     (1, 8, 40, 40, 20, 3, 1, 1, 4, 32),   # 28 KB: past the pass's
     (1, 8, 48, 44, 20, 3, 1, 1, 4, 32),   # 37 KB: past the Gram's as well
+    (1, 6, 24, 24, 30, 7, 2, 2, 3, 20),   # 49 positions: four groups of counts
     (2, 8, 4, 4, 1050, 3, 1, 0, 8, 256),  # 9450 pairs at the largest K and C's
 ]
 
 
+# The codes at the start: drawn, all the same, or one half the same.
+@pytest.mark.parametrize("start", ["drawn", "one", "half"])
 @pytest.mark.parametrize("case", CASES, ids=[str(c) for c in CASES])
-def test_ec_conv_edges(case):
+def test_ec_conv_edges(case, start):
+    if start != "drawn" and case[9] > 130:
+        pytest.skip("long in the oracle")
     if not torch.cuda.is_available():
         pytest.skip("no GPU")
     from oracle import ec_conv
@@ -41,6 +46,10 @@ def test_ec_conv_edges(case):
     print("ec_conv edge", case, flush=True)
     rng = np.random.Generator(np.random.PCG64(9400 + CASES.index(case)))
     S, T, D0, c0 = problem(rng, N, Cs, H, W, Ct, dk, st, pd, Csp, K)
+    if start == "one":
+        c0[...] = K - 1
+    elif start == "half":  # rows made from the list and from counts in one layer
+        c0[: Ct // 2] = 1 % K
     D, c, obj = run_gpu(api_mod, torch.device("cuda:0"), S, T, D0, c0, st, pd, 1, 1)
     Dr, cr, hr = ec_conv.ec_conv(S, T, D0, c0, st, pd, 1, 1)
     assert np.array_equal(c, cr), int((c != cr).sum())
