@@ -228,13 +228,13 @@ size_t gram_lds_bytes(const EccParams& q) {
 hipError_t launch_gram(const float* S, const EccParams& q, size_t lds, double* gpart, double* G, hipStream_t stream) {
   const int pw = (q.Wo - 1) * q.stride + q.dk, plane = ((q.Ho - 1) * q.stride + q.dk) * pw;
   const dim3 grid((unsigned)q.M, kGramChunks);
-#define QCNN_GRAM(nt) \
-  case nt: hipLaunchKernelGGL(ecc_gram_mfma_kernel<nt>, grid, dim3(kCThreads), lds, stream, S, q, pw, plane, gpart); \
-    break;
-  switch ((q.P * q.Csp + 15) / 16) { QCNN_GRAM(1) QCNN_GRAM(2) QCNN_GRAM(3) QCNN_GRAM(4) }
-#undef QCNN_GRAM
-  const hipError_t e = hipGetLastError();
+  const int nt = (q.P * q.Csp + 15) / 16;
+  auto gram = nt == 1 ? ecc_gram_mfma_kernel<1> : nt == 2 ? ecc_gram_mfma_kernel<2> : nt == 3 ? ecc_gram_mfma_kernel<3>
+                                                                                               : ecc_gram_mfma_kernel<4>;
+  hipError_t e = allow_max_lds((const void*)gram);  // sums 32 KB, maps 32 KB, offsets of up to 8192 outputs 32 KB
   if (e != hipSuccess) return e;
+  hipLaunchKernelGGL(gram, grid, dim3(kCThreads), lds, stream, S, q, pw, plane, gpart);
+  if ((e = hipGetLastError()) != hipSuccess) return e;
   const size_t total = (size_t)q.M * q.P * q.P * q.Csp * q.Csp;
   hipLaunchKernelGGL(ecc_gram_sum_kernel, dim3((unsigned)ceil_div_z(total, kCThreads)), dim3(kCThreads), 0, stream,
                      (const double*)gpart, q, G);
@@ -593,13 +593,19 @@ size_t pass_shape(const EccParams& q, PassShape* ps) {
 hipError_t launch_pass(const float* S, const EccParams& q, const PassShape& ps, size_t lds, int ma, int m,
                        const double* delta, double* E, double* opart, double* part, hipStream_t stream) {
   const dim3 grid((unsigned)ceil_div(q.Ct, 64), (unsigned)(q.N * ps.parts));
-#define QCNN_PASS(nt) \
-  case nt: hipLaunchKernelGGL(ecc_pass_kernel<nt>, grid, dim3(kCThreads), lds, stream, S, q, ps, ma, m, delta, E, \
-                              opart, part); break;
+  auto pass = ecc_pass_kernel<8>;
   switch ((q.P * q.Csp + 15) / 16) {
-    QCNN_PASS(1) QCNN_PASS(2) QCNN_PASS(3) QCNN_PASS(4) QCNN_PASS(5) QCNN_PASS(6) QCNN_PASS(7) QCNN_PASS(8)
+    case 1: pass = ecc_pass_kernel<1>; break;
+    case 2: pass = ecc_pass_kernel<2>; break;
+    case 3: pass = ecc_pass_kernel<3>; break;
+    case 4: pass = ecc_pass_kernel<4>; break;
+    case 5: pass = ecc_pass_kernel<5>; break;
+    case 6: pass = ecc_pass_kernel<6>; break;
+    case 7: pass = ecc_pass_kernel<7>; break;
   }
-#undef QCNN_PASS
+  const hipError_t e = allow_max_lds((const void*)pass);  // maps 48 KB, offsets of up to 6144 outputs 24 KB
+  if (e != hipSuccess) return e;
+  hipLaunchKernelGGL(pass, grid, dim3(kCThreads), lds, stream, S, q, ps, ma, m, delta, E, opart, part);
   return hipGetLastError();
 }
 

@@ -58,10 +58,12 @@ def test_ec_conv_edges(case, start):
 
 
 @pytest.mark.parametrize("case", [(1, 16, 5, 5, 655, 5, 1, 2, 8, 193), (2, 16, 4, 4, 1820, 3, 1, 1, 8, 256),
-                                  (1, 7, 4, 4, 16384, 1, 1, 0, 7, 256)], ids=str)
+                                  (1, 7, 4, 4, 16384, 1, 1, 0, 7, 256),
+                                  (1536, 1, 78, 78, 1, 1, 1, 0, 1, 2),  # 73 KB of LDS in the pass
+                                  (2, 1, 90, 90, 4, 7, 1, 0, 1, 5)], ids=str)  # 93 KB for the Gram blocks
 def test_ec_conv_largest(case):
     """The largest pair counts (C_t d_k^2 up to 16384) with K and C's at their
-    largest: the objective falls step by step and ends at the error of the
+    largest, and the largest LDS of the pass and of the Gram kernel: the objective falls step by step and ends at the error of the
     sub-codebooks and codes that were returned (float64, on sub-codebooks
     rounded to fp32)."""
     if not torch.cuda.is_available():
