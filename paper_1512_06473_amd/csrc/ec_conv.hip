@@ -467,10 +467,10 @@ __global__ __launch_bounds__(kCThreads) void ecc_pass_kernel(const float* __rest
                                                            int ma, int m, const double* __restrict__ delta,
                                                            double* __restrict__ E, double* __restrict__ opart,
                                                            double* __restrict__ part) {
-  extern __shared__ float smf[];
-  __shared__ double red[kCThreads / kWave];
+  extern __shared__ double smd[];
   const int QN = q.P * q.Csp, size = q.Csp * ps.plane;
-  float* sa = smf;                                // subspace ma's maps
+  double* red = smd;                              // a sum per wave (no static LDS beside the largest dynamic)
+  float* sa = reinterpret_cast<float*>(smd + kCThreads / kWave);  // subspace ma's maps
   float* sm = sa + size;                          // subspace m's
   int* qoff = reinterpret_cast<int*>(sm + size);  // [16 NT] offset of (p, j)
   int* ooff = qoff + 16 * NT;                     // [16 tiles] offset of an output
@@ -587,7 +587,7 @@ size_t pass_shape(const EccParams& q, PassShape* ps) {
   int parts = std::max(1, std::min(ceil_div(1536, waves), tiles / 4));
   ps->tiles = ceil_div(tiles, parts);
   ps->parts = ceil_div(tiles, ps->tiles);
-  return (size_t)2 * q.Csp * plane * 4 + (size_t)16 * ((q.P * q.Csp + 15) / 16) * 4 + (size_t)16 * ps->tiles * 4;
+  return (size_t)kCThreads / kWave * 8 + (size_t)2 * q.Csp * plane * 4 + (size_t)16 * ((q.P * q.Csp + 15) / 16) * 4 + (size_t)16 * ps->tiles * 4;
 }
 
 hipError_t launch_pass(const float* S, const EccParams& q, const PassShape& ps, size_t lds, int ma, int m,
