@@ -448,7 +448,8 @@ __global__ __launch_bounds__(kCThreads) void ecc_corr_kernel(const float* __rest
 // register i of lane l of a result holds row 4 i + l / 16, column l % 16, and
 // that is the second product's B operand of its reduction step i as it stands.
 // A workgroup is 4 waves of 16 channels each over `tiles` 16-position tiles of
-// one image (blockIdx.y = image x pass_parts + part); the two subspaces' input
+// `images` images, one after the other with H^T kept in registers (blockIdx.y =
+// image group x parts + part); the two subspaces' input
 // maps sit in LDS with their zero halos, and tables give an output's and a
 // (p, j)'s offset in them.  Grid order of the sums: part[blockIdx.y][c][p][j],
 // opart[blockIdx.y gridDim.x + blockIdx.x].
@@ -456,7 +457,8 @@ __global__ __launch_bounds__(kCThreads) void ecc_corr_kernel(const float* __rest
 // written once, take a third of that); apply and correlation as kernels of
 // their own took 35 + 60 us at 384 channels, 32 x 13 x 13 outputs, 3x3, C's = 4.
 struct PassShape {
-  int parts, tiles;  // workgroups per image and channel block, 16-position tiles of each
+  int images, groups;  // images per workgroup, groups of them
+  int parts, tiles;    // workgroups per image and channel block, 16-position tiles of each
   int pw, plane;     // staged map: columns, positions per channel
 };
 
@@ -475,17 +477,10 @@ __global__ __launch_bounds__(kCThreads) void ecc_pass_kernel(const float* __rest
   int* qoff = reinterpret_cast<int*>(sm + size);  // [16 NT] offset of (p, j)
   int* ooff = qoff + 16 * NT;                     // [16 tiles] offset of an output
   const int tid = threadIdx.x, lane = tid & (kWave - 1), wave = tid / kWave;
-  const int n = blockIdx.y / ps.parts, t0 = (blockIdx.y - n * ps.parts) * ps.tiles;
+  const int group = blockIdx.y / ps.parts, t0 = (blockIdx.y - group * ps.parts) * ps.tiles;
+  const int n0 = group * ps.images, n1 = min(q.N, n0 + ps.images);
   const int ntiles = min(ps.tiles, (q.O + 15) / 16 - t0);
   const size_t HW = (size_t)q.H * q.W;
-  for (int i = tid; i < size; i += kCThreads) {
-    const int j = i / ps.plane, r = i - j * ps.plane;
-    const int y = r / ps.pw - q.pad, x = r % ps.pw - q.pad;
-    const bool in = (unsigned)y < (unsigned)q.H && (unsigned)x < (unsigned)q.W;
-    const float* src = S + ((size_t)n * q.Cs + j) * HW + (in ? (size_t)y * q.W + x : 0);
-    sa[i] = in && ma >= 0 ? src[(size_t)ma * q.Csp * HW] : 0.f;
-    sm[i] = in && m >= 0 ? src[(size_t)m * q.Csp * HW] : 0.f;
-  }
   for (int i = tid; i < 16 * NT; i += kCThreads) {
     const int p = i / q.Csp, j = i - p * q.Csp;
     qoff[i] = i < QN ? j * ps.plane + (p / q.dk) * ps.pw + p % q.dk : 0;
@@ -494,11 +489,9 @@ __global__ __launch_bounds__(kCThreads) void ecc_pass_kernel(const float* __rest
     const int o = t0 * 16 + i;
     ooff[i] = o < q.O ? (o / q.Wo) * q.stride * ps.pw + (o % q.Wo) * q.stride : 0;
   }
-  __syncthreads();
   const int col = lane & 15, quad = lane >> 4;
   const int c = (blockIdx.x * (kCThreads / kWave) + wave) * 16 + col;
   const bool live = c < q.Ct;
-  double* er = E + ((size_t)n * q.Ct + (live ? c : 0)) * q.O;
   // the change of ma as the first product's B operand (0 past the (p, j))
   double db[4 * NT];
 #pragma unroll
@@ -510,45 +503,58 @@ __global__ __launch_bounds__(kCThreads) void ecc_pass_kernel(const float* __rest
 #pragma unroll
   for (int t = 0; t < NT; ++t) h[t] = d4v{0.0, 0.0, 0.0, 0.0};
   double sq = 0.0;
-  double e[4];
-  auto load_e = [&](int t, double (&v)[4]) {
-#pragma unroll
-    for (int i = 0; i < 4; ++i) {
-      const int o = (t0 + t) * 16 + 4 * i + quad;
-      v[i] = live && o < q.O ? er[o] : 0.0;
+  for (int n = n0; n < n1; ++n) {
+    if (n > n0) __syncthreads();  // the last image's maps are read
+    for (int i = tid; i < size; i += kCThreads) {
+      const int j = i / ps.plane, r = i - j * ps.plane;
+      const int y = r / ps.pw - q.pad, x = r % ps.pw - q.pad;
+      const bool in = (unsigned)y < (unsigned)q.H && (unsigned)x < (unsigned)q.W;
+      const float* src = S + ((size_t)n * q.Cs + j) * HW + (in ? (size_t)y * q.W + x : 0);
+      sa[i] = in && ma >= 0 ? src[(size_t)ma * q.Csp * HW] : 0.f;
+      sm[i] = in && m >= 0 ? src[(size_t)m * q.Csp * HW] : 0.f;
     }
-  };
-  if (ntiles > 0) load_e(0, e);
-  for (int t = 0; t < ntiles; ++t) {
-    double en[4] = {0.0, 0.0, 0.0, 0.0};
-    if (t + 1 < ntiles) load_e(t + 1, en);  // one tile ahead
-    if (ma >= 0) {
-      const float* base = sa + ooff[16 * t + col];
-      d4v d = {0.0, 0.0, 0.0, 0.0};
-#pragma unroll
-      for (int kk = 0; kk < 4 * NT; ++kk)
-        if (4 * kk < QN) d = __builtin_amdgcn_mfma_f64_16x16x4f64((double)base[qoff[4 * kk + quad]], db[kk], d, 0, 0, 0);
+    __syncthreads();  // the maps, and the tables before the first image
+    double* er = E + ((size_t)n * q.Ct + (live ? c : 0)) * q.O;
+    double e[4];
+    auto load_e = [&](int t, double (&v)[4]) {
 #pragma unroll
       for (int i = 0; i < 4; ++i) {
         const int o = (t0 + t) * 16 + 4 * i + quad;
-        if (live && o < q.O) {
-          e[i] -= d[i];
-          er[o] = e[i];
-          sq += e[i] * e[i];
+        v[i] = live && o < q.O ? er[o] : 0.0;
+      }
+    };
+    if (ntiles > 0) load_e(0, e);
+    for (int t = 0; t < ntiles; ++t) {
+      double en[4] = {0.0, 0.0, 0.0, 0.0};
+      if (t + 1 < ntiles) load_e(t + 1, en);  // one tile ahead
+      if (ma >= 0) {
+        const float* base = sa + ooff[16 * t + col];
+        d4v d = {0.0, 0.0, 0.0, 0.0};
+#pragma unroll
+        for (int kk = 0; kk < 4 * NT; ++kk)
+          if (4 * kk < QN) d = __builtin_amdgcn_mfma_f64_16x16x4f64((double)base[qoff[4 * kk + quad]], db[kk], d, 0, 0, 0);
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+          const int o = (t0 + t) * 16 + 4 * i + quad;
+          if (live && o < q.O) {
+            e[i] -= d[i];
+            er[o] = e[i];
+            sq += e[i] * e[i];
+          }
         }
       }
-    }
-    if (m >= 0) {
+      if (m >= 0) {
 #pragma unroll
-      for (int kk = 0; kk < 4; ++kk) {
-        const float* base = sm + ooff[16 * t + 4 * kk + quad];
+        for (int kk = 0; kk < 4; ++kk) {
+          const float* base = sm + ooff[16 * t + 4 * kk + quad];
 #pragma unroll
-        for (int u = 0; u < NT; ++u)
-          h[u] = __builtin_amdgcn_mfma_f64_16x16x4f64((double)base[qoff[16 * u + col]], e[kk], h[u], 0, 0, 0);
+          for (int u = 0; u < NT; ++u)
+            h[u] = __builtin_amdgcn_mfma_f64_16x16x4f64((double)base[qoff[16 * u + col]], e[kk], h[u], 0, 0, 0);
+        }
       }
-    }
 #pragma unroll
-    for (int i = 0; i < 4; ++i) e[i] = en[i];
+      for (int i = 0; i < 4; ++i) e[i] = en[i];
+    }
   }
   if (m >= 0 && live) {
     double* dst = part + ((size_t)blockIdx.y * q.Ct + c) * QN;
@@ -583,7 +589,13 @@ size_t pass_shape(const EccParams& q, PassShape* ps) {
   // at least 1536 waves of 16 channels (1.5 per SIMD) as long as a piece keeps
   // 4 tiles: with fewer, SIMDs stay idle; with more, the sums over the pieces
   // grow
-  const int tiles = (q.O + 15) / 16, waves = ceil_div(q.Ct, 16) * q.N;
+  const int tiles = (q.O + 15) / 16, cb = ceil_div(q.Ct, 16);
+  // ... and past twice that a workgroup takes several images: the partial sums
+  // stay at 3072 x 16 channels x (p, j) doubles whatever N (one per image was
+  // d_k^2 C's / (H_o W_o) times the residual)
+  ps->images = std::max(1, (int)((long long)q.N * cb / 3072));
+  ps->groups = ceil_div(q.N, ps->images);
+  const int waves = cb * ps->groups;
   int parts = std::max(1, std::min(ceil_div(1536, waves), tiles / 4));
   ps->tiles = ceil_div(tiles, parts);
   ps->parts = ceil_div(tiles, ps->tiles);
@@ -592,7 +604,7 @@ size_t pass_shape(const EccParams& q, PassShape* ps) {
 
 hipError_t launch_pass(const float* S, const EccParams& q, const PassShape& ps, size_t lds, int ma, int m,
                        const double* delta, double* E, double* opart, double* part, hipStream_t stream) {
-  const dim3 grid((unsigned)ceil_div(q.Ct, 64), (unsigned)(q.N * ps.parts));
+  const dim3 grid((unsigned)ceil_div(q.Ct, 64), (unsigned)(ps.groups * ps.parts));
   auto pass = ecc_pass_kernel<8>;
   switch ((q.P * q.Csp + 15) / 16) {
     case 1: pass = ecc_pass_kernel<1>; break;
@@ -1296,8 +1308,8 @@ hipError_t launch_ecc_csp(const EccParams& q, const float* S, const float* T, fl
   size_t bytes = 0;
   PassShape ps{};
   const size_t pass_lds = pass_shape(q, &ps);
-  const int nchunks = pass_lds ? q.N * ps.parts : q.nchunks;
-  const int ablocks = pass_lds ? ceil_div(q.Ct, 64) * q.N * ps.parts : eblocks;  // block sums of a step's E^2
+  const int nchunks = pass_lds ? ps.groups * ps.parts : q.nchunks;
+  const int ablocks = pass_lds ? ceil_div(q.Ct, 64) * ps.groups * ps.parts : eblocks;  // block sums of a step's E^2
   const size_t szE = total * 8, szPart = (size_t)nchunks * npairs * CSP * 8, szH = (size_t)npairs * CSP * 8;
   const size_t szG = (size_t)q.M * q.P * q.P * CSP * CSP * 8, szD = (size_t)q.M * q.K * CSP * 8;
   const size_t szDelta = (size_t)npairs * CSP * 8, szOp = (size_t)std::max(std::max(eblocks, ablocks), sblocks) * 8, szCt = (size_t)q.M * npairs;

@@ -29,6 +29,8 @@ CASES = [
     (1, 8, 40, 40, 20, 3, 1, 1, 4, 32),   # 28 KB: past the pass's
     (1, 8, 48, 44, 20, 3, 1, 1, 4, 32),   # 37 KB: past the Gram's as well
     (1, 6, 24, 24, 30, 7, 2, 2, 3, 20),   # 49 positions: four groups of counts
+    (7001, 4, 3, 3, 5, 3, 1, 0, 4, 8),    # one output an image: two images per workgroup, the last alone
+    (1240, 2, 4, 3, 70, 3, 1, 0, 2, 6),   # the same with five channel blocks
     (2, 8, 4, 4, 1050, 3, 1, 0, 8, 256),  # 9450 pairs at the largest K and C's
 ]
 
@@ -78,3 +80,27 @@ def test_ec_conv_largest(case):
     for Dx, cx, want in ((D0, c0, obj[0]), (D, c, obj[-1])):
         err = ((T - oracle.conv_direct(S, Dx, cx, st, pd)) ** 2).sum()
         assert abs(err - want) <= 1e-5 * obj[0], (err, want)
+
+
+def test_ec_conv_scratch_of_many_images():
+    """The partial correlations do not grow with the images: 20000 of one output
+    each, 64 channels, C's = 8 (one set per image would be 737 MB)."""
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    dev = torch.device("cuda:0")
+    N, Ct = 20000, 64
+    g = torch.Generator(device=dev).manual_seed(9600)
+    S = torch.randn((N, 8, 3, 3), generator=g, device=dev)
+    T = torch.randn((N, Ct, 1, 1), generator=g, device=dev)
+    D = torch.randn((1, 4, 8), generator=g, device=dev)
+    c = torch.randint(0, 4, (Ct, 3, 3, 1), generator=g, device=dev, dtype=torch.uint8)
+    s = torch.cuda.Stream(dev)  # a scratch buffer of its own
+    s.wait_stream(torch.cuda.current_stream(dev))
+    with torch.cuda.stream(s):
+        torch.cuda.synchronize()
+        before = torch.cuda.mem_get_info(dev)[0]
+        obj = api_mod.ec_conv(S, T, D, c, 1, 0, 1, 1)
+        torch.cuda.synchronize()
+        used = before - torch.cuda.mem_get_info(dev)[0]
+    assert bool(torch.isfinite(obj).all())
+    assert used <= 200 << 20, used
