@@ -11,7 +11,12 @@
 //   * held until the process ends (the library pool keeps freed memory;
 //     the device's default pool is left as the application set it);
 //   * locked for the whole enqueue of a call, so that two host threads that
-//     share a stream cannot interleave their kernels over one buffer.
+//     share a stream cannot interleave their kernels over one buffer;
+//   * once a call on the stream has been captured into a graph, never freed:
+//     the graph holds the address.  A call that needs more while the stream is
+//     capturing takes plain device memory (a stream-ordered allocation there
+//     would belong to the graph, and the buffer outlives it).  Each buffer kept
+//     is at least 5/4 of the one before it.
 // Calls on different streams use different buffers and never wait for each
 // other.
 #include <map>
@@ -29,7 +34,27 @@ struct Slot {
   std::mutex mu;  // held by a Scratch for the enqueue of one call
   void* ptr = nullptr;
   size_t bytes = 0;
+  bool captured = false;  // a graph may hold ptr
 };
+
+bool capturing(hipStream_t stream) {
+  hipStreamCaptureStatus status = hipStreamCaptureStatusNone;
+  if (hipStreamIsCapturing(stream, &status) != hipSuccess) {
+    (void)hipGetLastError();  // the null stream beside a capture: the allocation reports it
+    return false;
+  }
+  return status == hipStreamCaptureStatusActive;
+}
+
+// Device memory for a call that is being captured.
+hipError_t capture_alloc(void** ptr, size_t bytes) {
+  hipStreamCaptureMode mode = hipStreamCaptureModeRelaxed;
+  hipError_t e = hipThreadExchangeStreamCaptureMode(&mode);
+  if (e != hipSuccess) return e;
+  e = hipMalloc(ptr, bytes);
+  const hipError_t e2 = hipThreadExchangeStreamCaptureMode(&mode);
+  return e != hipSuccess ? e : e2;
+}
 
 std::mutex g_mu;  // guards the maps (not the slots' contents)
 
@@ -57,9 +82,11 @@ hipError_t Scratch::acquire(hipStream_t stream, size_t bytes) {
   }
   s->mu.lock();
   slot_ = s;
+  const bool capture = bytes > 0 && capturing(stream);
+  if (capture) s->captured = true;
   if (s->bytes < bytes) {
     if (s->ptr) {
-      e = hipFreeAsync(s->ptr, stream);
+      e = s->captured ? hipSuccess : hipFreeAsync(s->ptr, stream);
       s->ptr = nullptr;
       s->bytes = 0;
       if (e != hipSuccess) return e;
@@ -67,7 +94,7 @@ hipError_t Scratch::acquire(hipStream_t stream, size_t bytes) {
     // Round up to 2 MiB and to 5/4 of the request, so that a few layers of
     // growing size do not each trigger a new allocation.
     const size_t want = ((bytes + bytes / 4) + ((size_t)2 << 20) - 1) & ~(((size_t)2 << 20) - 1);
-    e = pool_alloc(&s->ptr, want, stream);
+    e = capture ? capture_alloc(&s->ptr, want) : pool_alloc(&s->ptr, want, stream);
     if (e != hipSuccess) {
       s->ptr = nullptr;
       return e;

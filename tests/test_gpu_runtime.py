@@ -49,3 +49,43 @@ def test_default_pool_left_alone(dev):
     after = default_pool_threshold(dev.index or 0)
     assert after == before, (before, after)
     assert after != 2 ** 64 - 1
+
+
+def test_capture_on_a_stream_without_scratch(dev):
+    """Calls captured on a stream that no call has used, so that their workspace
+    is made during the capture, and a larger call on that stream afterwards,
+    which takes a larger one: every replay still equals the eager calls (the
+    graph's buffer is neither the graph's own nor freed)."""
+    hip = ctypes.CDLL("libamdhip64.so")
+    handle = ctypes.c_void_p()
+    assert hip.hipStreamCreate(ctypes.byref(handle)) == 0
+    s = torch.cuda.ExternalStream(handle.value, device=dev)
+    rng = np.random.Generator(np.random.PCG64(5))
+
+    def put(*a):
+        return [torch.from_numpy(np.ascontiguousarray(v)).to(dev) for v in a]
+
+    x, D, codes = put(*wl.random_conv(rng, 4, 256, 13, 13, 384, 3, 1, 1, 4, 128))
+    plan = api.ConvPlan(x.shape, D, codes, 1, 1)
+    xf, Df, cf = put(*wl.random_fc(rng, 2, 4096, 1000, 4, 32))
+    big = put(*wl.random_conv(rng, 16, 256, 28, 28, 256, 3, 1, 1, 8, 128))
+    y, z = plan(x), api.fc_forward(xf, Df, cf)  # kernel attributes, on another stream
+    torch.cuda.synchronize()
+    g = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(g, stream=s):
+        plan(x, y)
+        api.fc_forward(xf, Df, cf, out=z)
+    torch.cuda.synchronize()
+    for rep in range(4):
+        for t in (x, xf):
+            t.copy_(torch.randn(t.shape, device=dev).abs_())
+        want = plan(x), api.fc_forward(xf, Df, cf)
+        torch.cuda.synchronize()
+        with torch.cuda.stream(s):
+            if rep > 0:
+                api.conv_forward(*big, 1, 1)
+            y.fill_(float("nan"))
+            z.fill_(float("nan"))
+            g.replay()
+        torch.cuda.synchronize()
+        assert torch.equal(y, want[0]) and torch.equal(z, want[1]), rep
