@@ -634,8 +634,10 @@ hipError_t update(const QShape& q, const float* W, const uint8_t* codes, float* 
   // aligned sub-vectors, at most four sums per lane, and subspaces for three
   // workgroups on every four CUs.  us, 4096 rows, K = 32, one subspace per
   // workgroup -> four: C's = 4, 512 subspaces 42.8 -> 41.3, 256 35 -> 39; 768
-  // 51 -> 42; 2304 119 -> 69; C's = 8, 512 61 -> 64, 1024 83 -> 66.
-  if (q.P == 1 && (q.Csp == 4 || q.Csp == 8) && q.M >= 768 && q.Cs % 4 == 0 && q.K * q.Csp <= 256 &&
+  // 51 -> 42; 2304 119 -> 69; C's = 8, 512 61 -> 64, 1024 83 -> 66.  Twice as many
+  // where a row's four codes are not one aligned dword: 769 of C's = 4, K = 64 50
+  // -> 60, 1026 68 -> 71, 2305 115 -> 94.
+  if (q.P == 1 && (q.Csp == 4 || q.Csp == 8) && q.M >= (q.M % 4 == 0 ? 768 : 1536) && q.Cs % 4 == 0 && q.K * q.Csp <= 256 &&
       ((uintptr_t)W & 15) == 0 && ((uintptr_t)codes & 3) == 0) {
     auto f = q.Csp == 8 ? pq_update_fc_kernel<8, 5> : q.K <= 32 ? pq_update_fc_kernel<4, 5> : pq_update_fc_kernel<4, 6>;
     const int sets = ceil_div(q.M, kUpSubs);
