@@ -1061,6 +1061,11 @@ bool conv_dense_supported(const ConvShape& s) {
 //     for its first and last microseconds: 256 products per output, with
 //     64 output channels or fewer 512 (a tile then stages twice the input per
 //     product: 32 -> 64 channels on 28 x 28, 64 images: 33 us against 35 us).
+//     With fewer than 64 channels most of a tile is padding, and 3x3 kernels of
+//     C's = 7 and 8 have the cheapest table: from 1.7e9 padded multiply-adds on
+//     (us per call; 64 -> 24 channels, 28 x 28, 55 images, 1.6e9: 33 against 42; 512 ->
+//     16, 14 x 14, 22 images, 1.3e9: 33 against 41; 42 images, 2.4e9: 47 against
+//     46).
 //     A packed kernel row (fewer than 8 input channels) is padded to whole
 //     units and stages several rows per output row: from 1e9 multiply-adds on
 //     (AlexNet conv1: 38 us against 44 us for 4 images, 71 against 60 us for
@@ -1075,6 +1080,7 @@ bool conv_dense_better(const ConvShape& s, int table_chain) {
 bool conv_dense_large(const ConvShape& s) {
   const int products = s.Cs * s.dk * s.dk;
   const double macs = (double)s.N * s.Ho * s.Wo * s.Ct * products;
+  if (s.Csp > 6 && s.dk <= 3 && s.Ct < 64 && macs * 64 / s.Ct < 1.7e9) return false;
   return products >= (s.Ct <= 64 ? 512 : 256) && macs >= (s.dk > 1 && s.Cs < 8 ? 1e9 : s.Csp <= 4 ? 1.5e8 : 3e8);
 }
 
