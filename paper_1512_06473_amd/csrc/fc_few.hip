@@ -93,13 +93,15 @@ __global__ __launch_bounds__(kThreads) void fc_few_kernel(const float* __restric
   // wait (one at a time, the build took more than the layer).
   auto build = [&](auto vec, int mb, int total) {
     constexpr int V = decltype(vec)::value;  // elements per load
-    for (int e0 = tid; e0 < total; e0 += kThreads * kBuild) {
+    for (int b0 = 0; b0 < total; b0 += kThreads * kBuild) {
+      const int e0 = b0 + tid;
       float s[kBuild][NI];
 #pragma unroll
       for (int u = 0; u < kBuild; ++u)
 #pragma unroll
         for (int i = 0; i < NI; ++i) s[u][i] = 0.f;
-      for (int j = 0; j < p.Csp; j += V) {
+      const int csp = mb + (b0 >> p.lb) < p.M ? p.Csp : 0;  // nothing to load past the last subspace
+      for (int j = 0; j < csp; j += V) {
         float dv[kBuild][V], xv[kBuild][NI][V];
 #pragma unroll
         for (int u = 0; u < kBuild; ++u) {
@@ -305,8 +307,10 @@ bool fc_relays(int N, int Cs, int M, int K, int Csp, int Ct) { return !fc_few_be
 
 hipError_t launch_fc_forward(int N, int Cs, int M, int K, int Csp, int Ct, const float* x, const float* D,
                              CodeStream codes, const float* bias, int relu, float* y, hipStream_t stream) {
-  return (fc_relays(N, Cs, M, K, Csp, Ct) ? launch_fc_tiled : launch_fc_few)(N, Cs, M, K, Csp, Ct, x, D, codes, bias,
-                                                                             relu, y, stream);
+  auto launch = fc_relays(N, Cs, M, K, Csp, Ct) ? launch_fc_tiled
+                : !fc_tiled_supported(N, Cs, M, K, Csp, Ct) && fc_pq_better(N, M, K, Csp, Ct) ? launch_fc_pq
+                                                                                              : launch_fc_few;
+  return launch(N, Cs, M, K, Csp, Ct, x, D, codes, bias, relu, y, stream);
 }
 
 }  // namespace qcnn

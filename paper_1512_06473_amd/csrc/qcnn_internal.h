@@ -243,6 +243,11 @@ bool fc_few_better(int N, int Cs, int M, int K, int Csp, int Ct);
 hipError_t launch_fc_few(int N, int Cs, int M, int K, int Csp, int Ct, const float* x, const float* D,
                          CodeStream codes, const float* bias, int relu, float* y, hipStream_t stream);
 bool fc_relays(int N, int Cs, int M, int K, int Csp, int Ct);
+// Of the layers past fc_tiled's K or C's, those of few subspaces and many images
+// (fc_gather.hip).
+bool fc_pq_better(int N, int M, int K, int Csp, int Ct);
+hipError_t launch_fc_pq(int N, int Cs, int M, int K, int Csp, int Ct, const float* x, const float* D, CodeStream codes,
+                        const float* bias, int relu, float* y, hipStream_t stream);
 
 // Parameter quantization (quantize.hip); objective arrays are device float64.
 hipError_t launch_pq_assign(int Ct, int Cs, int dk, const float* W, const float* D, int M, int K, int Csp,

@@ -1,12 +1,14 @@
-"""The FC kernel that reads the code stream itself (csrc/fc_few.hip), at the
-sizes where it can go wrong, against the CPU oracle (Eq. (5)).
+"""The FC kernels that read the code stream itself (csrc/fc_few.hip, and
+csrc/fc_gather.hip for few subspaces and many images), at the sizes where they
+can go wrong, against the CPU oracle (Eq. (5)).
 
 Byte codes, packed codes and a plan of either must agree bit for bit; against
 the oracle, integer data is exact and float data is within the bound of a sum
 of M products of C's terms in fp32 taken relative to the sum of magnitudes A:
 a table entry is C's fused steps, and the longest chain of lookups is M / 4 + 2
 plus one step per split (at most 256 of at most 32 groups each, never more
-than M / 32) and the bias, so (C's + M / 4 + M / 32 + 4) 2^-24 A bounds it.
+than M / 32) and the bias, so (C's + M / 4 + M / 32 + 4) 2^-24 A bounds it.  The
+other kernel adds its M lookups in one chain: (C's + M + 4) 2^-24 A.
 """
 import numpy as np
 import pytest
@@ -32,6 +34,18 @@ CASES = [
     (300, 70, 16, 32, 1030), # more blocks than CUs: no split
     (1, 2304, 4, 32, 4096),  # fc6 of AlexNet
 ]
+# few subspaces, images for 128, 256 or 512 workgroups: the two sides of each line
+GATHER = [
+    (8193, 3, 9, 32, 3),     # 129 workgroups
+    (8200, 4, 9, 32, 3),     # 129 workgroups, past 3 subspaces: fc_few
+    (16383, 32, 16, 16, 7),  # 256 workgroups, the last image missing
+    (16383, 33, 16, 16, 7),
+    (8131, 16, 16, 16, 257), # two channel blocks, 256 workgroups
+    (16321, 17, 16, 16, 257),
+    (16321, 8, 4, 200, 300),
+    (32769, 2, 16, 256, 65), # 513 workgroups, byte codes
+    (65535, 30, 9, 33, 2),   # 1024 workgroups, 64 channels or fewer
+]
 
 
 @pytest.fixture(scope="module")
@@ -56,11 +70,11 @@ def bits(t):
 
 
 @pytest.mark.parametrize("integer", [False, True])
-@pytest.mark.parametrize("case", CASES, ids=[str(c) for c in CASES])
+@pytest.mark.parametrize("case", CASES + GATHER, ids=str)
 def test_fc_few(api, dev, oracle, case, integer):
     N, M, Csp, K, Ct = case
     print("fc few", case, integer, flush=True)
-    rng = np.random.Generator(np.random.PCG64(9100 + CASES.index(case)))
+    rng = np.random.Generator(np.random.PCG64(9100 + (CASES + GATHER).index(case)))
     x, D, codes = wl.random_fc(rng, N, M * Csp, Ct, Csp, K, integer=integer)
     bias = rng.integers(-3, 4, size=Ct).astype(np.float32)
     relu = N % 2 == 0
@@ -77,7 +91,7 @@ def test_fc_few(api, dev, oracle, case, integer):
     assert np.array_equal(bits(y), bits(api.fc_forward(off, Dd, cd, bd, relu)))
     ref, A = oracle.fc_lut(x, D, codes, bias=bias, relu=relu, with_bound=True)
     err = np.abs(y.cpu().numpy().astype(np.float64) - ref)
-    tol = 0 if integer else (Csp + M / 4 + M / 32 + 4) * 2.0 ** -24
+    tol = 0 if integer else (Csp + (M if case in GATHER else M / 4 + M / 32) + 4) * 2.0 ** -24
     assert np.all(err <= tol * A), float(err.max())
     plan.close()
 
