@@ -58,6 +58,9 @@
 // up to 1.4 times the table kernel's error.
 #include <stdio.h>
 #include <stdlib.h>
+#include <string.h>
+
+#include <new>
 
 #include "qcnn_internal.h"
 
@@ -874,11 +877,15 @@ __global__ __launch_bounds__(256) void dense_weights_kernel(const float* __restr
   }
 }
 
+}  // namespace
+
 struct DensePlan {
   DenseParams p;
   int TW, IT;
   size_t lds, weight_bytes, partial_bytes;
 };
+
+namespace {
 
 // Weights read ahead past a tile's last unit: three steps of up to 2 groups
 // (and one unit where the last chunk has none for a group).
@@ -916,7 +923,7 @@ bool set_window(const ConvShape& s, DenseParams* p) {
   return p->rows != 0;
 }
 
-bool make_plan(const ConvShape& s, DensePlan* out) {
+bool plan_layer(const ConvShape& s, DensePlan* out) {
   if ((long long)s.N * s.Cs * s.H * s.W * 4 > (1LL << 31) - 1) return false;  // 32-bit buffer offsets
   DenseParams p{};
   p.N = s.N; p.Cs = s.Cs; p.H = s.H; p.W = s.W; p.M = s.M; p.K = s.K; p.Csp = s.Csp; p.Ct = s.Ct;
@@ -987,6 +994,21 @@ bool make_plan(const ConvShape& s, DensePlan* out) {
   out->TW = TW;
   out->IT = std::max(2, items);
   return true;
+}
+
+// The plan of a layer.  A call asks for it several times (the dispatch, the
+// workspace, the launch; 1.4 us each): the thread's last answer is kept, by the
+// shape's value.
+bool make_plan(const ConvShape& s, DensePlan* out) {
+  static thread_local ConvShape last{};  // N = 0: no layer
+  static thread_local bool ok = false;
+  static thread_local DensePlan plan;
+  if (memcmp(&s, &last, sizeof s) != 0) {
+    ok = plan_layer(s, &plan);
+    last = s;
+  }
+  if (ok) *out = plan;
+  return ok;
 }
 
 template <int TW, int IT>
@@ -1101,11 +1123,25 @@ hipError_t launch_conv_dense_weights(const ConvShape& s, const float* D, CodeStr
   return launch_weights(pl, D, codes, w, stream);
 }
 
+DensePlan* conv_dense_plan_new(const ConvShape& s) {
+  DensePlan* pl = new (std::nothrow) DensePlan;
+  if (pl && !make_plan(s, pl)) {
+    delete pl;
+    pl = nullptr;
+  }
+  return pl;
+}
+
+void conv_dense_plan_delete(DensePlan* pl) { delete pl; }
+
 hipError_t launch_conv_dense(const ConvShape& s, const float* x, const float* D, CodeStream codes, const char* w,
                              const float* bias, int relu, float* y, hipStream_t stream, const Workspace* ws,
-                             const PoolSpec* pool) {
+                             const PoolSpec* pool, const DensePlan* plan) {
   DensePlan pl;
-  if (!make_plan(s, &pl)) return hipErrorInvalidConfiguration;
+  if (plan)
+    pl = *plan;
+  else if (!make_plan(s, &pl))
+    return hipErrorInvalidConfiguration;
   pl.p.relu = relu;
   const size_t wb = w ? 0 : up256(pl.weight_bytes), pb = up256(pl.partial_bytes);
   const size_t full = pool ? (size_t)s.N * s.Ct * s.Ho * s.Wo * sizeof(float) : 0;

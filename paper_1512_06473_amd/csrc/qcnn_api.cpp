@@ -404,6 +404,7 @@ struct qcnn_plan {
   const float* D;
   const float* bias;
   const uint8_t* codes;
+  qcnn::DensePlan* dense;  // kind 3: the kernel's plan
 };
 
 namespace {
@@ -488,13 +489,18 @@ qcnn_status qcnn_conv_plan_create(int N, int C_s, int H, int W, const float* cod
   proto.nx = c.nx;
   proto.ny = c.ny;
   const ConvShape sh = c.sh;
-  if (dense)  // the rebuilt weights
-    return make_plan(
+  if (dense) {  // the rebuilt weights
+    proto.dense = qcnn::conv_dense_plan_new(sh);
+    if (!proto.dense) return QCNN_ERR_HIP;
+    s = make_plan(
         proto, codebooks, c.nd, codes, c.nc, c.cb, qcnn::conv_dense_weight_bytes(sh),
         [&](const qcnn::CodeStream& cs, uint8_t* out) {
           return qcnn::launch_conv_dense_weights(sh, codebooks, cs, reinterpret_cast<char*>(out), st);
         },
         bias, plan, st);
+    if (s != QCNN_OK) qcnn::conv_dense_plan_delete(proto.dense);
+    return s;
+  }
   return make_plan(
       proto, codebooks, c.nd, codes, c.nc, c.cb, proto.relaid ? qcnn::conv_flat_code_bytes(sh) : 0,
       [&](const qcnn::CodeStream& cs, uint8_t* out) { return qcnn::launch_conv_flat_codes(sh, cs, out, st); }, bias,
@@ -551,7 +557,7 @@ qcnn_status qcnn_plan_forward(const qcnn_plan* plan, const float* x, float* y, v
   const qcnn::PoolSpec* pool = plan->pooled ? &plan->pool : nullptr;
   if (plan->kind == 3)
     return hip_status(qcnn::launch_conv_dense(sh, x, plan->D, cs, reinterpret_cast<const char*>(plan->codes),
-                                              plan->bias, plan->relu, y, st, nullptr, pool));
+                                              plan->bias, plan->relu, y, st, nullptr, pool, plan->dense));
   if (plan->relaid)
     return hip_status(qcnn::launch_conv_flat_relaid(sh, x, plan->D, plan->codes, plan->bias, plan->relu, y, st, pool));
   if (pool)
@@ -569,6 +575,7 @@ qcnn_status qcnn_plan_destroy(qcnn_plan* plan) {
   if (e == hipSuccess) e = hipFree(plan->mem);
   if (cur != plan->device) (void)hipSetDevice(cur);
   if (e != hipSuccess) return QCNN_ERR_HIP;
+  qcnn::conv_dense_plan_delete(plan->dense);
   delete plan;
   return QCNN_OK;
 }

@@ -153,6 +153,8 @@ size_t conv_half_workspace(const ConvShape& s);
 hipError_t launch_conv_half(const ConvShape& s, const float* x, const float* D, CodeStream codes,
                             const float* bias, int relu, float* y, hipStream_t stream, const Workspace* ws);
 
+struct DensePlan;
+
 // Implicit GEMM on the fp16 matrix cores with weights rebuilt from the
 // codebooks (conv_dense.hip).  The weights are made by
 // launch_conv_dense_weights into conv_dense_weight_bytes(s) bytes (once per
@@ -169,7 +171,11 @@ hipError_t launch_conv_dense_weights(const ConvShape& s, const float* D, CodeStr
 // D and codes are only read when w is null.  With `pool`, y is the pooled map.
 hipError_t launch_conv_dense(const ConvShape& s, const float* x, const float* D, CodeStream codes, const char* w,
                              const float* bias, int relu, float* y, hipStream_t stream, const Workspace* ws,
-                             const PoolSpec* pool = nullptr);
+                             const PoolSpec* pool = nullptr, const DensePlan* plan = nullptr);
+// The host-side plan that launch_conv_dense makes for a layer, to be kept with
+// it (null: not supported, or no memory).
+DensePlan* conv_dense_plan_new(const ConvShape& s);
+void conv_dense_plan_delete(DensePlan* plan);
 
 // Brackets the main kernel of a call with a pair of HIP events on its
 // stream while kernel timing is switched on (qcnn_timing_enable); does
