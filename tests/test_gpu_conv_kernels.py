@@ -1,10 +1,11 @@
 """GPU parity of every conv kernel family on the shapes the default one serves.
 
-The library picks one kernel per layer (the flattened-grid kernel where it
-can tile the layer).  QCNN_CONV_KERNEL = half puts the two-table kernel
-(conv_half.hip: half-wave table rows, a builder wave, two tables in LDS)
-first, = generic forces the simple per-subspace kernel, and
-QCNN_TABLE_BUILD = valu makes the default kernel build its tables with
+The library picks one kernel per layer (the dense one for large layers, else
+the flattened-grid kernel where it can tile the layer).  QCNN_CONV_KERNEL =
+flat puts the flattened-grid kernel first (tables built on MFMA), = half the
+two-table kernel (conv_half.hip: half-wave table rows, a builder wave, two
+tables in LDS), = generic forces the simple per-subspace kernel, and
+QCNN_TABLE_BUILD = valu makes the flattened-grid kernel build its tables with
 vector fused multiply-adds instead of MFMA (the comparison variant); each is
 checked here against the CPU oracle on the headline layer (full size, float within
 the bound and integer data bit for bit) and on stride-1 edge shapes (ragged
@@ -47,9 +48,9 @@ def dev():
     return torch.device("cuda:0")
 
 
-@pytest.fixture(params=["half", "generic", "valu"])
+@pytest.fixture(params=["flat", "half", "generic", "valu"])
 def kernel(request, monkeypatch):
-    if request.param == "valu":  # the default kernel with its tables built on the vector ALUs
+    if request.param == "valu":  # the flattened-grid kernel with its tables built on the vector ALUs
         monkeypatch.delenv("QCNN_CONV_KERNEL", raising=False)
         monkeypatch.setenv("QCNN_TABLE_BUILD", "valu")
     else:

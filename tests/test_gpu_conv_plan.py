@@ -5,11 +5,13 @@ A plan's forward must equal the per-call entry point with the same
 arguments bit for bit: qcnn_conv_forward without pooling, and
 qcnn_conv_pool_forward with it (both are compared with the CPU oracle's
 Eq. (7) in their own test files; one case here is also compared with the
-oracle directly).  Layers cover the flat kernel with and without subspace
-splits (the split sum, the pooled split sum, a full map pooled after an
-unsplit layer), the strided and row-group layouts, and layers that other
-kernels run (C'_s = 16, K = 256, and the kernel forced at creation through
-QCNN_CONV_KERNEL), where the plan keeps a copy of the caller's codes.
+oracle directly).  With the flat kernel forced, layers cover it with and
+without subspace splits (the split sum, the pooled split sum, a full map
+pooled after an unsplit layer) and its strided and row-group layouts; by
+default the larger of them run the dense kernel, whose plan keeps the rebuilt
+weights.  Layers that the two-table and generic kernels run (C'_s = 16, K =
+256, and those forced at creation through QCNN_CONV_KERNEL) keep a copy of
+the caller's codes.
 """
 import numpy as np
 import pytest
@@ -74,7 +76,7 @@ def bits(t):
     return t.cpu().numpy().view(np.uint32)
 
 
-@pytest.mark.parametrize("kernel", ["default", "half", "generic"])
+@pytest.mark.parametrize("kernel", ["default", "flat", "dense", "half", "generic"])
 @pytest.mark.parametrize("integer", [False, True])
 @pytest.mark.parametrize("case", CASES, ids=[str(c[:10]) for c in CASES])
 def test_plan_equals_per_call(api, dev, monkeypatch, case, integer, kernel):

@@ -8,10 +8,11 @@ Two references for every case:
 * the CPU oracle's conv (Eq. (7)) with float64 window maxima: within the
   window maximum of the conv's bound (|max a - max b| <= max |a - b|), and
   bit for bit on integer data.
-Layers whose subspaces the flat kernel splits over workgroups (small
-batches, AlexNet conv2 and conv5 shapes) take the pooled split-sum kernel;
-the others (conv1's strided layout at one split, the two-table and the
-generic kernels) pool a full map in the workspace.
+With the flat kernel forced, layers whose subspaces it splits over
+workgroups (small batches, AlexNet conv2 and conv5 shapes) take the pooled
+split-sum kernel; the others (conv1's strided layout at one split, the
+two-table and the generic kernels, and the dense kernel, which conv2 and
+conv5 run by default) pool a full map in the workspace.
 """
 import numpy as np
 import pytest
@@ -51,7 +52,7 @@ def api():
     return a
 
 
-@pytest.fixture(params=["default", "half", "generic"])
+@pytest.fixture(params=["default", "flat", "dense", "half", "generic"])
 def kernel(request, monkeypatch):
     if request.param == "default":
         monkeypatch.delenv("QCNN_CONV_KERNEL", raising=False)

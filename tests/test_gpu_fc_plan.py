@@ -5,8 +5,9 @@ A plan's forward must equal qcnn_fc_forward with the same arguments bit for
 bit (qcnn_fc_forward itself is compared with the CPU oracle's Eq. (5) in
 test_gpu_parity.py; one case here is also compared with the oracle).
 Layers cover the tiled FC kernel with and without splits over subspaces and
-layers the generic FC kernel runs (K > 64, C'_s > 8), where the plan keeps
-a copy of the caller's codes.
+layers of the kernel that reads the code stream itself (few images or few
+subspaces; K > 64, C'_s > 8), where the plan keeps a copy of the caller's
+codes.
 """
 import numpy as np
 import pytest
@@ -23,10 +24,12 @@ CASES = [
     (128, 9216, 4096, 4, 32, False, False),   # AlexNet fc6 shape at the benchmark's batch
     (64, 4096, 1000, 1, 16, True, False),     # fc8 setting: C's = 1, K = 16
     (64, 4096, 4096, 4, 32, True, True),      # fc7 at N = 64
-    (5, 96, 40, 4, 64, True, True),           # a few images, ragged C_t
-    (33, 128, 70, 8, 16, False, True),        # C's = 8
-    (16, 256, 48, 4, 128, True, False),       # K = 128: the generic FC kernel
-    (7, 192, 24, 16, 32, False, False),       # C's = 16: the generic FC kernel
+    (5, 96, 40, 4, 64, True, True),           # a few images, ragged C_t: the code stream
+    (33, 128, 70, 8, 16, False, True),        # C's = 8, the same
+    (16, 256, 48, 4, 128, True, False),       # K = 128, the same
+    (7, 192, 24, 16, 32, False, False),       # C's = 16, the same
+    (1000, 68, 1030, 4, 48, True, True),      # tiled, unsplit; the last phase holds one subspace
+    (515, 136, 2301, 8, 64, False, False),    # tiled, unsplit, C's = 8, K = 64
 ]
 
 

@@ -244,6 +244,10 @@ FC_EDGE = [
     (96, 640, 300, 8, 64),    # K = 64 (four codeword blocks), C's = 8
     (200, 192, 70, 4, 48),    # K = 48, two image blocks, ragged channels
     (128, 68, 40, 4, 32),     # M = 17: the last phase holds one subspace
+    # tiled without splits (the smaller ones above run fc_few)
+    (1000, 68, 1030, 4, 48),  # the same on 16 image blocks, K = 48
+    (4095, 40, 70, 5, 48),    # C's = 5, the last image missing
+    (1003, 8, 1029, 1, 16),   # C's = 1
 ]
 
 

@@ -7,9 +7,10 @@ buffer), so the outputs must agree bit for bit.  Each case makes two
 allocation-free calls in a row, the second on a smaller input, so that the
 second runs over the first one's leftovers in the shared scratch; the
 smaller call is also held to the oracle's bound (Eq. (7)).  One case per
-conv kernel family: the flattened-grid kernel with split partial sums (the
-AlexNet conv3 layer at N = 32), the two-table kernel, and the generic
-kernel (stride 4, no temporaries).  A layer too large for the scratch is
+conv kernel family: the flattened-grid kernel with split partial sums and
+the dense kernel with its rebuilt weights and the sums of tiles cut into runs
+(both the AlexNet conv3 layer at N = 32), the two-table kernel, and the
+generic kernel (stride 4, no temporaries).  A layer too large for the scratch is
 refused with QCNN_ERR_WORKSPACE and leaves the output untouched.
 """
 import numpy as np
@@ -56,19 +57,17 @@ def layer(rng, dev, shape, integer=False):
 CASES = [
     # (kernel family forced, big shape, smaller shape):
     # N, Cs, H, W, Ct, dk, stride, pad, C's, K
-    (None, (32, 256, 13, 13, 384, 3, 1, 1, 4, 128), (4, 256, 13, 13, 384, 3, 1, 1, 4, 128)),
+    ("flat", (32, 256, 13, 13, 384, 3, 1, 1, 4, 128), (4, 256, 13, 13, 384, 3, 1, 1, 4, 128)),
+    ("dense", (32, 256, 13, 13, 384, 3, 1, 1, 4, 128), (4, 256, 13, 13, 384, 3, 1, 1, 4, 128)),
     ("half", (8, 64, 13, 13, 96, 3, 1, 1, 4, 64), (2, 32, 9, 11, 40, 3, 1, 1, 4, 64)),
     ("generic", (4, 3, 67, 67, 32, 11, 4, 0, 3, 64), (1, 3, 35, 35, 20, 11, 4, 0, 3, 64)),
 ]
 
 
-@pytest.mark.parametrize("kernel,big,small", CASES, ids=["flat", "half", "generic"])
+@pytest.mark.parametrize("kernel,big,small", CASES, ids=["flat", "dense", "half", "generic"])
 @pytest.mark.parametrize("integer", [False, True])
 def test_noalloc_equals_conv_forward(dev, oracle, monkeypatch, kernel, big, small, integer):
-    if kernel is not None:
-        monkeypatch.setenv("QCNN_CONV_KERNEL", kernel)
-    else:
-        monkeypatch.delenv("QCNN_CONV_KERNEL", raising=False)
+    monkeypatch.setenv("QCNN_CONV_KERNEL", kernel)
     rng = np.random.Generator(np.random.PCG64(sum(big) + integer))
     calls = [layer(rng, dev, big, integer), layer(rng, dev, small, integer)]
     print("noalloc", kernel, big, small, integer, flush=True)
@@ -118,13 +117,16 @@ def test_noalloc_refuses_layers_beyond_its_scratch(dev):
     assert bool((y == 7.0).all())
 
 
-def test_noalloc_under_graph_capture(dev):
+@pytest.mark.parametrize("kernel", ["flat", "dense"])
+def test_noalloc_under_graph_capture(dev, monkeypatch, kernel):
     """The allocation-free forward recorded into a HIP graph (the callers it
     is for): each replay, with eager work and a synchronization between
     replays and a new input copied into the captured input buffer each time,
     equals the eager qcnn_conv_forward on that input bit for bit.  The layer
     is split over workgroups, so the captured work includes the code
-    re-layout, the gather kernel and the split-sum kernel."""
+    re-layout, the gather kernel and the split-sum kernel, or the weights'
+    rebuild, the product kernel and the sum of the runs."""
+    monkeypatch.setenv("QCNN_CONV_KERNEL", kernel)
     rng = np.random.Generator(np.random.PCG64(10))
     c = layer(rng, dev, (4, 256, 13, 13, 384, 3, 1, 1, 4, 128))
     y = torch.empty(c["shape"], device=dev)
