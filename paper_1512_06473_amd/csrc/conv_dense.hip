@@ -12,12 +12,23 @@
 // win wherever the layer fills the tiles.
 //
 // Precision.  Each fp32 factor v is scaled by a power of two and split into
-// two fp16 values, v 2^e = h + l 2^-11 (round to nearest: h has 11 bits, l
-// the next 11 or more, |v 2^e - h - l 2^-11| <= 2^-24 |v 2^e|).  A product is
-// h h' + (h l' + l h') 2^-11, the left-out l l' being below 2^-24 of it; the
-// MFMA adds the exact fp16 products in fp32.  h h' and the cross terms have
-// accumulators of their own, so that scaling l by 2^11 keeps it out of the
-// fp16 subnormals: a factor keeps its 22 bits down to 2^-28 of the largest one.
+// two fp16 values, v 2^e = h + l 2^-11 + r, each rounded to nearest: h has 11
+// bits, l the next 11, and with l's sign a factor keeps 23 of its 24 bits,
+// |r| <= 2^-23 |v 2^e| (0 for three values in four).  A product is
+// h h' + (h l' + l h') 2^-11 (the split of a precise product into short ones,
+// T. J. Dekker, "A floating-point technique for extending the available
+// precision", 1971); the left-out l l' is at most 2^-22 of it, so a product is
+// off by 2^-21 of itself at worst.  The MFMA adds the exact fp16 products in
+// fp32.  What decides is the sums: the errors of the products average out, and
+// the two-level sums here (fold(), the runs' sums in float64) are rounded less
+// often than a chain of table entries.  Measured over 300 random layers that
+// the dispatch sends here, against float64: 0.29 to 0.99 times the table
+// kernel's error, median 0.62.  With l l' as a fourth product: 5 % less error, 10
+// to 18 % more time.
+//
+// h h' and the cross terms have accumulators of their own, so that scaling l by
+// 2^11 keeps it out of the fp16 subnormals: the largest input lies at 2^14 to
+// 2^15, and a factor down to 2^-27 of that keeps its 23 bits, down to 2^-28 22.
 // Smaller inputs -- any one: the weights on the large values beside it may be
 // zero, and the result is then its products alone -- are left to passes of their
 // own over the tile (its chunks that hold any), one per 28 binades, whose sums
@@ -46,16 +57,16 @@
 // the lanes' rows; the fp32 -> fp16 split happens on the way into LDS,
 // double-buffered behind the previous chunk's products.
 //
-// Bound and measured (MI355X).  With no staging at all the kernel takes 0.78
-// of its time (VGG conv3 shape, 16 x 256 x 56 x 56 -> 256, 3x3: 194 -> 156 us with
-// 128-position tiles), without weight loads 0.97, without LDS reads 1.0; the
-// matrix cores are busy about half the time at the 1.96 GHz they run at under
-// this load.  The rest is each tile's start (scale exchange and first loads,
-// 5 us) and end (2 us).  Against the table kernels, through a plan: AlexNet
-// conv3 shape, 32 images: 84 -> 47 us; conv2 with its max-pool, 37 images: 307 ->
-// 122 us; VGG conv3 shape per call: 273 -> 219 us (0.27 of the fp16 peak).  One
-// workgroup of 8 waves per CU instead of two of 4: 55 us, 252 us; 128-position tiles without the fold: 51 us, 207 us at
-// up to 1.4 times the table kernel's error.
+// Bound and measured (MI355X).  By the SQ counters, VGG conv3 shape (16 x 256 x
+// 56 x 56 -> 256, 3x3): the matrix cores are busy 37 % of the kernel's clocks, the
+// LDS 28 % (12 of them conflicts), waves wait a third of theirs; AlexNet conv3
+// shape, 32 images, where every tile is a piece of a longer one: 26 %, 20 % (9).
+// So no unit is near its rate; the chain of each tile's start (scale exchange,
+// first loads, 5 us) and end (2 us) is what two workgroups per CU overlap only in
+// part.  Against the table kernels, through a plan: AlexNet conv3 shape, 32
+// images: 84 -> 47 us; conv2 with its max-pool, 37 images: 307 -> 123 us; VGG conv3
+// shape per call: 273 -> 215 us (0.27 of the fp16 peak).  One workgroup of 8 waves
+// per CU instead of two of 4: 55 us, 252 us.
 #include <stdio.h>
 #include <stdlib.h>
 #include <string.h>
@@ -109,7 +120,6 @@ constexpr int kNT = 96;  // positions per tile
 constexpr int kCF = kNT / 32;
 constexpr int kSumStride = kNT + 8;  // floats per channel of a tile's sums in LDS
 constexpr int kCUs = 256;
-constexpr int kFold = 9;
 constexpr int kBand = 28;     // binades of one range band: scaled magnitudes 2^-14 .. 2^14 (2^15 in band 0)
 constexpr int kMaxBands = 2;  // bands after the first that a tile takes in split form
 constexpr uint32_t kOOB = 0x80000000u;  // buffer offset past every input: reads 0
@@ -412,12 +422,18 @@ __device__ __forceinline__ bool products(const TileState<IT, XP>& ts, int tgrp, 
   const int lane_k = (lane >> 5) * 16;
   const int tap_step = p.pitch - p.SUB * 64, row_step = (p.PW - p.kw) * p.pitch;
   int parity = 0;  // LDS buffer of the current chunk
-  int folded = 0;  // steps since the last fold
-  // The MFMA adds 8 products at a time: the running sum is rounded K / 8
-  // times.  Folding it into a second one every kFold units or more keeps the
-  // chains short (96 -> 256 channels, 5x5, 64 images, relative error against
-  // float64: 2.8e-7 -> 1.5e-7; the table kernel's is 2.1e-7).
+  int since = 0;   // steps since the last fold
+  // The MFMA adds 8 products at a time: the running sum is rounded twice a
+  // step.  Folding it into a second one every few steps keeps both chains
+  // short, about 2 fold_at and u1 - u0 over fold_at roundings long (96 -> 256
+  // channels, 5x5, 64 images, relative error against float64: 2.8e-7 without,
+  // 1.5e-7 with a fold per chunk of 25 steps, 1.2e-7 with one every 9 or 10;
+  // the table kernel's is 2.1e-7.  Every 6 instead of 9 steps: 1.21e-7 -> 1.18e-7
+  // for 128 -> 381 channels, 3x3, 72 steps, but 1.36e-7 -> 1.39e-7 and 1 % of the
+  // time for 256 -> 256, 144 steps; every 3: 1.59e-7 and 4 %).
+  const int fold_at = u1 - u0 <= 96 * KG ? 6 : 9;
   auto fold = [&]() {
+    since = 0;
 #pragma unroll
     for (int j = 0; j < kCF; ++j)
 #pragma unroll
@@ -486,9 +502,12 @@ __device__ __forceinline__ bool products(const TileState<IT, XP>& ts, int tgrp, 
         step(0);
         step(1);
         step(2);
+        since += 3;
+        if (since >= fold_at) fold();
       }
       while (u < u_end) {  // at most two
         step(0);
+        ++since;
         const h8 th = wh[0], tl = wl[0];
         wh[0] = wh[1];
         wl[0] = wl[1];
@@ -498,11 +517,7 @@ __device__ __forceinline__ bool products(const TileState<IT, XP>& ts, int tgrp, 
         wl[2] = tl;
       }
       off -= p.dk * p.PW * p.pitch;  // from past the last tap to the next chunk's first
-      folded += u_end - c * upc;
-      if (folded >= kFold * KG) {
-        folded = 0;
-        fold();
-      }
+      if (since >= fold_at) fold();
       placed = true;
     } else {
       placed = false;
@@ -769,20 +784,20 @@ __global__ __launch_bounds__(2 * kNT) void dense_reduce_kernel(const float* __re
   const int pl = row / p.Ho, yo = row - pl * p.Ho;
   const int n = pl / p.S, xo = (pl - n * p.S) * p.sw + xl;
   if (q >= p.Q || xo >= p.Wo) return;
-  float s[8];
+  double s[8];  // (in fp32 the runs were another chain of up to 30 roundings)
 #pragma unroll
-  for (int i = 0; i < 8; ++i) s[i] = 0.f;
+  for (int i = 0; i < 8; ++i) s[i] = 0.0;
   for (int w = wf; w <= wl; ++w) {
     const size_t slot = w + blockIdx.x;
     const float* src = partial + slot * (MT * kNT) + tl * kNT + threadIdx.x % kNT;
 #pragma unroll
-    for (int i = 0; i < 8; ++i) s[i] += src[i * kNT];
+    for (int i = 0; i < 8; ++i) s[i] += (double)src[i * kNT];
   }
 #pragma unroll
   for (int i = 0; i < 8; ++i) {
     const int t = tb * MT + tl + i;
     if (t < p.Ct) {
-      float v = s[i] + (bias ? bias[t] : 0.f);
+      float v = (float)(s[i] + (bias ? (double)bias[t] : 0.0));
       if (p.relu) v = fmaxf(v, 0.f);
       y[(((size_t)n * p.Ct + t) * p.Ho + yo) * p.Wo + xo] = v;
     }
@@ -1070,9 +1085,9 @@ bool conv_dense_supported(const ConvShape& s) {
 // entries the layer's table kernel adds up one after the other (0: none can
 // tile it but the generic kernel).
 //   * Precision: the table kernels' relative error grows with the square root
-//     of that chain (9 to 18 entries 1.0e-7, 72 1.5e-7, 144 2.1e-7, 288
-//     3.1e-7), this one's stays at 1.2e-7 to 1.6e-7 from 500 to 5000 products:
-//     not larger from about 48 entries on.
+//     of that chain (9 to 18 entries 1.0e-7, 48 1.1e-7 to 1.3e-7, 72 1.5e-7, 144
+//     2.1e-7, 288 3.1e-7), this one's stays at 0.9e-7 to 1.4e-7 from 200 to 5000
+//     products: not larger from 48 entries on (0.99 of it there, 0.9 at 50).
 //   * Time: the generic table kernel is slower by a factor of 10 or more
 //     (256 channels 13 x 13, 3x3, K = 256, 8 images: 1841 us against 28 us).  Against
 //     the other two a call has about 6 us more to win back, in a layer of at

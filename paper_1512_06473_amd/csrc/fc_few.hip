@@ -21,8 +21,8 @@
 //
 // Bound by the chain codeword loads -> table -> code loads -> lookups with 4 to
 // 8 waves per CU and by the two launches, not by bytes (fc6 for one image: 5.9
-// MB of packed codes, 1 us).  fc6, one image, packed codes per call: 68 us with
-// fc_tiled and its re-layout, 18 us here, of which the kernel is 12 (23 with
+// MB of packed codes, 1 us).  fc6, one image, packed codes per call: 64 us with
+// fc_tiled and its re-layout, 16 us here, of which the kernel is 12 (23 with
 // one table entry per lane in flight) and the sum of the splits 3.  The kernel
 // that took K > 64 and C's > 8 before read each code for 64 lanes: 1024 to
 // 1024, C's = 16, one image 221 -> 12 us, 128 images 240 -> 17 us; 25088 to

@@ -179,6 +179,64 @@ def test_dense_range_bands(dev, oracle, shape, power, what):
     assert np.array_equal(plan(T(x, dev)).cpu().numpy(), y)
 
 
+def _exact(x, D, codes, s, p):
+    """The dense correlation with the rebuilt weights, float64 on the GPU."""
+    W = torch.stack([D[m][codes[..., m].long()] for m in range(D.shape[0])], -2).flatten(-2).permute(0, 3, 1, 2)
+    dk = codes.shape[1]
+    out = [(n - dk + 2 * p) // s + 1 for n in x.shape[2:]]
+    cols = torch.nn.functional.unfold(x.double(), dk, padding=p, stride=s)
+    Wm = W.reshape(W.shape[0], -1).double().contiguous()
+    return torch.stack([Wm @ c for c in cols]).reshape(x.shape[0], -1, *out)
+
+
+@pytest.mark.parametrize("shape", [
+    # N, Cs, H, W, Ct, dk, stride, pad, Csp, K: chains of 48 to 64 table entries
+    (47, 40, 20, 20, 324, 5, 1, 2, 8, 128),   # 25 steps a chunk, whole tiles and pieces
+    (9, 232, 8, 8, 131, 5, 1, 2, 8, 128),     # tiles of many pieces
+    (22, 160, 12, 12, 56, 5, 1, 2, 8, 128),   # two reduction groups
+    (28, 140, 14, 12, 356, 3, 2, 1, 4, 64),   # stride 2
+    (41, 396, 49, 48, 156, 1, 1, 0, 4, 16),   # 1x1
+], ids=str)
+def test_dense_error_not_above_the_tables(dev, shape, monkeypatch):
+    """Layers with the shortest chains of table entries that still go to this
+    kernel: its relative error (2-norm, against float64, mean of three inputs) is
+    not larger than the table kernel's."""
+    from paper_1512_06473_amd import api
+    N, Cs, H, W, Ct, dk, s, p, Csp, K = shape
+    err = {}
+    for seed in range(3):
+        g = torch.Generator(device=dev)
+        g.manual_seed(seed)
+        x = torch.randn((N, Cs, H, W), generator=g, device=dev).clamp_min_(0.0)
+        D = 0.05 * torch.randn((Cs // Csp, K, Csp), generator=g, device=dev)
+        codes = torch.randint(0, K, (Ct, dk, dk, Cs // Csp), generator=g, device=dev, dtype=torch.uint8)
+        ref = _exact(x, D, codes, s, p)
+        for kernel in ("dense", "flat"):
+            monkeypatch.setenv("QCNN_CONV_KERNEL", kernel)
+            y = api.conv_forward(x, D, codes, s, p).double()
+            err[kernel] = err.get(kernel, 0.0) + float((y - ref).norm() / ref.norm()) / 3.0
+    assert err["dense"] <= err["flat"], err
+
+
+@pytest.mark.parametrize("Cs", [16, 64])
+@pytest.mark.parametrize("tail", [4093, 4097, 4095, 2049, 1])
+def test_dense_significands(dev, Cs, tail):
+    """Factors that all lose the most in the split (every significand 1 + tail
+    2^-23): a factor keeps 23 bits (2^-23 of it), and the product of the two low
+    parts is left out (2^-22), 2^-21 of a product in all.  On top of that the sums
+    of Cs products: two roundings a step of 16 channels, three folds and joins,
+    the MFMA's own no finer than 2^-23 each."""
+    rng = np.random.Generator(np.random.PCG64(tail))
+    x, D, codes = wl.random_conv(rng, 2, Cs, 9, 11, 70, 1, 1, 0, 4, 32)
+    v = np.float32(1.0 + tail * 2.0 ** -23)
+    x = (v * np.float32(2.0) ** rng.integers(-3, 4, x.shape)).astype(np.float32)
+    D = (v * np.float32(2.0) ** rng.integers(-3, 4, D.shape)).astype(np.float32)
+    y = conv(dev, x, D, codes, 1, 0).astype(np.float64)
+    W = np.concatenate([D[m][codes[:, 0, 0, m]] for m in range(Cs // 4)], 1).astype(np.float64)
+    ref = np.einsum("tc,nchw->nthw", W, x.astype(np.float64))  # every product is positive: A = ref
+    assert np.all(np.abs(y - ref) <= (2.0 ** -21 + (2 * Cs / 16 + 3) * 2.0 ** -23) * ref)
+
+
 @pytest.mark.parametrize("where", ["x", "D", "packed rows"])
 def test_dense_non_finite(dev, where, monkeypatch):
     """Infinities and NaN reach exactly the outputs they reach through the
