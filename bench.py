@@ -454,11 +454,11 @@ def main():
             "frac_at_best_kernel": mfma_flops / (float(np.min(kl)) * 1e-3) / MFMA_F16_PEAK,
             "step_frac": mfma_flops / sec / MFMA_F16_PEAK,
             # The LDS bytes that the paper's table reads would move, over this
-            # kernel's time (it reads no table): the measure of the target.
+            # kernel's time.  It reads no table: a ratio of work, not a use of
+            # the LDS, and no measure of the table kernel's target (0.5).
             "table_read_equivalent": {"achieved_GB_s": lds_achieved / 1e9, "frac": table_frac,
                                       "step_frac": w["lds"] / sec / workmodel.LDS_PEAK_BPS,
                                       "frac_of_measured_peak": lds_achieved / lds_peak["bytes_per_s"],
-                                      "target_frac": 0.5, "target_met": bool(table_frac >= 0.5),
                                       "algorithmic_bytes_per_launch": w["lds"]},
             "kernel_launches_timed": len(kl),
             "algorithmic_flops_per_launch": mfma_flops,
@@ -477,6 +477,7 @@ def main():
     per = {}
     extra = [] if args.configs == "none" else [c for c in args.configs.split(",") if c]
     main_kernel = {"small_conv_n1": "conv_flat", "alexnet_fc6_n128": "fc_tiled", "vgg16_conv3_n16": "conv_dense"}
+    no_table = ("vgg16_conv3_n16", "alexnet_n64")  # conv layers by products (of alexnet_n64, all five)
     for cfg in extra:
         st, wlc, dc = make_step(cfg)
         steps = max(5, args.steps // (10 if cfg in ("vgg16_conv3_n16", "alexnet_n64") else 1))
@@ -487,13 +488,14 @@ def main():
         wc = work_of(wlc)
         s_ = m * 1e-3
         row = {"ms_per_step": m, "images_s": wlc.N / s_, "effective_dense_gflops": wc["dense_flops"] / s_ / 1e9,
-               "lds_frac": wc["lds"] / s_ / workmodel.LDS_PEAK_BPS,
+               # the dense conv kernel reads no table: its layers' table bytes are an equivalent
+               "table_read_equivalent_frac" if cfg in no_table else "lds_frac": wc["lds"] / s_ / workmodel.LDS_PEAK_BPS,
                "hbm_frac": wc["hbm"] / s_ / workmodel.HBM_PEAK_BPS, "steps": steps,
                "step_ms_stats": stats(step_times(st, nlc, 1)),
                "main_kernels_ms_per_step": float(np.sum(kl)) / nlc, "main_kernel_launches_per_step": per_step}
         if cfg in main_kernel:
             row["kernel_us_stats"] = stats(kl, 1e3)
-            row["kernel_lds_frac"] = wc["lds"] / (float(np.mean(kl)) * 1e-3) / workmodel.LDS_PEAK_BPS
+            row["kernel_table_read_equivalent_frac" if cfg in no_table else "kernel_lds_frac"] = wc["lds"] / (float(np.mean(kl)) * 1e-3) / workmodel.LDS_PEAK_BPS
             row["traffic"] = measured_traffic("%s_%s" % (main_kernel[cfg], cfg), [main_kernel[cfg] + ".hip"])
         if cfg == "alexnet_n64":
             # Table 1 per layer: the main kernel of every PQ layer (launch order
@@ -533,17 +535,15 @@ def main():
                     kk = karr[:, ki]
                     ki += 1
                     r_["kernel_us_stats"] = stats(kk, 1e3)
-                    r_["kernel_lds_frac"] = lw.lds_bytes / (float(np.mean(kk)) * 1e-3) / workmodel.LDS_PEAK_BPS
-                    r_["layer_lds_frac"] = lw.lds_bytes / (layer_ms[i] * 1e-3) / workmodel.LDS_PEAK_BPS
+                    what = "lds_frac" if kind.startswith("fc") else "table_read_equivalent_frac"
+                    r_["kernel_" + what] = lw.lds_bytes / (float(np.mean(kk)) * 1e-3) / workmodel.LDS_PEAK_BPS
+                    r_["layer_" + what] = lw.lds_bytes / (layer_ms[i] * 1e-3) / workmodel.LDS_PEAK_BPS
                 else:
                     r_["layer_hbm_frac"] = lw.hbm_bytes / (layer_ms[i] * 1e-3) / workmodel.HBM_PEAK_BPS
                 rows.append(r_)
             row["per_layer"] = rows
             row["traffic_per_step"] = measured_traffic("alexnet_n64", ["conv_dense.hip", "fc_tiled.hip", "glue.hip"],
                                                        "hbm_bytes_per_step")
-            row["step_lds_frac"] = row["lds_frac"]
-            row["target_step_lds_frac"] = 0.35
-            row["target_met"] = bool(row["lds_frac"] >= 0.35)
             del net, xin, h
         per[cfg] = row
         del st

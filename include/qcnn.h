@@ -333,7 +333,10 @@ qcnn_status qcnn_ec_fc(const float* S, int N, int C_s, const float* T, int C_t,
  * forward's layouts): updated in place; objective (output, nullable):
  * [1 + sweeps M] float64, the error before the first step and after every
  * subspace step.  Arithmetic is float64 (a workspace of 8 N C_t H_o W_o
- * bytes plus small per-subspace arrays); normal equations solved as in
+ * bytes, partial sums of at most 128 (6144 + C_t / 16) d_k^2 C'_s bytes
+ * whatever N, 72 M (d_k^2 C'_s)^2 bytes of Gram blocks, and small arrays;
+ * where d_k^2 C'_s > 128 or the maps are large, 2 MB C'_s of partial sums
+ * and 8 M (d_k^2 C'_s)^2); normal equations solved as in
  * qcnn_ec_fc (elimination in channel order, a pivot <= 1e-12 x the largest
  * diagonal entry dropping that coordinate); a sub-codeword that no position
  * uses keeps its value; ties go to the lowest index.  Limits: C'_s <= 8,
