@@ -60,7 +60,7 @@
 // Bound and measured (MI355X).  By the SQ counters, VGG conv3 shape (16 x 256 x
 // 56 x 56 -> 256, 3x3): the matrix cores are busy 37 % of the kernel's clocks, the
 // LDS 28 % (12 of them conflicts), waves wait a third of theirs; AlexNet conv3
-// shape, 32 images, where every tile is a piece of a longer one: 26 %, 20 % (9).
+// shape, 32 images, where every tile is a piece of a longer one: 25 %, 20 % (9).
 // So no unit is near its rate; the chain of each tile's start (scale exchange,
 // first loads, 5 us) and end (2 us) is what two workgroups per CU overlap only in
 // part.  Against the table kernels, through a plan: AlexNet conv3 shape, 32
@@ -108,6 +108,7 @@ struct DenseParams {
   int rows;         // staged grid positions per tile, a multiple of 16
   int pitch;        // bytes per staged position
   int relu;
+  int fold_at;      // steps between two folds of a wave's running sums
   int per_run, extra;  // shared units per run; the first `extra` runs have one more
   FastDiv d_sw, d_Ho, d_S, d_PW, d_PH, d_upt, d_upc, d_SUB, d_kw, d_tb, d_Cs;
 };
@@ -423,15 +424,15 @@ __device__ __forceinline__ bool products(const TileState<IT, XP>& ts, int tgrp, 
   const int tap_step = p.pitch - p.SUB * 64, row_step = (p.PW - p.kw) * p.pitch;
   int parity = 0;  // LDS buffer of the current chunk
   int since = 0;   // steps since the last fold
+  const int fold_at = __builtin_amdgcn_readfirstlane(p.fold_at);  // (kept: not read again in the loop)
   // The MFMA adds 8 products at a time: the running sum is rounded twice a
   // step.  Folding it into a second one every few steps keeps both chains
-  // short, about 2 fold_at and u1 - u0 over fold_at roundings long (96 -> 256
+  // short, about 2 fold_at and steps over fold_at roundings long (96 -> 256
   // channels, 5x5, 64 images, relative error against float64: 2.8e-7 without,
   // 1.5e-7 with a fold per chunk of 25 steps, 1.2e-7 with one every 9 or 10;
   // the table kernel's is 2.1e-7.  Every 6 instead of 9 steps: 1.21e-7 -> 1.18e-7
   // for 128 -> 381 channels, 3x3, 72 steps, but 1.36e-7 -> 1.39e-7 and 1 % of the
   // time for 256 -> 256, 144 steps; every 3: 1.59e-7 and 4 %).
-  const int fold_at = u1 - u0 <= 96 * KG ? 6 : 9;
   auto fold = [&]() {
     since = 0;
 #pragma unroll
@@ -971,6 +972,7 @@ bool plan_layer(const ConvShape& s, DensePlan* out) {
   p.chunks = ceil_div(p.VC, 16 * p.SUB);
   p.upt = p.chunks * p.taps * p.SUB;
   const int TW = s.Ct <= 64 ? 2 : 4;
+  p.fold_at = p.upt <= 96 * kWaves / TW ? 6 : 9;
   const size_t sums = (size_t)32 * TW * kSumStride * 4;
   out->lds = std::max((size_t)2 * p.rows * p.pitch, sums) + 256;
   if (out->lds > kLdsBytes) return false;
