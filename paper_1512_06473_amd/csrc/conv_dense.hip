@@ -21,9 +21,9 @@
 // off by 2^-21 of itself at worst.  The MFMA adds the exact fp16 products in
 // fp32.  What decides is the sums: the errors of the products average out, and
 // the two-level sums here (fold(), the runs' sums in float64) are rounded less
-// often than a chain of table entries.  Measured over 300 random layers that
-// the dispatch sends here, against float64: 0.29 to 0.99 times the table
-// kernel's error, median 0.62.  With l l' as a fourth product: 5 % less error, 10
+// often than a chain of table entries.  Measured over 400 random layers that
+// the dispatch sends here, against float64: 0.24 to 0.97 times the table
+// kernel's error, median 0.63.  With l l' as a fourth product: 5 % less error, 10
 // to 18 % more time.
 //
 // h h' and the cross terms have accumulators of their own, so that scaling l by
@@ -60,12 +60,12 @@
 // Bound and measured (MI355X).  By the SQ counters, VGG conv3 shape (16 x 256 x
 // 56 x 56 -> 256, 3x3): the matrix cores are busy 37 % of the kernel's clocks, the
 // LDS 28 % (12 of them conflicts), waves wait a third of theirs; AlexNet conv3
-// shape, 32 images, where every tile is a piece of a longer one: 25 %, 20 % (9).
+// shape, 32 images, where every tile is cut into pieces: 26 %, 20 % (9).
 // So no unit is near its rate; the chain of each tile's start (scale exchange,
 // first loads, 5 us) and end (2 us) is what two workgroups per CU overlap only in
 // part.  Against the table kernels, through a plan: AlexNet conv3 shape, 32
-// images: 84 -> 47 us; conv2 with its max-pool, 37 images: 307 -> 123 us; VGG conv3
-// shape per call: 273 -> 215 us (0.27 of the fp16 peak).  One workgroup of 8 waves
+// images: 84 -> 47 us; conv2 with its max-pool, 37 images: 307 -> 124 us; VGG conv3
+// shape per call: 273 -> 220 us (its kernel 203 us, 0.34 of the fp16 peak).  One workgroup of 8 waves
 // per CU instead of two of 4: 55 us, 252 us.
 #include <stdio.h>
 #include <stdlib.h>
